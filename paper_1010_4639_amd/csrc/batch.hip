@@ -46,6 +46,12 @@ struct Inst {
     double tol_nb, nb, rho, alpha, sigma, rho_next, res_true, pad3;
 };
 
+// Workgroups (= dot partials) of one system at most.  Every update workgroup
+// reads all partials of its system: 1024 x R doubles stay small beside its
+// own vector elements, and 1024 workgroups of a product fill the GPU at the
+// occupancy of the slices (4 waves per SIMD).
+constexpr int kMaxSysWgs = 1024;
+
 struct WgDesc {
     int32_t sys, lead;   // system; 1 for the system's first workgroup
     int32_t rb0, rb1;    // row blocks [rb0, rb1)
@@ -417,16 +423,71 @@ __global__ __launch_bounds__(kBlock) void k_bspmm_slices(const WgDesc *__restric
     }
 }
 
-// Per instance r of this workgroup's system: sum of the system's partials
-// (fixed order), by thread r.
+// Partials of a system, summed per right-hand side by the whole workgroup, in
+// two steps so that the loads can be issued ahead of a kernel's own: thread t
+// adds the partials wg0 * R + t, + kBlock, ... (right-hand side t % R, since
+// R divides kBlock) in index order, four loads at a time; then lanes of equal
+// right-hand side by a butterfly and the waves in index order.  Every
+// workgroup of the system gets the same bits; all R sums end in sums[R].
+// (One thread per right-hand side adding the partials one by one took 220 of
+// the 227 us of an update kernel at 340 workgroups per system.)
 template <int R>
-__device__ __forceinline__ double sys_sum(const double *__restrict__ part, const WgDesc &W, int r)
+__device__ __forceinline__ double sys_partial(const double *__restrict__ part, const WgDesc &W)
 {
+    const int m = (W.wg1 - W.wg0) * R, t = threadIdx.x;
+    const double *p = part + (size_t)W.wg0 * R;
     double s = 0.0;
-    for (int w = W.wg0; w < W.wg1; ++w)
-        s += part[w * R + r];
+    for (int j = t; j < m; j += 4 * kBlock) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { // unguarded (index clamped), then selected
+            const double q = p[min(j + u * kBlock, m - 1)];
+            v[u] = j + u * kBlock < m ? q : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            s += v[u];
+    }
     return s;
 }
+
+template <int R>
+__device__ __forceinline__ void sys_sums(double s, double (&red)[kWaves][R], double (&sums)[R])
+{
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int o = 32; o >= R; o >>= 1)
+        s += __shfl_xor(s, o, 64);
+    __syncthreads();
+    if ((t & 63) < R)
+        red[t >> 6][t & 63] = s;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        double a = red[0][r];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w)
+            a += red[w][r];
+        sums[r] = a;
+    }
+}
+
+// The vector kernels take V neighbouring elements per load (a pair of
+// right-hand sides of one row where R is even: 16 bytes, aligned, since a row
+// starts at a multiple of R elements), the first kBPre loads of a thread
+// before the system's partials are summed.  A thread keeps its right-hand
+// sides, because the stride kBlock * V is a multiple of R.
+constexpr int kBPre = 4;
+template <int R>
+struct BVec {
+    static constexpr int V = R % 2 == 0 ? 2 : 1;
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+template <>
+struct BVec<1> {
+    static constexpr int V = 1;
+    typedef double type __attribute__((ext_vector_type(1)));
+};
 
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_bupdate_r(const WgDesc *__restrict__ wgs, double *__restrict__ Rv,
@@ -434,54 +495,111 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_r(const WgDesc *__restrict__
                                                       const double *__restrict__ sig_part,
                                                       double *__restrict__ rho_part)
 {
-    __shared__ double red[kWaves];
-    __shared__ double sh_alpha[R];
-    __shared__ int sh_act[R];
+    constexpr int V = BVec<R>::V;
+    typedef typename BVec<R>::type vec;
+    __shared__ double red[kWaves][R];
     const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x;
-    if (t < R) {
-        Inst *I = &inst[W.sys * R + t];
-        int a = I->status == kRun;
-        double al = 0.0;
-        if (a) {
-            const double sg = sys_sum<R>(sig_part, W, t);
-            if (!(sg > 0.0) || !isfinite(sg)) {
-                if (W.lead) {
-                    I->iters = I->k;
-                    I->sigma = sg;
-                    I->status = kBreakdown;
-                }
-                a = 0;
-            } else {
-                al = I->rho / sg;
-                if (W.lead) {
-                    I->alpha = al;
-                    I->sigma = sg;
-                    I->k = I->k + 1;
-                }
+    const vec *q = reinterpret_cast<const vec *>(Q + (size_t)W.i0 * R);
+    vec *rv = reinterpret_cast<vec *>(Rv + (size_t)W.i0 * R);
+    const int m = (W.i1 - W.i0) * (R / V);
+    int status[R];
+    double rho[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        status[r] = inst[W.sys * R + r].status;
+        rho[r] = inst[W.sys * R + r].rho;
+    }
+    vec qv[kBPre], v[kBPre];
+#pragma unroll
+    for (int u = 0; u < kBPre; ++u) { // (a workgroup has at least one row: m >= 1)
+        const int j = min(t + u * kBlock, m - 1);
+        qv[u] = q[j];
+        v[u] = rv[j];
+    }
+    double sg[R];
+    sys_sums<R>(sys_partial<R>(sig_part, W), red, sg);
+    double al[R];
+    bool act[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        act[r] = status[r] == kRun;
+        al[r] = 0.0;
+        if (!act[r])
+            continue;
+        Inst *I = &inst[W.sys * R + r];
+        const bool bad = !(sg[r] > 0.0) || !isfinite(sg[r]);
+        if (bad) {
+            act[r] = false;
+            if (W.lead && t == 0) {
+                I->iters = I->k;
+                I->sigma = sg[r];
+                I->status = kBreakdown;
+            }
+        } else {
+            al[r] = rho[r] / sg[r];
+            if (W.lead && t == 0) {
+                I->alpha = al[r];
+                I->sigma = sg[r];
+                I->k = I->k + 1;
             }
         }
-        sh_alpha[t] = al;
-        sh_act[t] = a;
     }
-    __syncthreads();
-    const int r = t % R; // the stride is a multiple of R: a thread keeps its instance
-    const bool act = sh_act[r] != 0;
-    const double al = sh_alpha[r];
-    double acc = 0.0;
-    if (act) {
-        const size_t j1 = (size_t)W.i1 * R;
-        for (size_t j = (size_t)W.i0 * R + t; j < j1; j += kBlock) {
-            const double rv = fma(-al, Q[j], Rv[j]);
-            Rv[j] = rv;
-            acc = fma(rv, rv, acc);
-        }
-    }
+    // this thread's right-hand sides: r0 .. r0 + V - 1
+    const int r0 = (t * V) % R;
+    double mal[V], acc[V];
+    bool on[V];
+    bool any = false;
 #pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-        const double s = block_sum(r == rr ? acc : 0.0, red);
-        if (t == 0)
-            rho_part[blockIdx.x * R + rr] = s;
+    for (int c = 0; c < V; ++c) {
+        mal[c] = -al[c];
+        on[c] = act[c];
+#pragma unroll
+        for (int r = V; r < R; r += V)
+            if (r0 == r) {
+                mal[c] = -al[r + c];
+                on[c] = act[r + c];
+            }
+        acc[c] = 0.0;
+        any |= on[c];
+    }
+    if (any) {
+        auto step = [&](vec x, vec y, int j) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                const double z = fma(mal[c], x[c], y[c]);
+                if (on[c]) { // a stopped right-hand side keeps its residual
+                    y[c] = z;
+                    acc[c] = fma(z, z, acc[c]);
+                }
+            }
+            rv[j] = y;
+        };
+#pragma unroll
+        for (int u = 0; u < kBPre; ++u)
+            if (t + u * kBlock < m)
+                step(qv[u], v[u], t + u * kBlock);
+        for (int j = t + kBPre * kBlock; j < m; j += kBlock)
+            step(q[j], rv[j], j);
+    }
+    // workgroup sums per right-hand side, as in sys_sums
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+#pragma unroll
+        for (int o = 32; o >= R / V; o >>= 1)
+            acc[c] += __shfl_xor(acc[c], o, 64);
+    __syncthreads();
+    if ((t & 63) < R / V)
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            red[t >> 6][r0 + c] = acc[c];
+    __syncthreads();
+    if (t < R) {
+        double a = red[0][t];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w)
+            a += red[w][t];
+        rho_part[blockIdx.x * R + t] = a;
     }
 }
 
@@ -490,42 +608,83 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_xp(const WgDesc *__restrict_
                                                        double *__restrict__ P, const double *__restrict__ Rv,
                                                        Inst *inst, const double *__restrict__ rho_part)
 {
-    __shared__ double sh_alpha[R], sh_beta[R];
-    __shared__ int sh_act[R], sh_conv[R];
+    constexpr int V = BVec<R>::V;
+    typedef typename BVec<R>::type vec;
+    __shared__ double red[kWaves][R];
     const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x;
-    if (t < R) {
-        Inst *I = &inst[W.sys * R + t];
-        const int a = I->status == kRun;
-        double be = 0.0;
-        int conv = 0;
-        if (a) {
-            const double rn = sys_sum<R>(rho_part, W, t);
-            be = rn / I->rho;
-            conv = sqrt(rn) <= I->tol_nb;
-            if (W.lead) {
-                I->rho_next = rn;
-                I->conv_next = conv;
-            }
-        }
-        sh_alpha[t] = a ? I->alpha : 0.0;
-        sh_beta[t] = be;
-        sh_act[t] = a;
-        sh_conv[t] = conv;
+    const vec *rv = reinterpret_cast<const vec *>(Rv + (size_t)W.i0 * R);
+    vec *x = reinterpret_cast<vec *>(X + (size_t)W.i0 * R), *p = reinterpret_cast<vec *>(P + (size_t)W.i0 * R);
+    const int m = (W.i1 - W.i0) * (R / V);
+    bool act[R], any = false;
+    double rho[R], al[R], tol[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const Inst *I = &inst[W.sys * R + r];
+        act[r] = I->status == kRun;
+        rho[r] = I->rho;
+        al[r] = I->alpha;
+        tol[r] = I->tol_nb;
+        any |= act[r];
     }
-    __syncthreads();
-    const int r = t % R;
-    if (!sh_act[r])
+    if (!any)
         return;
-    const double al = sh_alpha[r], be = sh_beta[r];
-    const bool conv = sh_conv[r] != 0;
-    const size_t j1 = (size_t)W.i1 * R;
-    for (size_t j = (size_t)W.i0 * R + t; j < j1; j += kBlock) {
-        const double pj = P[j];
-        X[j] = fma(al, pj, X[j]);
-        if (!conv)
-            P[j] = fma(be, pj, Rv[j]);
+    vec pv[kBPre], xv[kBPre], v[kBPre];
+#pragma unroll
+    for (int u = 0; u < kBPre; ++u) {
+        const int j = min(t + u * kBlock, m - 1);
+        pv[u] = p[j];
+        xv[u] = x[j];
+        v[u] = rv[j];
     }
+    double rn[R];
+    sys_sums<R>(sys_partial<R>(rho_part, W), red, rn);
+    bool conv[R];
+    double be[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        be[r] = rn[r] / rho[r];
+        conv[r] = sqrt(rn[r]) <= tol[r];
+        if (act[r] && W.lead && t == 0) {
+            Inst *I = &inst[W.sys * R + r];
+            I->rho_next = rn[r];
+            I->conv_next = conv[r];
+        }
+    }
+    const int r0 = (t * V) % R;
+    double ta[V], tb[V];
+    bool on[V], go[V]; // x moves; the direction moves too
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+        ta[c] = al[c];
+        tb[c] = be[c];
+        on[c] = act[c];
+        go[c] = act[c] && !conv[c];
+#pragma unroll
+        for (int r = V; r < R; r += V)
+            if (r0 == r) {
+                ta[c] = al[r + c];
+                tb[c] = be[r + c];
+                on[c] = act[r + c];
+                go[c] = act[r + c] && !conv[r + c];
+            }
+    }
+    auto step = [&](vec pj, vec xj, vec rj, int j) {
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+            const double xn = fma(ta[c], pj[c], xj[c]), pn = fma(tb[c], pj[c], rj[c]);
+            xj[c] = on[c] ? xn : xj[c];
+            pj[c] = go[c] ? pn : pj[c];
+        }
+        x[j] = xj;
+        p[j] = pj;
+    };
+#pragma unroll
+    for (int u = 0; u < kBPre; ++u)
+        if (t + u * kBlock < m)
+            step(pv[u], xv[u], v[u], t + u * kBlock);
+    for (int j = t + kBPre * kBlock; j < m; j += kBlock)
+        step(p[j], x[j], rv[j], j);
 }
 
 // After each graph launch: apply the pending stop decisions and count the
@@ -587,33 +746,37 @@ __global__ __launch_bounds__(kBlock) void k_binit_vec(const WgDesc *__restrict__
     }
 }
 
-// One thread per instance: ||b||, r0'r0, status, tolerance.
+// One workgroup per system: ||b||, r0'r0, status, tolerance of its instances.
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_binit_state(const WgDesc *__restrict__ wgs,
-                                                        const int32_t *__restrict__ sys_wg0, Inst *inst, int ninst,
+                                                        const int32_t *__restrict__ sys_wg0, Inst *inst,
                                                         const double *__restrict__ rho_part,
                                                         const double *__restrict__ bb_part, double tol, int maxit)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= ninst)
+    __shared__ double red[kWaves][R];
+    const WgDesc W = wgs[sys_wg0[blockIdx.x]];
+    double bb[R], rr[R];
+    sys_sums<R>(sys_partial<R>(bb_part, W), red, bb);
+    sys_sums<R>(sys_partial<R>(rho_part, W), red, rr);
+    if (threadIdx.x != 0)
         return;
-    const int s = i / R, r = i % R;
-    const WgDesc W = wgs[sys_wg0[s]];
-    const double nb = sqrt(sys_sum<R>(bb_part, W, r));
-    const double rho = sys_sum<R>(rho_part, W, r);
-    Inst *I = &inst[i];
-    I->k = 0;
-    I->iters = 0;
-    I->maxit = maxit;
-    I->nb = nb;
-    I->rho = rho;
-    I->alpha = 0.0;
-    I->sigma = 0.0;
-    I->res_true = 0.0;
-    I->tol_nb = tol * nb;
-    I->rho_next = rho;
-    I->conv_next = sqrt(rho) <= tol * nb ? 1 : 0;
-    I->status = !isfinite(nb) ? kNonfinite : (nb == 0.0 ? kZeroRhs : kRun);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double nb = sqrt(bb[r]), rho = rr[r];
+        Inst *I = &inst[W.sys * R + r];
+        I->k = 0;
+        I->iters = 0;
+        I->maxit = maxit;
+        I->nb = nb;
+        I->rho = rho;
+        I->alpha = 0.0;
+        I->sigma = 0.0;
+        I->res_true = 0.0;
+        I->tol_nb = tol * nb;
+        I->rho_next = rho;
+        I->conv_next = sqrt(rho) <= tol * nb ? 1 : 0;
+        I->status = !isfinite(nb) ? kNonfinite : (nb == 0.0 ? kZeroRhs : kRun);
+    }
 }
 
 template <int R>
@@ -640,10 +803,11 @@ __global__ __launch_bounds__(kBlock) void k_bresid(const WgDesc *__restrict__ wg
 // Copy out: x of the instance (unless b had a non-finite entry: untouched;
 // b == 0: zero), and the true relative residual per instance.
 template <int R>
-__global__ __launch_bounds__(kBlock) void k_bfinish(const WgDesc *__restrict__ wgs, const int32_t *__restrict__ sys_wg0,
-                                                    Inst *inst, const double *__restrict__ part,
+__global__ __launch_bounds__(kBlock) void k_bfinish(const WgDesc *__restrict__ wgs, Inst *inst,
+                                                    const double *__restrict__ part,
                                                     const double *__restrict__ Xw, double *__restrict__ X)
 {
+    __shared__ double red[kWaves][R];
     const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x, r = t % R;
     const Inst *I = &inst[W.sys * R + r];
@@ -654,12 +818,16 @@ __global__ __launch_bounds__(kBlock) void k_bfinish(const WgDesc *__restrict__ w
             continue;
         X[j] = st == kZeroRhs ? 0.0 : Xw[j];
     }
-    if (W.lead && t < R) {
-        Inst *Ir = &inst[W.sys * R + t];
-        const double s = sys_sum<R>(part, W, t);
-        Ir->res_true = Ir->nb > 0.0 ? sqrt(s) / Ir->nb : 0.0;
+    if (W.lead) { // the whole workgroup
+        double s[R];
+        sys_sums<R>(sys_partial<R>(part, W), red, s);
+        if (t == 0)
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr) {
+                Inst *Ir = &inst[W.sys * R + rr];
+                Ir->res_true = Ir->nb > 0.0 ? sqrt(s[rr]) / Ir->nb : 0.0;
+            }
     }
-    (void)sys_wg0;
 }
 
 } // namespace
@@ -787,7 +955,7 @@ int build_plan(cg_batch *h, int ept, int wg_target)
         const int nrbs = sys_rb0[s + 1] - sys_rb0[s];
         const int64_t nnzs = (int64_t)ptr[h->sys_off[s + 1]] - ptr[h->sys_off[s]];
         int g = (int)std::llround((double)wg_target * (double)nnzs / (double)std::max<int64_t>(h->nnz, 1));
-        g = std::max(1, std::min(g, nrbs));
+        g = std::max(1, std::min({g, nrbs, kMaxSysWgs}));
         wg0[s] = (int32_t)w.size();
         for (int k = 0; k < g; ++k) {
             WgDesc d{};
@@ -907,7 +1075,7 @@ int build_plan_slices(cg_batch *h, int wg_target)
         const int q0 = h->hsl_sys0[s], nq = h->hsl_sys0[s + 1] - q0;
         const int64_t nnzs = (int64_t)ptr[h->sys_off[s + 1]] - ptr[h->sys_off[s]];
         int g = (int)std::llround((double)wg_target * (double)nnzs / (double)std::max<int64_t>(h->nnz, 1));
-        g = std::max(1, std::min(g, nq));
+        g = std::max(1, std::min({g, nq, kMaxSysWgs}));
         wg0[s] = (int32_t)w.size();
         for (int k = 0; k < g; ++k) {
             WgDesc d{};
@@ -1045,12 +1213,11 @@ void iteration(cg_batch *h, hipStream_t s)
 template <int R>
 void init_r(cg_batch *h, const double *B, const double *X0, double tol, int maxit, hipStream_t s)
 {
-    const int ninst = h->nsys * R;
     spmm_any<R>(h, X0, h->Q, nullptr, s);
     hipLaunchKernelGGL(k_binit_vec<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, B, X0, h->Q, h->Rv, h->P, h->Xw,
                        h->rho, h->bb);
-    hipLaunchKernelGGL(k_binit_state<R>, dim3((ninst + kBlock - 1) / kBlock), dim3(kBlock), 0, s, h->wgs,
-                       h->sys_wg0, h->inst, ninst, h->rho, h->bb, tol, maxit);
+    hipLaunchKernelGGL(k_binit_state<R>, dim3(h->nsys), dim3(kBlock), 0, s, h->wgs, h->sys_wg0, h->inst, h->rho,
+                       h->bb, tol, maxit);
 }
 
 template <int R>
@@ -1058,7 +1225,7 @@ void finish_r(cg_batch *h, const double *B, double *X, hipStream_t s)
 {
     spmm_any<R>(h, h->Xw, h->Q, nullptr, s);
     hipLaunchKernelGGL(k_bresid<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, B, h->Q, h->bb);
-    hipLaunchKernelGGL(k_bfinish<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sys_wg0, h->inst, h->bb, h->Xw, X);
+    hipLaunchKernelGGL(k_bfinish<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->inst, h->bb, h->Xw, X);
 }
 
 int build_graph(cg_batch *h)
