@@ -639,31 +639,39 @@ int mixed_rescale(cg_handle *h)
     return CG_OK;
 }
 
-// Every array derived from the FP64 values (CSC panel order, the mixed
-// FP32 scaled copy) rebuilt from dm.val, on the handle's stream.
-int refresh_values(cg_handle *h)
+// Every array derived from the FP64 values (the layout the products read,
+// the mixed FP32 scaled copy) rebuilt on the handle's stream from `src`: the
+// values in the matrix's entry order, or with `order` in the caller's.  The
+// FP32 copy is made from dm.val.
+int refresh_values(cg_handle *h, const double *src, const int32_t *order)
 {
     DevMatrix &m = h->dm;
-    const int64_t nnz = h->plan.nnz;
-    if (m.panel && !m.slices)
-        launch_permute(nnz, m.val, m.pn_src, m.pn_val, h->stream);
-    if (m.slices)
-        launch_permute((int64_t)h->plan.sl_src.size(), m.val, m.sl_src, m.sl_val, h->stream);
-    if (m.sym_slices || m.compact)
-        launch_permute(m.ss_positions, m.val, m.ss_src, m.ss_val, h->stream);
+    const int64_t nnz = h->plan.nnz, np = (int64_t)h->plan.sl_src.size();
+    launch_fill_layout(m, nnz, np, src, order, h->stream);
     HIP_TRY(h, hipGetLastError());
     if (h->mixed && m.n > 0) {
         const int st = mixed_rescale(h);
         if (st != CG_OK)
             return st;
-        if (m.panel && !m.slices)
-            launch_permute(nnz, m.val32, m.pn_src, m.pn_val32, h->stream);
-        if (m.slices)
-            launch_permute((int64_t)h->plan.sl_src.size(), m.val32, m.sl_src, m.sl_val32, h->stream);
-        if (m.sym_slices || m.compact)
-            launch_permute(m.ss_positions, m.val32, m.ss_src, m.ss_val32, h->stream);
+        launch_fill_layout32(m, nnz, np, h->stream);
         HIP_TRY(h, hipGetLastError());
     }
+    return CG_OK;
+}
+
+// After creation: the values in entry order are given back where nothing
+// reads them again (waits for the work that still does).
+int drop_entry_values(cg_handle *h)
+{
+    DevMatrix &m = h->dm;
+    if (m.n == 0 || m.keeps_val())
+        return CG_OK;
+    void *p = const_cast<double *>(m.val);
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    HIP_TRY(h, hipFree(p));
+    h->allocs.erase(std::remove(h->allocs.begin(), h->allocs.end(), p), h->allocs.end());
+    h->dev_bytes -= std::max<size_t>((size_t)h->plan.nnz, 1) * sizeof(double);
+    m.val = nullptr;
     return CG_OK;
 }
 
@@ -913,7 +921,9 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
         if (st == CG_OK)
             st = dalloc(h.get(), &h->flag, 1);
         if (st == CG_OK)
-            st = refresh_values(h.get());
+            st = refresh_values(h.get(), h->dm.val, nullptr);
+        if (st == CG_OK)
+            st = drop_entry_values(h.get());
         if (st != CG_OK) {
             g_err = h->err;
             release(h.get());
@@ -1188,9 +1198,11 @@ int cg_set_values(cg_handle *h, const double *vals)
         return CG_ERR_ARG;
     }
     hipStream_t s = h->stream;
+    if (!h->dm.keeps_val()) // straight into the layout the products read
+        return refresh_values(h, vals, h->perm);
     launch_set_values(nnz, vals, h->perm, const_cast<double *>(h->dm.val), s);
     HIP_TRY(h, hipGetLastError());
-    return refresh_values(h);
+    return refresh_values(h, h->dm.val, nullptr);
 }
 
 int cg_pattern_grad(cg_handle *h, const double *lam, const double *x, double *grad)

@@ -53,7 +53,7 @@ struct DevMatrix {
     int lanes = 16;
     const int32_t *ptr = nullptr;
     const int32_t *idx = nullptr;
-    const double *val = nullptr;
+    const double *val = nullptr;   // null where only the planned layout's copy is kept (keeps_val)
     const float *val32 = nullptr;  // mixed precision: values of D^-1/2 A D^-1/2 in FP32
     const double *dscale = nullptr; // mixed precision: D^-1/2
     // CSR
@@ -117,6 +117,9 @@ struct DevMatrix {
     int spmv_blocks() const { return format == kCsr || slices ? csr_blocks : scatter_wgs; }
     // the product ends with a row pass (parked slot sums, rows with no writer)
     int64_t part_doubles = 0;             // entries of `part` (0: no parked sums)
+    // the values in the matrix's entry order are read after creation: by the
+    // products of unsliced CSR and symmetric blocks, and by the FP32 rescaling
+    bool keeps_val() const { return val32 != nullptr || !(slices || compact || sym_slices || panel); }
     bool row_pass() const
     {
         return panel ? pn_gather : compact ? parked > 0 : (format == kSymCsr && ncolors > 1);
@@ -182,10 +185,19 @@ void launch_init_state(const DevMatrix &m, DevState *st, const double *bb_part, 
 void launch_true_residual(const DevMatrix &m, const double *b, const double *q, double *part, DevState *st,
                           hipStream_t s);
 void launch_fill(int n, double *x, double v, hipStream_t s);
-// dst[k] = src[perm[k]] for k < nnz, 0 where perm[k] < 0 (values into the
-// CSC panel order or the CSR slice positions)
-void launch_permute(int64_t nnz, const double *src, const int32_t *perm, double *dst, hipStream_t s);
-void launch_permute(int64_t nnz, const float *src, const int32_t *perm, float *dst, hipStream_t s);
+// dst[k] = src[perm[k]] for k < nnz, 0 where perm[k] < 0; with `order`,
+// src[order[perm[k]]]
+void launch_permute(int64_t nnz, const double *src, const int32_t *perm, double *dst, hipStream_t s,
+                    const int32_t *order = nullptr);
+void launch_permute(int64_t nnz, const float *src, const int32_t *perm, float *dst, hipStream_t s,
+                    const int32_t *order = nullptr);
+// Values into the layout the products read (slices, compact or coloured
+// blocks, CSC panel order): from nnz values in the matrix's entry order, or,
+// with `order`, in the caller's (entry k is src[order[k]]).  Nothing to do for
+// a plan that reads the values as they are (CSR row blocks, long rows).
+void launch_fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, const double *src,
+                        const int32_t *order, hipStream_t s);
+void launch_fill_layout32(const DevMatrix &m, int64_t nnz, int64_t sl_positions, hipStream_t s);
 // val[k] = src[perm ? perm[k] : k] for k < nnz
 void launch_set_values(int64_t nnz, const double *src, const int32_t *perm, double *val, hipStream_t s);
 // mixed precision: recompute D^-1/2 (into sc, the caller's row order) and the FP32 scaled values from

@@ -547,15 +547,97 @@ __global__ __launch_bounds__(kBlock) void k_panel_rows(int nch, const int32_t *_
 }
 
 // dst[k] = src[perm[k]] (0 where perm[k] < 0): values into the panel order
-// or the slice positions
+// or the slice positions; with `order`, src holds the entries in the caller's
+// order (entry j of the normalised matrix is the caller's order[j]).
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_permute(int64_t nnz, const T *__restrict__ src,
-                                                    const int32_t *__restrict__ perm, T *__restrict__ dst)
+                                                    const int32_t *__restrict__ perm,
+                                                    const int32_t *__restrict__ order, T *__restrict__ dst)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k < nnz) {
         const int32_t j = perm[k];
-        dst[k] = j >= 0 ? src[j] : T(0);
+        dst[k] = j >= 0 ? src[order ? order[j] : j] : T(0);
+    }
+}
+
+// Values of CSR rows into their slices, straight from the row pointers (the
+// entries of 64 consecutive rows are one contiguous run): a wavefront stages
+// the run in LDS with coalesced loads and writes the positions from there,
+// two values per store, padding 0.  Bytes bound it: 8 read and 8 written per
+// entry, at the device-copy rate (14.8 M entries: 46 us, 5.2 TB/s).  The
+// permutation list of k_permute adds 4 and its gather touches a cache line
+// per lane, and the values were first copied into the handle: 41 + 85 us.  A slice of more than kFillEntries
+// entries reads them from memory instead (one line per lane).
+constexpr int kFillEntries = 1024; // 8 KB of LDS per wavefront: 16 a row, 20 waves per CU
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_fill_slices(int nl, int ns, const int32_t *__restrict__ ptr,
+                                                        const int32_t *__restrict__ off, const T *__restrict__ src,
+                                                        T *__restrict__ dst)
+{
+    __shared__ T stage[kWaves][kFillEntries];
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int sl = blockIdx.x * kWaves + wv;
+    const bool has = sl < ns;
+    const int e0 = has ? off[sl] : 0, w = has ? (off[sl + 1] - e0) / kSliceRows : 0;
+    const int l = min((has ? sl : 0) * kSliceRows + lane, nl);
+    const int a = has ? ptr[l] : 0, len = has ? ptr[min(l + 1, nl)] - a : 0;
+    const int base = __shfl(a, 0), cnt = __shfl(a + len, 63) - base;
+    const bool staged = cnt <= kFillEntries;
+    if (staged) {
+        T v[kFillEntries / kSliceRows];
+#pragma unroll
+        for (int m = 0; m < kFillEntries / kSliceRows; ++m) {
+            const int i = lane + m * kSliceRows;
+            v[m] = i < cnt ? __builtin_nontemporal_load(src + base + i) : T(0);
+        }
+#pragma unroll
+        for (int m = 0; m < kFillEntries / kSliceRows; ++m)
+            stage[wv][lane + m * kSliceRows] = v[m];
+    }
+    __syncthreads();
+    typename Vec2<T>::type *d2 = reinterpret_cast<typename Vec2<T>::type *>(dst + e0);
+    for (int k = 0; k + 1 < w; k += 2) {
+        typename Vec2<T>::type v;
+        v.x = k < len ? (staged ? stage[wv][a - base + k] : src[a + k]) : T(0);
+        v.y = k + 1 < len ? (staged ? stage[wv][a - base + k + 1] : src[a + k + 1]) : T(0);
+        d2[(k >> 1) * kSliceRows + lane] = v;
+    }
+    if (w & 1)
+        dst[e0 + (w - 1) * kSliceRows + lane] =
+            w - 1 < len ? (staged ? stage[wv][a - base + w - 1] : src[a + w - 1]) : T(0);
+}
+
+// Values of symmetric rows into their compact blocks, from the row pointers:
+// thread t of a block's workgroup reads its line's (at most 8) entries, which
+// are contiguous, and writes them at the block's positions.  8 bytes read and
+// written per entry and 8 per line, instead of a 4-byte source per position.
+template <class T>
+__global__ __launch_bounds__(kCompactThreads) void k_fill_compact(const CompactBlock *__restrict__ blocks,
+                                                                  const int32_t *__restrict__ vperm,
+                                                                  const int32_t *__restrict__ ptr,
+                                                                  const T *__restrict__ src, T *__restrict__ dst)
+{
+    const CompactBlock bk = blocks[blockIdx.x];
+    const int t = threadIdx.x;
+    if (t == 0 && (bk.nl * bk.len & 1))
+        dst[bk.pos0 + bk.nl * bk.len] = T(0); // blocks start at even positions
+    if (t >= bk.nl)
+        return;
+    const int row = vperm[bk.line0 + t];
+    const int a = ptr[row], len = ptr[row + 1] - a;
+    T v[kStreamPerThread];
+#pragma unroll
+    for (int k = 0; k < kStreamPerThread; ++k)
+        v[k] = k < len ? src[a + k] : T(0);
+#pragma unroll
+    for (int k = 0; k < kStreamPerThread; k += 2) {
+        if (k + 1 < bk.len) {
+            typename Vec2<T>::type q = {v[k], v[k + 1]};
+            *reinterpret_cast<typename Vec2<T>::type *>(dst + bk.pos0 + k * bk.nl + 2 * t) = q;
+        } else if (k < bk.len) {
+            dst[bk.pos0 + k * bk.nl + t] = v[k];
+        }
     }
 }
 
@@ -1484,32 +1566,78 @@ __global__ __launch_bounds__(kBlock) void k_mx_scale(int n, const int32_t *__res
 // CSR (line = row i): -lam_l x_idx; CSC (line = column j): -lam_idx x_l;
 // symmetric CSR (upper, one stored value stands for A_ij and A_ji):
 // -(lam_l x_idx + lam_idx x_l), and -lam_l x_l on the diagonal.  Written in
-// the caller's entry order (out[perm[k]]).  One thread per line.
-__global__ __launch_bounds__(kBlock) void k_pattern_grad(int fmt, int n, const int32_t *__restrict__ ptr,
+// the caller's entry order (out[perm[k]]).
+// A wavefront takes 64 consecutive lines, whose entries are one contiguous
+// run: the lanes read indices and write gradients along the run, so both are
+// whole cache lines, and learn each entry's line from a byte map in LDS (each
+// lane marks its own line's entries, a window of the run at a time); the
+// line's own lam / x come from that lane's register.  Bytes bound it: 12 per
+// entry (14.8 M entries: 54 us, 3.3 TB/s; one thread per line, writing 8 and
+// reading 4 bytes a cache line apart, took 280 us).
+constexpr int kGradWindow = 2048; // entries mapped at a time
+constexpr int kGradUnroll = 4;
+template <int FMT>
+__global__ __launch_bounds__(kBlock) void k_pattern_grad(int n, const int32_t *__restrict__ ptr,
                                                          const int32_t *__restrict__ idx,
                                                          const double *__restrict__ lam,
                                                          const double *__restrict__ x,
                                                          const int32_t *__restrict__ perm, double *__restrict__ out)
 {
 #pragma clang fp contract(off)
-    const int l = blockIdx.x * kBlock + threadIdx.x;
-    if (l >= n)
-        return;
+    __shared__ uint8_t map[kWaves][kGradWindow];
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int l0 = (blockIdx.x * kWaves + wv) * 64;
+    const int l = min(l0 + lane, n - 1);
+    const bool has = l0 + lane < n;
     const double ll = lam[l], xl = x[l];
-    for (int k = ptr[l]; k < ptr[l + 1]; ++k) {
-        const int j = idx[k];
-        double g;
-        if (fmt == kCsr) {
-            g = -(ll * x[j]);
-        } else if (fmt == kCsc) {
-            g = -(lam[j] * xl);
-        } else if (j == l) {
-            g = -(ll * xl);
-        } else {
-            const double t1 = ll * x[j], t2 = lam[j] * xl; // two rounded products, then one rounded sum
-            g = -(t1 + t2);
+    const int a = ptr[min(l0 + lane, n)], b = has ? ptr[l + 1] : a;
+    const int e0 = __shfl(a, 0), cnt = __shfl(b, 63) - e0;
+    // (all waves of the workgroup walk as many windows as the longest needs)
+    __shared__ int len[kWaves];
+    if (lane == 0)
+        len[wv] = cnt;
+    __syncthreads();
+    int most = len[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w)
+        most = max(most, len[w]);
+    for (int64_t w0 = 0; w0 < most; w0 += kGradWindow) {
+        const int base = e0 + (int)min(w0, (int64_t)cnt), stop = e0 + (int)min(w0 + kGradWindow, (int64_t)cnt);
+        for (int k = max(a, base); k < min(b, stop); ++k)
+            map[wv][k - base] = (uint8_t)lane;
+        __syncthreads();
+        for (int64_t k0 = base; k0 < stop; k0 += 64 * kGradUnroll) {
+            int j[kGradUnroll], r[kGradUnroll];
+#pragma unroll
+            for (int u = 0; u < kGradUnroll; ++u) { // past the end: the run's last entry again, not stored
+                const int k = (int)min(k0 + u * 64 + lane, (int64_t)stop - 1);
+                j[u] = __builtin_nontemporal_load(idx + k);
+                r[u] = map[wv][k - base];
+            }
+            double xj[kGradUnroll], lj[kGradUnroll];
+#pragma unroll
+            for (int u = 0; u < kGradUnroll; ++u) {
+                xj[u] = FMT != kCsc ? x[j[u]] : 0.0;
+                lj[u] = FMT != kCsr ? lam[j[u]] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < kGradUnroll; ++u) {
+                const int64_t k = k0 + u * 64 + lane;
+                const double rl = __shfl(ll, r[u]), rx = __shfl(xl, r[u]);
+                double g;
+                if (FMT == kCsr) {
+                    g = -(rl * xj[u]);
+                } else if (FMT == kCsc) {
+                    g = -(lj[u] * rx);
+                } else {
+                    const double t1 = rl * xj[u], t2 = lj[u] * rx; // two rounded products, then one rounded sum
+                    g = j[u] == l0 + r[u] ? -t1 : -(t1 + t2);
+                }
+                if (k < stop)
+                    out[perm ? perm[k] : k] = g;
+            }
         }
-        out[perm ? perm[k] : k] = g;
+        __syncthreads();
     }
 }
 
@@ -1930,18 +2058,59 @@ void launch_fill(int n, double *x, double v, hipStream_t s)
         hipLaunchKernelGGL(k_fill, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, n, x, v);
 }
 
-void launch_permute(int64_t nnz, const double *src, const int32_t *perm, double *dst, hipStream_t s)
+void launch_permute(int64_t nnz, const double *src, const int32_t *perm, double *dst, hipStream_t s,
+                    const int32_t *order)
 {
     if (nnz > 0)
         hipLaunchKernelGGL(k_permute<double>, dim3((unsigned)((nnz + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, nnz,
-                           src, perm, dst);
+                           src, perm, order, dst);
 }
 
-void launch_permute(int64_t nnz, const float *src, const int32_t *perm, float *dst, hipStream_t s)
+void launch_permute(int64_t nnz, const float *src, const int32_t *perm, float *dst, hipStream_t s,
+                    const int32_t *order)
 {
     if (nnz > 0)
         hipLaunchKernelGGL(k_permute<float>, dim3((unsigned)((nnz + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, nnz,
-                           src, perm, dst);
+                           src, perm, order, dst);
+}
+
+namespace {
+// values in the caller's / normalised entry order -> the planned layout
+template <class T>
+void fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, const T *src, const int32_t *order, T *sl, T *ss,
+                 T *pn, hipStream_t s)
+{
+    // row-contiguous sources (CSR rows, symmetric rows of compact blocks) in
+    // the matrix's own order go through the row pointers; a permuted source
+    // (lower triangle), panel slots and expanded triangles through the list
+    if (m.slices && m.format == kCsr && order == nullptr) {
+        if (m.nslices > 0)
+            hipLaunchKernelGGL(k_fill_slices<T>, dim3((m.nslices + kWaves - 1) / kWaves), dim3(kBlock), 0, s, m.n,
+                               m.nslices, m.ptr, m.sl_off, src, sl);
+    } else if (m.slices) {
+        launch_permute(sl_positions, src, m.sl_src, sl, s, order);
+    } else if (m.panel) {
+        launch_permute(nnz, src, m.pn_src, pn, s, order);
+    }
+    if (m.compact && order == nullptr) {
+        if (m.nblocks > 0)
+            hipLaunchKernelGGL(k_fill_compact<T>, dim3(m.nblocks), dim3(kCompactThreads), 0, s, m.cblocks, m.vperm,
+                               m.ptr, src, ss);
+    } else if (m.compact || m.sym_slices) {
+        launch_permute(m.ss_positions, src, m.ss_src, ss, s, order);
+    }
+}
+} // namespace
+
+void launch_fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, const double *src,
+                        const int32_t *order, hipStream_t s)
+{
+    fill_layout(m, nnz, sl_positions, src, order, m.sl_val, m.ss_val, m.pn_val, s);
+}
+
+void launch_fill_layout32(const DevMatrix &m, int64_t nnz, int64_t sl_positions, hipStream_t s)
+{
+    fill_layout(m, nnz, sl_positions, m.val32, nullptr, m.sl_val32, m.ss_val32, m.pn_val32, s);
 }
 
 void launch_set_values(int64_t nnz, const double *src, const int32_t *perm, double *val, hipStream_t s)
@@ -1963,9 +2132,15 @@ void launch_mx_rescale(const DevMatrix &m, double *sc, float *v32, int32_t *bad,
 void launch_pattern_grad(const DevMatrix &m, const double *lam, const double *x, const int32_t *perm, double *out,
                          hipStream_t s)
 {
-    if (m.n > 0)
-        hipLaunchKernelGGL(k_pattern_grad, dim3((m.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m.format, m.n,
-                           m.ptr, m.idx, lam, x, perm, out);
+    if (m.n <= 0)
+        return;
+    const dim3 g((m.n + kBlock - 1) / kBlock);
+    if (m.format == kCsr)
+        hipLaunchKernelGGL(k_pattern_grad<kCsr>, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
+    else if (m.format == kCsc)
+        hipLaunchKernelGGL(k_pattern_grad<kCsc>, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
+    else
+        hipLaunchKernelGGL(k_pattern_grad<kSymCsr>, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
 }
 
 } // namespace cgmi
