@@ -37,6 +37,17 @@ __device__ __forceinline__ PT gather0(const PT *__restrict__ x, int c)
     }
 }
 
+// Store of a value that a later kernel reads: through the XCD's L2 to memory
+// at once (an agent-scope store), so the lines are clean when the kernel ends
+// and its write-back has nothing left to do, and the writes of a streaming
+// kernel leave in step with its reads.  160^3 CSR iteration, all vector
+// stores: 175.0 -> 171.8 us (product 126.4 -> 124.3); 61x59x57: 14.5 -> 14.1.
+template <class T>
+__device__ __forceinline__ void store_through(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int W>
 __device__ __forceinline__ double group_sum(double v)
 {

@@ -32,6 +32,19 @@ __device__ __forceinline__ T matrix_load(const T *p)
         return *p;
 }
 
+// Stores of a CSR product's sums: written through (store_through) where the
+// matrix is streamed (160^3 product 126.4 -> 124.3 us).  A cache-resident
+// product is not bound by them (100^3: 25.5, 25.6 written through), and panel
+// slots, whose targets are spread, lose (150x140x155: 145.9 -> 146.6).
+template <bool NT>
+__device__ __forceinline__ void sum_store(double *p, double v)
+{
+    if constexpr (NT)
+        store_through(p, v);
+    else
+        *p = v;
+}
+
 // Two-element vectors for the paired loads of the sliced layout (native
 // vector types, which the non-temporal load builtin accepts).
 typedef int int2v __attribute__((ext_vector_type(2)));
@@ -436,9 +449,9 @@ __global__ __launch_bounds__(kBlock) void k_spmv_slices(int nl, int ns, const in
         for (int j = 0; j < S; ++j)
             if (l[j] < nl) {
                 if (!PANEL || l[j] < first_parked)
-                    y[tg[j]] = a[j];
+                    sum_store<NT && !PANEL>(y + tg[j], a[j]);
                 else
-                    part[tg[j]] = a[j]; // parked by row: at most one colour-1 slot per row
+                    sum_store<NT && !PANEL>(part + tg[j], a[j]); // parked by row: at most one colour-1 slot per row
                 if constexpr (FUSED) {
                     // the row's new direction and the x update it owes
                     const double po = fd.pold[l[j]];
@@ -1256,11 +1269,12 @@ __device__ __forceinline__ void row_values(const double *__restrict__ q, const d
 // is recorded here.
 // KP: elements per thread loaded up front (the chunk's, up to 8 x 256;
 // registers sized to the chunk, so small chunks keep more waves resident).
+// through: r written through (store_through); the launch decides.
 template <int GATHER, int PPT, bool FUSED, int KP>
 __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *__restrict__ r,
                                                      const double *__restrict__ q, DevState *st,
                                                      const double *__restrict__ sig_part, int n_sig,
-                                                     double *__restrict__ rho_part, RowPass g)
+                                                     double *__restrict__ rho_part, RowPass g, bool through)
 {
     __shared__ double red[kWaves];
     // the gate, the partials and the first vector elements are loaded
@@ -1311,7 +1325,10 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *_
         const int i = i0 + t + u * kBlock;
         if (i < i1) {
             const double ri = fma(-alpha, qv[u], rv[u]);
-            r[i] = ri;
+            if (through)
+                store_through(r + i, ri);
+            else
+                r[i] = ri;
             acc = fma(ri, ri, acc);
         }
     }
@@ -1370,16 +1387,16 @@ __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, double *
     for (int u = 0; u < KP; ++u) {
         const int i = i0 + t + u * kBlock;
         if (i < i1) {
-            x[i] = fma(alpha, pv[u], xv[u]);
+            store_through(x + i, fma(alpha, pv[u], xv[u]));
             if (!conv)
-                p[i] = (PT)fma(beta, pv[u], rv[u]);
+                store_through(p + i, (PT)fma(beta, pv[u], rv[u]));
         }
     }
     for (int i = i0 + t + KP * kBlock; i < i1; i += kBlock) {
         const double pi = (double)p[i];
-        x[i] = fma(alpha, pi, x[i]);
+        store_through(x + i, fma(alpha, pi, x[i]));
         if (!conv)
-            p[i] = (PT)fma(beta, pi, r[i]);
+            store_through(p + i, (PT)fma(beta, pi, r[i]));
     }
 }
 
@@ -1923,11 +1940,16 @@ void launch_update_r(const DevMatrix &m, double *r, const double *q, DevState *s
     g.has_c0 = m.has_c0;
     g.part = m.part; // iterations use the handle's own buffer
     const int mode = rows_deferred && m.row_pass() ? (m.panel ? 2 : m.compact ? 3 : 1) : 0;
+    // r written through, except after the row pass of a cache-resident matrix
+    // or of panels: iteration with / without, CSR 61x59x57 14.1 / 14.9 us and
+    // 160^3 171.7 / 172.6, compact 160^3 165.4 / 167.7; compact 100^3 40.9 /
+    // 40.1, panels 150x140x155 177.0 / 176.5
+    const bool through = mode == 0 || (mode == 3 && !m.matrix_cached);
     const dim3 grid(m.vec_blocks), blk(kBlock);
     const int kp = prefetch_depth(m.vec_chunk);
 #define CGMI_UPDATE_R_KP(G, P, F, K)                                                                         \
     hipLaunchKernelGGL((k_update_r<G, P, F, K>), grid, blk, 0, s, m.n, m.vec_chunk, r, q, st, sig_part, nsig,   \
-                       rho_part, g)
+                       rho_part, g, through)
 #define CGMI_UPDATE_R(G, P, F)                                                                               \
     do {                                                                                                     \
         switch (kp) {                                                                                        \
