@@ -108,9 +108,9 @@ typedef struct {
                                 with slices != 0, the triangle expanded into full-row slices (systems
                                 whose vector kernels have at most 256 workgroups, n <= 65 536) */
     int64_t slots;           /* scatter formats: total (block, target) write slots */
-    int64_t plan_bytes;      /* device bytes of the plan beyond ptr / idx / vals */
+    int64_t plan_bytes;      /* device bytes of the product's plan beyond ptr / idx / vals */
     int64_t parked;          /* scatter formats: slot sums parked and added by the row pass */
-    int64_t device_bytes;    /* every device byte the handle holds (matrix, plan, work vectors) */
+    int64_t device_bytes;    /* every device byte the handle holds (matrix, plans, work vectors) */
 } cg_plan_stats;
 
 /*

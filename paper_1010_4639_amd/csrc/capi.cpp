@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
@@ -35,6 +36,7 @@ struct cg_handle {
     Plan plan;
     DevMatrix dm;
     int device = 0;
+    int cus = 0;                   // compute units of the device
     hipStream_t stream = nullptr;  // caller's stream (null stream by default)
     hipStream_t capture = nullptr; // private stream used only to record the graph
     std::vector<void *> allocs;
@@ -45,6 +47,7 @@ struct cg_handle {
     // product forms the direction, which alternates between p and p2
     bool fused = false;
     double *p2 = nullptr;
+    unsigned long long *words = nullptr; // resident solve (one kernel): the exchanged words
     double *sig = nullptr, *sig_spmv = nullptr, *rho = nullptr, *bb = nullptr;
     DevState *st = nullptr;
     DevState *host_st = nullptr; // pinned, 2 entries
@@ -197,6 +200,25 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
         m.sl_d16 = d16;
         m.sl_src = src;
         m.sl_val = sv;
+        if (p.rs_wgs > 0) {
+            int32_t *gp, *gc;
+            uint16_t *lc, *lo;
+            if ((st = upload(h, &gp, p.rs_gptr.data(), p.rs_gptr.size())) != CG_OK ||
+                (st = upload(h, &gc, p.rs_gcol.data(), p.rs_gcol.size())) != CG_OK ||
+                (st = upload(h, &lc, p.rs_lcol.data(), p.rs_lcol.size())) != CG_OK ||
+                (st = upload(h, &lo, p.rs_lown.data(), p.rs_lown.size())) != CG_OK ||
+                (st = dalloc(h, &h->words, (size_t)resident_words(p.csr_blocks, p.vec_blocks, n))) != CG_OK)
+                return st;
+            m.rs_wgs = p.rs_wgs;
+            m.rs_threads = p.rs_threads;
+            m.rs_slices = p.rs_slices;
+            m.rs_width = p.rs_width;
+            m.rs_cols = p.rs_cols;
+            m.rs_gptr = gp;
+            m.rs_gcol = gc;
+            m.rs_lcol = lc;
+            m.rs_lown = lo;
+        }
         if (h->mixed && (st = dalloc(h, &m.sl_val32, std::max<size_t>(p.sl_src.size(), 1))) != CG_OK)
             return st;
     }
@@ -426,8 +448,10 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
     // r and p costs less than the third launch; on large systems it costs
     // more.  Experiments: CGMI_FUSED=0 / 1 (1: wherever the plan allows).
     bool fuse = p.vec_blocks <= kBlock;
-    if (const char *e = std::getenv("CGMI_FUSED"))
+    if (const char *e = std::getenv("CGMI_FUSED")) {
         fuse = std::strcmp(e, "0") != 0;
+        m.rs_wgs = 0;
+    }
     h->fused = fuse && n > 0 && ((m.slices && !m.panel) || m.compact);
     if (h->fused && (st = dalloc(h, &h->p2, nv)) != CG_OK)
         return st;
@@ -605,6 +629,46 @@ int run_until_stop(cg_handle *h, hipGraphExec_t ge, DevState *st, int32_t *statu
     }
 }
 
+// Resident solves in flight on each device, in workgroups.  A solve is
+// resident only while all of them together have at most one workgroup per
+// compute unit: then a workgroup that has not started finds a compute unit
+// with none of them, so all start whatever else runs, and no two solves wait
+// for each other's place.
+constexpr int kMaxDevices = 64;
+std::atomic<int> g_resident_wgs[kMaxDevices];
+
+class ResidentPlace {
+    std::atomic<int> *count_ = nullptr;
+    int wgs_ = 0;
+
+public:
+    ResidentPlace(int device, int wgs, int limit)
+    {
+        if (wgs <= 0 || device < 0 || device >= kMaxDevices)
+            return;
+        std::atomic<int> &c = g_resident_wgs[device];
+        int cur = c.load();
+        while (cur + wgs <= limit)
+            if (c.compare_exchange_weak(cur, cur + wgs)) {
+                count_ = &c;
+                wgs_ = wgs;
+                return;
+            }
+    }
+    ~ResidentPlace()
+    {
+        if (count_)
+            count_->fetch_sub(wgs_);
+    }
+    ResidentPlace(const ResidentPlace &) = delete;
+    ResidentPlace &operator=(const ResidentPlace &) = delete;
+    explicit operator bool() const { return count_ != nullptr; }
+};
+
+// Iterations of one resident launch: bounds the time a kernel runs (a few
+// milliseconds); the next launch goes on from the vectors it left.
+constexpr int kResidentIters = 1024;
+
 int read_state(cg_handle *h, DevState *st, DevState *out)
 {
     hipError_t e;
@@ -613,6 +677,47 @@ int read_state(cg_handle *h, DevState *st, DevState *out)
         (e = hipStreamSynchronize(h->stream)) != hipSuccess)
         return hip_fail(h->err, e, "state readback");
     *out = h->host_st[0];
+    return CG_OK;
+}
+
+// The iteration of an initialised solve as resident launches.  *status: where
+// it stopped, or kRun when a wait ran out (the solve is then lost).
+int run_resident(cg_handle *h, int32_t *status)
+{
+    const DevMatrix &m = h->dm;
+    ResidentArgs a;
+    a.n = m.n;
+    a.ns = m.nslices;
+    a.chunk = m.vec_chunk;
+    a.iters = kResidentIters;
+    a.nsig = m.csr_blocks;
+    a.nvec = m.vec_blocks;
+    a.off = m.sl_off;
+    a.val = m.sl_val;
+    a.gptr = m.rs_gptr;
+    a.gcol = m.rs_gcol;
+    a.lcol = m.rs_lcol;
+    a.lown = m.rs_lown;
+    a.r = h->r;
+    a.p = h->p;
+    a.x = h->xw;
+    a.q = h->q;
+    a.st = h->st;
+    a.words = h->words;
+    a.wait = 25000000; // 0.25 s; tests: CGMI_RESIDENT_WAIT
+    if (const char *e = std::getenv("CGMI_RESIDENT_WAIT"))
+        a.wait = std::atoll(e);
+    DevState s;
+    do {
+        launch_resident(m, a, h->stream);
+        const hipError_t e = hipGetLastError();
+        const int st = read_state(h, h->st, &s); // (waits for the launch in any case)
+        if (e != hipSuccess)
+            return hip_fail(h->err, e, "resident solve");
+        if (st != CG_OK)
+            return st;
+    } while (s.status == kRun && !s.aborted);
+    *status = s.aborted ? (int32_t)kRun : s.status;
     return CG_OK;
 }
 
@@ -630,9 +735,9 @@ int mixed_rescale(cg_handle *h)
     if (h->dm.vperm != nullptr)
         launch_permute(h->dm.n, sc, h->dm.vperm, const_cast<double *>(h->dm.dscale), s);
     HIP_TRY(h, hipGetLastError());
-    HIP_TRY(h, hipMemcpyAsync(&h->host_st[0].pad, h->flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(h, hipMemcpyAsync(&h->host_st[0].aborted, h->flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
-    if (h->host_st[0].pad) {
+    if (h->host_st[0].aborted) {
         h->err = "CG_MIXED needs a positive, finite diagonal entry in every line";
         return CG_ERR_ARG;
     }
@@ -914,6 +1019,8 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
         h->mixed = (flags & CG_MIXED) != 0;
         if (st == CG_OK) {
             hipError_t e = hipGetDevice(&h->device);
+            if (e == hipSuccess)
+                e = hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device);
             st = e == hipSuccess ? upload_all(h.get(), p0, i0, vals) : hip_fail(h->err, e, "hipGetDevice");
         }
         if (st == CG_OK && !perm.empty())
@@ -1036,24 +1143,38 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
         return done(CG_ERR_ARG);
     }
     hipStream_t s = h->stream;
-    int st = build_graph(h);
-    if (st != CG_OK)
-        return done(st);
+    int st;
+    hipError_t e;
     // initialisation (b and x0 in the device row order)
     const double *bi = vec_into(h, b, h->bp);
-    const double *x0 = vec_into(h, x, h->xw);
-    launch_spmv(h->dm, x0, h->q, h->sig_spmv, IterCtx{}, s);
-    launch_init_vec(h->dm, bi, x0, h->q, h->r, h->p, h->xw, h->rho, h->bb, s);
-    launch_init_state(h->dm, h->st, h->bb, h->rho, tol, maxit, s);
-    if (h->fused) // the first fused step forms p_0 = r_0 + beta * 0
-        launch_fill(n, h->p, 0.0, s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return done(hip_fail(h->err, e, "launch"));
-    // iteration: two graph launches in flight, poll the older one's state
+    auto start = [&](bool from_zero) {
+        const double *x0 = vec_into(h, x, h->xw);
+        launch_spmv(h->dm, x0, h->q, h->sig_spmv, IterCtx{}, s);
+        launch_init_vec(h->dm, bi, x0, h->q, h->r, h->p, h->xw, h->rho, h->bb, s);
+        launch_init_state(h->dm, h->st, h->bb, h->rho, tol, maxit, s);
+        if (from_zero) // the first step forms p_0 = r_0 + beta * 0
+            launch_fill(n, h->p, 0.0, s);
+        return hipGetLastError();
+    };
     int32_t status = kRun;
-    if ((st = run_until_stop(h, h->gexec, h->st, &status)) != CG_OK)
-        return done(st);
+    // the whole iteration in one kernel where it is planned and has a place
+    if (const ResidentPlace place{h->device, h->dm.rs_wgs, h->cus}) {
+        if ((e = start(true)) != hipSuccess)
+            return done(hip_fail(h->err, e, "launch"));
+        if ((st = run_resident(h, &status)) != CG_OK)
+            return done(st);
+        if (status == kRun) // a wait ran out: launches from now on
+            h->dm.rs_wgs = 0;
+    }
+    if (status == kRun) {
+        if ((st = build_graph(h)) != CG_OK)
+            return done(st);
+        if ((e = start(h->fused)) != hipSuccess)
+            return done(hip_fail(h->err, e, "launch"));
+        // two graph launches in flight, poll the older one's state
+        if ((st = run_until_stop(h, h->gexec, h->st, &status)) != CG_OK)
+            return done(st);
+    }
     // finish: copy x out, true residual of the returned x
     if (status == kConverged || status == kMaxit || status == kBreakdown) {
         e = vec_out_of(h, h->xw, x);

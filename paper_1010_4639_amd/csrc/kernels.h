@@ -43,7 +43,7 @@ struct DevState {
     double res_true; // ||b - A x|| / ||b|| (filled after the loop)
     double rho_next; // r'r after the latest r update (published for the next iteration's gate)
     int32_t conv_next; // sqrt(rho_next) <= tol_nb
-    int32_t pad;
+    int32_t aborted;   // a resident solve gave up waiting (resident.hip)
 };
 
 // Device image of a planned matrix.
@@ -112,6 +112,12 @@ struct DevMatrix {
     // sliced kernels: ordinary (cache-allocating) loads of the matrix streams
     // when the product's bytes fit the Infinity Cache, non-temporal otherwise
     bool matrix_cached = false;
+    // whole solve in one kernel (resident.hip; rs_wgs = 0: not planned)
+    int rs_wgs = 0, rs_threads = 0, rs_slices = 0; // workgroups, their threads, slices per wavefront
+    int rs_width = 0, rs_cols = 0;       // entries per line, columns per workgroup at most
+    const int32_t *rs_gptr = nullptr, *rs_gcol = nullptr; // columns of each workgroup's rows
+    const uint16_t *rs_lcol = nullptr;   // LDS place (bytes) of each entry's column, [slice][k][lane]
+    const uint16_t *rs_lown = nullptr;   // place (elements) of each row itself
     // vectors
     int vec_blocks = 0, vec_chunk = 0;
     int spmv_blocks() const { return format == kCsr || slices ? csr_blocks : scatter_wgs; }
@@ -155,6 +161,29 @@ void launch_spmv(const DevMatrix &m, const double *x, double *y, double *sig_par
 // y = A32 x with the FP32 copy of the scaled values (FP64 arithmetic).
 void launch_spmv32(const DevMatrix &m, const float *x, double *y, double *sig_part, const IterCtx &c,
                    hipStream_t s);
+// A resident solve (resident.hip) from the state, r, p and x that the
+// initialisation left (p = 0, rho = rho_next = r'r), at most `iters`
+// iterations: then the state says kRun and the next launch goes on from r, p
+// (the last direction), x, rho (the last but one r'r) and rho_next.
+// state->aborted: a wait ran out, r, p and x are lost.
+struct ResidentArgs {
+    int n, ns, chunk, iters;
+    int nsig, nvec; // product and vector workgroups of the launches: partials of p'q and r'r
+    const int32_t *off;
+    const double *val;
+    const int32_t *gptr, *gcol;
+    const uint16_t *lcol, *lown;
+    double *r, *p, *x, *q;
+    DevState *st;
+    unsigned long long *words; // resident_words
+    int64_t wait;              // ticks of the 100 MHz clock a wait may take; < 0: none (tests)
+};
+constexpr int kResidentRing = 4; // rounds that an exchanged word goes round
+constexpr int64_t resident_words(int64_t nsig, int64_t nvec, int64_t n) // two sums; residual entries, product sums
+{
+    return kResidentRing * (nsig + nvec + 2 * n);
+}
+void launch_resident(const DevMatrix &m, const ResidentArgs &a, hipStream_t s);
 // r -= alpha q with alpha = rho / sum(sig_part); rho_part <- partials of r'r.
 // rows_deferred: q came from a product launched with defer_rows, so each
 // q_i is finished here from the parked slot sums first.

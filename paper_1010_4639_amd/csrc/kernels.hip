@@ -1499,6 +1499,7 @@ __global__ __launch_bounds__(kBlock) void k_init_state(DevState *st, const doubl
         st->tol_nb = tol * nb;
         st->rho_next = rho;
         st->conv_next = sqrt(rho) <= tol * nb ? 1 : 0;
+        st->aborted = 0;
         st->status = !isfinite(nb) ? kNonfinite : (nb == 0.0 ? kZeroRhs : kRun);
     }
 }

@@ -220,12 +220,32 @@ static void plan_vectors(Plan &p)
     p.vec_chunk = (int)((n + g - 1) / g);
 }
 
+// Whether 16-bit offsets hold the columns of the slices (plan.h): each within
+// 32767 of the row its line adds to (line_row: the row of each line; null: the
+// line itself, CSR).  Columns ascend along a line, so its ends decide.
+// Experiments: CGMI_COL16=0 keeps 32-bit columns.
+static bool columns_banded(int64_t nl, const int32_t *seg_ptr, const int32_t *seg_col, const int32_t *line_row)
+{
+    if (const char *e = std::getenv("CGMI_COL16"))
+        if (std::strcmp(e, "0") == 0)
+            return false;
+    for (int64_t l = 0; l < nl; ++l) {
+        if (seg_ptr[l] == seg_ptr[l + 1])
+            continue;
+        const int64_t row = line_row ? line_row[l] : l;
+        if (seg_col[seg_ptr[l]] - row < -32767 || seg_col[seg_ptr[l + 1] - 1] - row > 32767)
+            return false;
+    }
+    return true;
+}
+
 // Slices (see plan.h) over `nl` lines whose entries are seg_ptr[l] ..
-// seg_ptr[l + 1] - 1, with columns seg_col and caller entries seg_src (null:
-// the position itself).  mode: 0 = when lines are short and the padding is
-// small, 1 = whenever the padded size fits 32-bit positions.
+// seg_ptr[l + 1] - 1, with ascending columns seg_col and caller entries seg_src
+// (null: the position itself); line_row: the row each line adds to (null:
+// itself).  mode: 0 = when lines are short and the padding is small, 1 =
+// whenever the padded size fits 32-bit positions.
 static bool plan_slices(Plan &p, int64_t nl, const int32_t *seg_ptr, const int32_t *seg_col, const int32_t *seg_src,
-                        int mode)
+                        const int32_t *line_row, int mode)
 {
     const int64_t nnz = nl > 0 ? seg_ptr[nl] : 0;
     const int64_t ns = (nl + kSliceRows - 1) / kSliceRows;
@@ -246,14 +266,21 @@ static bool plan_slices(Plan &p, int64_t nl, const int32_t *seg_ptr, const int32
     p.sl_lines = nl;
     p.sl_off.assign(off.begin(), off.end());
     p.sl_src.assign((size_t)padded, -1);
-    p.sl_col.assign((size_t)padded, -1);
+    const bool banded = columns_banded(nl, seg_ptr, seg_col, line_row);
+    if (banded)
+        p.sl_d16.assign((size_t)padded, kPad16);
+    else
+        p.sl_col.assign((size_t)padded, -1);
     for (int64_t r = 0; r < nl; ++r) {
         const int64_t sl = r / kSliceRows, lane = r % kSliceRows;
-        const int64_t w = (off[sl + 1] - off[sl]) / kSliceRows;
+        const int64_t w = (off[sl + 1] - off[sl]) / kSliceRows, row = line_row ? line_row[r] : r;
         for (int64_t k = seg_ptr[r]; k < seg_ptr[r + 1]; ++k) {
             const int64_t q = off[sl] + slice_position(k - seg_ptr[r], lane, w);
             p.sl_src[q] = seg_src ? seg_src[k] : (int32_t)k;
-            p.sl_col[q] = seg_col[k];
+            if (banded)
+                p.sl_d16[q] = (int16_t)(seg_col[k] - row);
+            else
+                p.sl_col[q] = seg_col[k];
         }
     }
     // one slice per wavefront up to kMaxSliceWgs workgroups, then each wave
@@ -277,43 +304,13 @@ static int slice_mode()
     return std::strcmp(e, "slices") == 0 ? 1 : std::strcmp(e, "rows") == 0 ? -1 : 0;
 }
 
-// 16-bit column offsets of CSR slices or CSC panel-slot slices (plan.h) when
-// every column is within 32767 of the row its line adds to (line_row: the
-// row of each line; null: the line itself, CSR); experiments: CGMI_COL16=0
-// keeps 32-bit columns.
-static void plan_col16(Plan &p, const int32_t *line_row)
-{
-    if (const char *e = std::getenv("CGMI_COL16"))
-        if (std::strcmp(e, "0") == 0)
-            return;
-    const int64_t ns = (int64_t)p.sl_off.size() - 1;
-    std::vector<int16_t> d16(p.sl_col.size(), kPad16);
-    for (int64_t sl = 0; sl < ns; ++sl) {
-        const int64_t w = (p.sl_off[sl + 1] - p.sl_off[sl]) / kSliceRows;
-        for (int64_t lane = 0; lane < kSliceRows; ++lane)
-            for (int64_t k = 0; k < w; ++k) {
-                const int64_t q = p.sl_off[sl] + slice_position(k, lane, w);
-                if (p.sl_col[q] < 0)
-                    continue;
-                const int64_t l = sl * kSliceRows + lane;
-                const int64_t d = (int64_t)p.sl_col[q] - (line_row ? line_row[l] : l);
-                if (d < -32767 || d > 32767)
-                    return;
-                d16[q] = (int16_t)d;
-            }
-    }
-    p.sl_d16.swap(d16);
-}
-
 static void plan_csr(Plan &p, const int32_t *ptr, const int32_t *idx)
 {
     const int64_t n = p.n;
     const double mean = (double)p.nnz / (double)n;
     const int mode = slice_mode();
-    if (mode >= 0 && plan_slices(p, n, ptr, idx, nullptr, mode)) {
-        plan_col16(p, nullptr);
+    if (mode >= 0 && plan_slices(p, n, ptr, idx, nullptr, nullptr, mode))
         return;
-    }
     if (mean <= kStreamMaxMeanRow) {
         // row blocks: <= `be` entries (<= kStreamEntries) and <= kStreamRows
         // rows; a row longer than kStreamEntries is a block of its own
@@ -438,8 +435,7 @@ static int plan_panels(Plan &p, const int32_t *ptr, const int32_t *idx, std::str
     p.max_lines = 0;
     const int mode = slice_mode();
     if (mode >= 0)
-        if (plan_slices(p, ns, p.pn_slot_ptr.data(), p.pn_col.data(), p.pn_src.data(), mode))
-            plan_col16(p, p.pn_slot_target.data());
+        plan_slices(p, ns, p.pn_slot_ptr.data(), p.pn_col.data(), p.pn_src.data(), p.pn_slot_target.data(), mode);
     return CG_OK;
 }
 
@@ -979,6 +975,86 @@ static bool plan_sym_compact(Plan &p, const int32_t *ptr, const int32_t *idx)
     return true;
 }
 
+// Resident solve (plan.h) of the CSR rows ptr / idx in the plan's slices.  A
+// workgroup stands for one vector workgroup of the launches per 256 threads
+// and for a run of product workgroups, so that its sums have their order.
+// 256 threads and one slice per wavefront up to 256 vector workgroups (n <=
+// 65 536); twice the threads, and one or two slices, up to 512 of at most 512
+// rows (n <= 262 144): a larger matrix does not fit the registers.  Lines and
+// column lists have to fit what the kernels hold.  Experiments:
+// CGMI_RESIDENT=0, never; CGMI_RESIDENT=256, the small form only.
+static void plan_resident(Plan &p, const int32_t *ptr, const int32_t *idx)
+{
+    bool wide_allowed = true;
+    if (const char *e = std::getenv("CGMI_RESIDENT")) {
+        if (std::strcmp(e, "0") == 0)
+            return;
+        wide_allowed = std::strcmp(e, "256") != 0;
+    }
+    const int64_t n = p.n, ns = (int64_t)p.sl_off.size() - 1, nsig = p.csr_blocks, nvec = p.vec_blocks;
+    if (!p.slices || ns > nsig * kWavesPerBlock || nsig > 4 * kBlock)
+        return;
+    const bool wide = nvec > kResidentWgs;
+    const int64_t G = wide ? (nvec + 1) / 2 : nvec, waves = wide ? 8 : 4;
+    if (G > kResidentWgs || (wide && !wide_allowed))
+        return;
+    int64_t width = 0, slices = (p.vec_chunk + kBlock - 1) / kBlock; // slices per wavefront = vector rows per thread
+    for (int64_t s = 0; s < ns; ++s)
+        width = std::max<int64_t>(width, (p.sl_off[s + 1] - p.sl_off[s]) / kSliceRows);
+    // first product workgroup and first slice of workgroup b
+    const auto first_wg = [&](int64_t b) { return b * nsig / G; };
+    const auto first_slice = [&](int64_t b) { return first_wg(b) * ns / nsig; };
+    for (int64_t b = 0; b < G; ++b)
+        slices = std::max<int64_t>(slices, (first_slice(b + 1) - first_slice(b) + waves - 1) / waves);
+    const int64_t cols = wide ? (slices == 1 ? 6 : 10) * 384 : 16 * 192;
+    if (slices > (wide ? 2 : 1) || width > (wide ? 16 : 32))
+        return;
+    std::vector<int32_t> gptr(1, 0), gcol, place((size_t)n);
+    std::vector<uint16_t> mark((size_t)n, 0); // workgroup + 1 that touched the column last
+    std::vector<uint16_t> lcol((size_t)p.sl_off[ns], 0xffff), lown((size_t)n, 0);
+    int64_t most = 0;
+    for (int64_t b = 0; b < G; ++b) {
+        const int64_t r0 = first_slice(b) * kSliceRows, r1 = std::min(n, first_slice(b + 1) * kSliceRows);
+        const uint16_t id = (uint16_t)(b + 1);
+        int64_t lo = n, hi = -1;
+        for (int64_t r = r0; r < r1; ++r) {
+            mark[r] = id;
+            for (int64_t k = ptr[r]; k < ptr[r + 1]; ++k)
+                mark[idx[k]] = id;
+            const int64_t c0 = ptr[r] < ptr[r + 1] ? std::min<int64_t>(r, idx[ptr[r]]) : r; // columns ascend
+            const int64_t c1 = ptr[r] < ptr[r + 1] ? std::max<int64_t>(r, idx[ptr[r + 1] - 1]) : r;
+            lo = std::min(lo, c0);
+            hi = std::max(hi, c1);
+        }
+        const size_t first = gcol.size();
+        for (int64_t c = lo; c <= hi; ++c)
+            if (mark[c] == id) {
+                place[c] = (int32_t)(gcol.size() - first);
+                gcol.push_back((int32_t)c);
+            }
+        const int64_t len = (int64_t)(gcol.size() - first);
+        if (len > cols)
+            return;
+        for (int64_t r = r0; r < r1; ++r) {
+            const int64_t s = r / kSliceRows;
+            lown[r] = (uint16_t)place[r];
+            for (int64_t k = ptr[r]; k < ptr[r + 1]; ++k)
+                lcol[p.sl_off[s] + (k - ptr[r]) * kSliceRows + r % kSliceRows] = (uint16_t)(8 * place[idx[k]]);
+        }
+        most = std::max(most, len);
+        gptr.push_back((int32_t)gcol.size());
+    }
+    p.rs_wgs = (int)G;
+    p.rs_threads = (int)(waves * kSliceRows);
+    p.rs_slices = (int)slices;
+    p.rs_width = (int)width;
+    p.rs_cols = (int)most;
+    p.rs_gptr.swap(gptr);
+    p.rs_gcol.swap(gcol);
+    p.rs_lcol.swap(lcol);
+    p.rs_lown.swap(lown);
+}
+
 // Symmetric CSR on a small system (vector kernels of at most 256
 // workgroups, n <= 65 536): there the product is bound by its launch and
 // its chain of dependent steps, not by the bytes the triangle saves, and the
@@ -1017,9 +1093,9 @@ static bool plan_sym_expanded(Plan &p, const int32_t *ptr, const int32_t *idx)
                 fsrc[next[j]++] = (int32_t)k;
             }
         }
-    if (!plan_slices(p, n, fptr.data(), fcol.data(), fsrc.data(), slice_mode()))
+    if (!plan_slices(p, n, fptr.data(), fcol.data(), fsrc.data(), nullptr, slice_mode()))
         return false;
-    plan_col16(p, nullptr);
+    plan_resident(p, fptr.data(), fcol.data());
     p.sym_expanded = true;
     return true;
 }
@@ -1038,6 +1114,7 @@ int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int
     plan_vectors(p);
     if (fmt == kCsr) {
         plan_csr(p, ptr0, idx0);
+        plan_resident(p, ptr0, idx0);
         p.cached = decide_cached(p);
         return CG_OK;
     }

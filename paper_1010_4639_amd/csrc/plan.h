@@ -102,6 +102,9 @@ constexpr double kSliceMaxPadding = 0.125; // slices only while padding <= this 
 // FEM systems: at 110^3 (~325 MB) ordinary loads are 6-12 % faster per
 // iteration, at 120^3 (~378 MB) 4-14 % slower.
 constexpr int64_t kCacheResidentBytes = 336ll << 20;
+// Resident solves (resident.hip): workgroups at most, the compute units of the
+// device (one each, so that all are resident at once).
+constexpr int kResidentWgs = 256;
 constexpr int kPanelMinWidth = 4096;    // CSC panels span at least this many columns
 constexpr int kPanelChunkEntries = kStreamEntries; // entries per CSC panel chunk
 constexpr int kPanelChunkSlots = kBlock;           // slots per CSC panel chunk (one thread each)
@@ -159,7 +162,7 @@ struct Plan {
     int64_t sl_lines = 0;                 // rows (CSR) or slots (CSC)
     std::vector<int32_t> sl_off;          // [slices + 1] first position of each slice (multiple of 64)
     std::vector<int32_t> sl_src;          // [positions] caller entry (0-based) at each position, -1 = padding
-    std::vector<int32_t> sl_col;          // [positions] column at each position, -1 = padding
+    std::vector<int32_t> sl_col;          // [positions] column at each position, -1 = padding (empty if sl_d16 is not)
     std::vector<int16_t> sl_d16;          // banded: column - (row of the line) at each position, kPad16 = padding (else empty)
     // scatter formats
     int nblocks = 0, ncolors = 0, max_entries = 0, max_lines = 0, max_slots = 0;
@@ -206,6 +209,15 @@ struct Plan {
     int32_t pn_first_parked = 0;          // slots >= this belong to colour 1
     // vector kernels
     int vec_blocks = 0, vec_chunk = 0;
+    // Whole solve in one kernel (resident.hip): sliced CSR rows, rs_wgs
+    // workgroups of rs_threads threads, rs_slices slices per wavefront.  Per
+    // workgroup the ascending list of the columns its rows touch, the rows
+    // themselves among them; per entry the place of its column in that list
+    // (bytes of a double, 0xffff = padding; entry k of lane l of a slice at
+    // off + 64 k + l), per row its own.
+    int rs_wgs = 0, rs_threads = 0, rs_slices = 0, rs_width = 0, rs_cols = 0;
+    std::vector<int32_t> rs_gptr, rs_gcol;
+    std::vector<uint16_t> rs_lcol, rs_lown;
 
     // bytes one sliced product reads from the matrix side (positions, slot
     // descriptors, contribution lists, parked sums); 0 if not sliced
