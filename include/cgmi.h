@@ -157,7 +157,10 @@ int cg_set_batch(cg_handle *h, int32_t iters_per_launch);
  * r -= alpha Ap, beta = r'r / r_old'r_old, p = r + beta p), with the one
  * product Ap per iteration of that section and every scalar kept on the
  * device -- the paper moves only the scalars between host and GPU; here the
- * host reads a status word once per launched group of iterations.
+ * host reads a status word once per launched group of iterations.  Systems of
+ * at most 262 144 rows whose rows are sliced run the whole iteration in one
+ * kernel where a workgroup per compute unit has a place on the device (same
+ * bits as the launches it takes otherwise).
  *   b     device, n float64 (read only)
  *   x     device, n float64: in x0, out the solution / last iterate; a
  *         buffer distinct from b (CG_ERR_ARG otherwise).
@@ -244,8 +247,9 @@ const char *cg_batch_last_error(const cg_batch *h);
 /* y = A x (device pointers, n float64 each, x and y must not overlap):
  * the sparse matrix-vector product of section III in the handle's storage
  * (CSR: one sum per row; symmetric: the stored triangle by rows plus its
- * mirror by columns; CSC: column scatter).  Asynchronous on the handle's
- * stream. */
+ * mirror by columns; CSC, and symmetric systems of at most 262 144 rows: one
+ * sum per row of the full rows that the handle lays out beside the format's
+ * own plan).  Asynchronous on the handle's stream. */
 int cg_spmv(cg_handle *h, const double *x, double *y);
 
 /*

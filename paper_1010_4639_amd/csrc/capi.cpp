@@ -35,6 +35,16 @@ static __device__ __align__(256) double scratch[(32u << 20) / sizeof(double)];
 struct cg_handle {
     Plan plan;
     DevMatrix dm;
+    // second layout by rows (plan.h: build_row_plan; rows.n = 0: none): lone
+    // products, and with rows_solve the iteration of cg_solve
+    Plan row_plan;
+    DevMatrix rows;
+    bool rows_solve = false;
+    // products and solves all run by rows: the storage format's own layout is
+    // planned (its summary is the handle's) but not kept on the device
+    bool lean = false;
+    const DevMatrix &product() const { return rows.n > 0 ? rows : dm; }
+    DevMatrix &solver() { return rows_solve ? rows : dm; }
     int device = 0;
     int cus = 0;                   // compute units of the device
     hipStream_t stream = nullptr;  // caller's stream (null stream by default)
@@ -137,6 +147,68 @@ void release(cg_handle *h)
     h->allocs.clear();
 }
 
+// The sliced layout of a plan, and its resident solve.
+int upload_slices(cg_handle *h, const Plan &p, DevMatrix &m, bool val32)
+{
+    int st;
+    int32_t *off, *col = nullptr, *src;
+    int16_t *d16 = nullptr;
+    double *sv;
+    if ((st = upload(h, &off, p.sl_off.data(), p.sl_off.size())) != CG_OK ||
+        (p.sl_d16.empty() ? (st = upload(h, &col, p.sl_col.data(), p.sl_col.size()))
+                          : (st = upload(h, &d16, p.sl_d16.data(), p.sl_d16.size()))) != CG_OK ||
+        (st = upload(h, &src, p.sl_src.data(), p.sl_src.size())) != CG_OK ||
+        (st = dalloc(h, &sv, std::max<size_t>(p.sl_src.size(), 1))) != CG_OK)
+        return st;
+    m.slices = true;
+    m.sl_lines = (int)p.sl_lines;
+    m.nslices = (int)p.sl_off.size() - 1;
+    m.sl_off = off;
+    m.sl_col = col;
+    m.sl_d16 = d16;
+    m.sl_src = src;
+    m.sl_val = sv;
+    if (p.rs_wgs > 0) {
+        int32_t *gp, *gc;
+        uint16_t *lc, *lo;
+        if ((st = upload(h, &gp, p.rs_gptr.data(), p.rs_gptr.size())) != CG_OK ||
+            (st = upload(h, &gc, p.rs_gcol.data(), p.rs_gcol.size())) != CG_OK ||
+            (st = upload(h, &lc, p.rs_lcol.data(), p.rs_lcol.size())) != CG_OK ||
+            (st = upload(h, &lo, p.rs_lown.data(), p.rs_lown.size())) != CG_OK ||
+            (st = dalloc(h, &h->words, (size_t)resident_words(p.csr_blocks, p.vec_blocks, p.n))) != CG_OK)
+            return st;
+        m.rs_wgs = p.rs_wgs;
+        m.rs_threads = p.rs_threads;
+        m.rs_slices = p.rs_slices;
+        m.rs_width = p.rs_width;
+        m.rs_cols = p.rs_cols;
+        m.rs_gptr = gp;
+        m.rs_gcol = gc;
+        m.rs_lcol = lc;
+        m.rs_lown = lo;
+    }
+    if (val32 && (st = dalloc(h, &m.sl_val32, std::max<size_t>(p.sl_src.size(), 1))) != CG_OK)
+        return st;
+    return CG_OK;
+}
+
+// The second layout by rows (plan.h): the fields that its products and its
+// iteration read.
+int upload_rows(cg_handle *h)
+{
+    const Plan &p = h->row_plan;
+    DevMatrix &m = h->rows;
+    m.format = kCsr;
+    m.n = (int)p.n;
+    m.lanes = p.lanes;
+    m.csr_blocks = p.csr_blocks;
+    m.vec_blocks = p.vec_blocks;
+    m.vec_chunk = p.vec_chunk;
+    m.matrix_cached = p.matrix_cached();
+    h->rows_solve = p.rs_wgs > 0;
+    return upload_slices(h, p, m, false);
+}
+
 int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector<int32_t> &idx0, const double *vals)
 {
     const Plan &p = h->plan;
@@ -182,47 +254,13 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
         m.csr_rbe = rbe;
         m.csr_nrb = (int)p.csr_rb.size() - 1;
     }
-    if (p.slices) {
-        int32_t *off, *col = nullptr, *src;
-        int16_t *d16 = nullptr;
-        double *sv;
-        if ((st = upload(h, &off, p.sl_off.data(), p.sl_off.size())) != CG_OK ||
-            (p.sl_d16.empty() ? (st = upload(h, &col, p.sl_col.data(), p.sl_col.size()))
-                              : (st = upload(h, &d16, p.sl_d16.data(), p.sl_d16.size()))) != CG_OK ||
-            (st = upload(h, &src, p.sl_src.data(), p.sl_src.size())) != CG_OK ||
-            (st = dalloc(h, &sv, std::max<size_t>(p.sl_src.size(), 1))) != CG_OK)
-            return st;
-        m.slices = true;
-        m.sl_lines = (int)p.sl_lines;
-        m.nslices = (int)p.sl_off.size() - 1;
-        m.sl_off = off;
-        m.sl_col = col;
-        m.sl_d16 = d16;
-        m.sl_src = src;
-        m.sl_val = sv;
-        if (p.rs_wgs > 0) {
-            int32_t *gp, *gc;
-            uint16_t *lc, *lo;
-            if ((st = upload(h, &gp, p.rs_gptr.data(), p.rs_gptr.size())) != CG_OK ||
-                (st = upload(h, &gc, p.rs_gcol.data(), p.rs_gcol.size())) != CG_OK ||
-                (st = upload(h, &lc, p.rs_lcol.data(), p.rs_lcol.size())) != CG_OK ||
-                (st = upload(h, &lo, p.rs_lown.data(), p.rs_lown.size())) != CG_OK ||
-                (st = dalloc(h, &h->words, (size_t)resident_words(p.csr_blocks, p.vec_blocks, n))) != CG_OK)
-                return st;
-            m.rs_wgs = p.rs_wgs;
-            m.rs_threads = p.rs_threads;
-            m.rs_slices = p.rs_slices;
-            m.rs_width = p.rs_width;
-            m.rs_cols = p.rs_cols;
-            m.rs_gptr = gp;
-            m.rs_gcol = gc;
-            m.rs_lcol = lc;
-            m.rs_lown = lo;
-        }
-        if (h->mixed && (st = dalloc(h, &m.sl_val32, std::max<size_t>(p.sl_src.size(), 1))) != CG_OK)
-            return st;
-    }
-    if (p.panel && n > 0) {
+    const bool lean = h->lean = h->row_plan.rs_wgs > 0 && !h->mixed;
+    if (p.slices && !lean && (st = upload_slices(h, p, m, h->mixed)) != CG_OK)
+        return st;
+    m.own_rows = p.format == kCsr;
+    if (lean) {
+        // (nothing of the format's layout)
+    } else if (p.panel && n > 0) {
         // CSC column panels: slots of colour 0 first (see plan.h).  A row
         // meets at most two panels, one of each colour (W >= 2 bw + 1), so it
         // has at most one parked sum: parked sums are stored by row, and one
@@ -447,15 +485,18 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
     // There every product workgroup reducing the r'r partials and gathering
     // r and p costs less than the third launch; on large systems it costs
     // more.  Experiments: CGMI_FUSED=0 / 1 (1: wherever the plan allows).
+    if (h->row_plan.n > 0 && (st = upload_rows(h)) != CG_OK)
+        return st;
+    DevMatrix &it = h->solver();
     bool fuse = p.vec_blocks <= kBlock;
     if (const char *e = std::getenv("CGMI_FUSED")) {
         fuse = std::strcmp(e, "0") != 0;
-        m.rs_wgs = 0;
+        it.rs_wgs = 0;
     }
-    h->fused = fuse && n > 0 && ((m.slices && !m.panel) || m.compact);
+    h->fused = fuse && n > 0 && ((it.slices && !it.panel) || it.compact);
     if (h->fused && (st = dalloc(h, &h->p2, nv)) != CG_OK)
         return st;
-    const size_t ns = (size_t)std::max(1, std::max(p.spmv_blocks(), p.vec_blocks));
+    const size_t ns = (size_t)std::max({1, p.spmv_blocks(), p.vec_blocks, h->rows.csr_blocks});
     if ((st = dalloc(h, &h->sig, ns)) != CG_OK || (st = dalloc(h, &h->sig_spmv, ns)) != CG_OK ||
         (st = dalloc(h, &h->rho, ns)) != CG_OK || (st = dalloc(h, &h->bb, ns)) != CG_OK ||
         (st = dalloc(h, &h->st, 1)) != CG_OK)
@@ -521,7 +562,8 @@ void enqueue_iteration(cg_handle *h, hipStream_t s, int parity)
     IterCtx c;
     c.st = h->st;
     c.rho_part = h->rho;
-    c.n_rho = h->dm.vec_blocks;
+    const DevMatrix &m = h->solver();
+    c.n_rho = m.vec_blocks;
     c.defer_rows = true;
     if (h->fused) {
         // product with the direction update (p_(k-1) in one buffer, p_k
@@ -531,13 +573,13 @@ void enqueue_iteration(cg_handle *h, hipStream_t s, int parity)
         c.pnew = parity ? h->p : h->p2;
         c.r = h->r;
         c.x = h->xw;
-        launch_spmv(h->dm, c.pold, h->q, h->sig, c, s);
-        launch_update_r(h->dm, h->r, h->q, h->st, h->sig, h->rho, s, true, true);
+        launch_spmv(m, c.pold, h->q, h->sig, c, s);
+        launch_update_r(m, h->r, h->q, h->st, h->sig, h->rho, s, true, true);
         return;
     }
-    launch_spmv(h->dm, h->p, h->q, h->sig, c, s);
-    launch_update_r(h->dm, h->r, h->q, h->st, h->sig, h->rho, s, true);
-    launch_update_xp(h->dm, h->xw, h->p, h->r, h->st, h->rho, s);
+    launch_spmv(m, h->p, h->q, h->sig, c, s);
+    launch_update_r(m, h->r, h->q, h->st, h->sig, h->rho, s, true);
+    launch_update_xp(m, h->xw, h->p, h->r, h->st, h->rho, s);
 }
 
 // One inner (mixed-precision) iteration: FP32 product, FP64 r update, FP64 c
@@ -684,7 +726,7 @@ int read_state(cg_handle *h, DevState *st, DevState *out)
 // it stopped, or kRun when a wait ran out (the solve is then lost).
 int run_resident(cg_handle *h, int32_t *status)
 {
-    const DevMatrix &m = h->dm;
+    const DevMatrix &m = h->solver();
     ResidentArgs a;
     a.n = m.n;
     a.ns = m.nslices;
@@ -753,6 +795,8 @@ int refresh_values(cg_handle *h, const double *src, const int32_t *order)
     DevMatrix &m = h->dm;
     const int64_t nnz = h->plan.nnz, np = (int64_t)h->plan.sl_src.size();
     launch_fill_layout(m, nnz, np, src, order, h->stream);
+    if (h->rows.n > 0)
+        launch_fill_layout(h->rows, 0, (int64_t)h->row_plan.sl_src.size(), src, order, h->stream);
     HIP_TRY(h, hipGetLastError());
     if (h->mixed && m.n > 0) {
         const int st = mixed_rescale(h);
@@ -769,7 +813,7 @@ int refresh_values(cg_handle *h, const double *src, const int32_t *order)
 int drop_entry_values(cg_handle *h)
 {
     DevMatrix &m = h->dm;
-    if (m.n == 0 || m.keeps_val())
+    if (m.n == 0 || (m.keeps_val() && !h->lean))
         return CG_OK;
     void *p = const_cast<double *>(m.val);
     HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -817,19 +861,19 @@ int static_scratch(cg_handle *h, double **out)
 // renumber their rows; every other plan keeps the caller's order).
 // into(): src in the caller's order -> dst in the device order; returns the
 // vector the device uses.  out_of(): device order -> caller's order.
-const double *vec_into(cg_handle *h, const double *src, double *dst)
+const double *vec_into(cg_handle *h, const DevMatrix &m, const double *src, double *dst)
 {
-    if (h->dm.vperm == nullptr)
+    if (m.vperm == nullptr)
         return src;
-    launch_permute(h->dm.n, src, h->dm.vperm, dst, h->stream);
+    launch_permute(m.n, src, m.vperm, dst, h->stream);
     return dst;
 }
 
-hipError_t vec_out_of(cg_handle *h, const double *src, double *dst)
+hipError_t vec_out_of(cg_handle *h, const DevMatrix &m, const double *src, double *dst)
 {
-    if (h->dm.vinv == nullptr)
-        return hipMemcpyAsync(dst, src, sizeof(double) * (size_t)h->dm.n, hipMemcpyDeviceToDevice, h->stream);
-    launch_permute(h->dm.n, src, h->dm.vinv, dst, h->stream);
+    if (m.vinv == nullptr)
+        return hipMemcpyAsync(dst, src, sizeof(double) * (size_t)m.n, hipMemcpyDeviceToDevice, h->stream);
+    launch_permute(m.n, src, m.vinv, dst, h->stream);
     return hipGetLastError();
 }
 
@@ -1016,6 +1060,8 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
         }
         if (st == CG_OK)
             st = build_plan(format, n, p0.data(), i0.data(), scatter_entries_override(), h->plan, h->err);
+        if (st == CG_OK)
+            build_row_plan(h->plan, p0.data(), i0.data(), h->row_plan);
         h->mixed = (flags & CG_MIXED) != 0;
         if (st == CG_OK) {
             hipError_t e = hipGetDevice(&h->device);
@@ -1073,11 +1119,12 @@ int cg_spmv(cg_handle *h, const double *x, double *y)
         h->err = "x / y NULL or aliased";
         return CG_ERR_ARG;
     }
-    if (h->dm.vperm != nullptr) { // through the device row order
-        launch_spmv(h->dm, vec_into(h, x, h->p), h->q, h->sig_spmv, IterCtx{}, h->stream);
-        HIP_TRY(h, vec_out_of(h, h->q, y));
+    const DevMatrix &m = h->product();
+    if (m.vperm != nullptr) { // through the device row order
+        launch_spmv(m, vec_into(h, m, x, h->p), h->q, h->sig_spmv, IterCtx{}, h->stream);
+        HIP_TRY(h, vec_out_of(h, m, h->q, y));
     } else {
-        launch_spmv(h->dm, x, y, h->sig_spmv, IterCtx{}, h->stream);
+        launch_spmv(m, x, y, h->sig_spmv, IterCtx{}, h->stream);
     }
     HIP_TRY(h, hipGetLastError());
     return CG_OK;
@@ -1093,8 +1140,9 @@ int cg_spmv_static(cg_handle *h, const double *x, double *y)
         h->err = "x / y NULL or aliased";
         return CG_ERR_ARG;
     }
-    // dot partials first (rounded up to 256 bytes), then the parked sums
-    const int64_t nsig = ((int64_t)std::max(1, h->dm.spmv_blocks()) + 31) / 32 * 32;
+    // dot partials first (rounded up to 256 bytes), then the parked sums (the
+    // limit is the storage format's, also where its product runs by rows)
+    const int64_t nsig = ((int64_t)std::max({1, h->dm.spmv_blocks(), h->rows.csr_blocks}) + 31) / 32 * 32;
     const int64_t need = nsig + h->dm.part_doubles;
     if (need > (int64_t)kStaticScratchDoubles) {
         h->err = "cg_spmv_static: the product needs " + std::to_string(need * 8) + " scratch bytes, more than the " +
@@ -1107,11 +1155,12 @@ int cg_spmv_static(cg_handle *h, const double *x, double *y)
         return st;
     IterCtx c;
     c.part = h->dm.part_doubles > 0 ? base + nsig : nullptr;
-    if (h->dm.vperm != nullptr) { // through the device row order (the handle's own vectors, no allocation)
-        launch_spmv(h->dm, vec_into(h, x, h->p), h->q, base, c, h->stream);
-        HIP_TRY(h, vec_out_of(h, h->q, y));
+    const DevMatrix &m = h->product();
+    if (m.vperm != nullptr) { // through the device row order (the handle's own vectors, no allocation)
+        launch_spmv(m, vec_into(h, m, x, h->p), h->q, base, c, h->stream);
+        HIP_TRY(h, vec_out_of(h, m, h->q, y));
     } else {
-        launch_spmv(h->dm, x, y, base, c, h->stream);
+        launch_spmv(m, x, y, base, c, h->stream);
     }
     HIP_TRY(h, hipGetLastError());
     return CG_OK;
@@ -1135,7 +1184,8 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
         h->err = "tol must be >= 0 and maxit >= 0";
         return done(CG_ERR_ARG);
     }
-    const int n = h->dm.n;
+    DevMatrix &m = h->solver();
+    const int n = m.n;
     if (n == 0)
         return done(CG_OK);
     if (!b || !x || b == x) {
@@ -1146,25 +1196,25 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
     int st;
     hipError_t e;
     // initialisation (b and x0 in the device row order)
-    const double *bi = vec_into(h, b, h->bp);
+    const double *bi = vec_into(h, m, b, h->bp);
     auto start = [&](bool from_zero) {
-        const double *x0 = vec_into(h, x, h->xw);
-        launch_spmv(h->dm, x0, h->q, h->sig_spmv, IterCtx{}, s);
-        launch_init_vec(h->dm, bi, x0, h->q, h->r, h->p, h->xw, h->rho, h->bb, s);
-        launch_init_state(h->dm, h->st, h->bb, h->rho, tol, maxit, s);
+        const double *x0 = vec_into(h, m, x, h->xw);
+        launch_spmv(m, x0, h->q, h->sig_spmv, IterCtx{}, s);
+        launch_init_vec(m, bi, x0, h->q, h->r, h->p, h->xw, h->rho, h->bb, s);
+        launch_init_state(m, h->st, h->bb, h->rho, tol, maxit, s);
         if (from_zero) // the first step forms p_0 = r_0 + beta * 0
             launch_fill(n, h->p, 0.0, s);
         return hipGetLastError();
     };
     int32_t status = kRun;
     // the whole iteration in one kernel where it is planned and has a place
-    if (const ResidentPlace place{h->device, h->dm.rs_wgs, h->cus}) {
+    if (const ResidentPlace place{h->device, m.rs_wgs, h->cus}) {
         if ((e = start(true)) != hipSuccess)
             return done(hip_fail(h->err, e, "launch"));
         if ((st = run_resident(h, &status)) != CG_OK)
             return done(st);
         if (status == kRun) // a wait ran out: launches from now on
-            h->dm.rs_wgs = 0;
+            m.rs_wgs = 0;
     }
     if (status == kRun) {
         if ((st = build_graph(h)) != CG_OK)
@@ -1177,11 +1227,11 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
     }
     // finish: copy x out, true residual of the returned x
     if (status == kConverged || status == kMaxit || status == kBreakdown) {
-        e = vec_out_of(h, h->xw, x);
+        e = vec_out_of(h, m, h->xw, x);
         if (e != hipSuccess)
             return done(hip_fail(h->err, e, "copy-out"));
-        launch_spmv(h->dm, h->xw, h->q, h->sig_spmv, IterCtx{}, s);
-        launch_true_residual(h->dm, bi, h->q, h->bb, h->st, s);
+        launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, s);
+        launch_true_residual(m, bi, h->q, h->bb, h->st, s);
     } else if (status == kZeroRhs) {
         launch_fill(n, x, 0.0, s);
     }
@@ -1236,8 +1286,8 @@ int cg_solve_mixed(cg_handle *h, const double *b, double *x, double tol, int32_t
     if (st != CG_OK)
         return done(st);
     // outer start: r = b - A x0, ||b||, ||r|| (FP64 product; device row order)
-    const double *bi = vec_into(h, b, h->bp);
-    const double *x0 = vec_into(h, x, h->xw);
+    const double *bi = vec_into(h, h->dm, b, h->bp);
+    const double *x0 = vec_into(h, h->dm, x, h->xw);
     launch_spmv(h->dm, x0, h->q, h->sig_spmv, IterCtx{}, s);
     launch_init_vec(h->dm, bi, x0, h->q, h->rout, h->p, h->xw, h->rho, h->bb, s);
     launch_init_state(h->dm, h->st, h->bb, h->rho, tol, maxit, s);
@@ -1295,7 +1345,7 @@ int cg_solve_mixed(cg_handle *h, const double *b, double *x, double tol, int32_t
             break;
         }
     }
-    hipError_t e = vec_out_of(h, h->xw, x);
+    hipError_t e = vec_out_of(h, h->dm, h->xw, x);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess)
@@ -1319,7 +1369,7 @@ int cg_set_values(cg_handle *h, const double *vals)
         return CG_ERR_ARG;
     }
     hipStream_t s = h->stream;
-    if (!h->dm.keeps_val()) // straight into the layout the products read
+    if (h->lean || !h->dm.keeps_val()) // straight into the layout the products read
         return refresh_values(h, vals, h->perm);
     launch_set_values(nnz, vals, h->perm, const_cast<double *>(h->dm.val), s);
     HIP_TRY(h, hipGetLastError());

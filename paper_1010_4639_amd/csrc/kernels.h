@@ -62,6 +62,7 @@ struct DevMatrix {
     int csr_nrb = 0;
     const int32_t *csr_rb = nullptr;
     const int2 *csr_rbe = nullptr;       // per row-block boundary: {first row, first entry}
+    bool own_rows = false;               // the slices' lines are the matrix's own rows (ptr), in its entry order
     bool slices = false;                 // sliced layout of CSR rows / CSC panel slots (plan.h)
     int sl_lines = 0, nslices = 0;
     const int32_t *sl_off = nullptr, *sl_col = nullptr, *sl_src = nullptr;

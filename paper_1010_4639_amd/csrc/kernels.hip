@@ -2106,7 +2106,7 @@ void fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, const T 
     // row-contiguous sources (CSR rows, symmetric rows of compact blocks) in
     // the matrix's own order go through the row pointers; a permuted source
     // (lower triangle), panel slots and expanded triangles through the list
-    if (m.slices && m.format == kCsr && order == nullptr) {
+    if (m.slices && m.own_rows && order == nullptr) {
         if (m.nslices > 0)
             hipLaunchKernelGGL(k_fill_slices<T>, dim3((m.nslices + kWaves - 1) / kWaves), dim3(kBlock), 0, s, m.n,
                                m.nslices, m.ptr, m.sl_off, src, sl);

@@ -259,8 +259,9 @@ static bool plan_slices(Plan &p, int64_t nl, const int32_t *seg_ptr, const int32
     const int64_t padded = off[ns];
     if (padded > INT32_MAX || nl > INT32_MAX)
         return false;
-    if (mode == 0 && (nl == 0 || (double)nnz / (double)nl > kStreamMaxMeanRow ||
-                      (double)(padded - nnz) > kSliceMaxPadding * nnz))
+    // (a small layout is bound by launches and latency, not by its padding)
+    const double pad = padded <= kSmallSlicePositions ? 1.0 : kSliceMaxPadding;
+    if (mode == 0 && (nl == 0 || (double)nnz / (double)nl > kStreamMaxMeanRow || (double)(padded - nnz) > pad * nnz))
         return false;
     p.slices = true;
     p.sl_lines = nl;
@@ -1055,6 +1056,63 @@ static void plan_resident(Plan &p, const int32_t *ptr, const int32_t *idx)
     p.rs_lown.swap(lown);
 }
 
+// Full rows of a matrix given otherwise: columns ascending, and for each entry
+// the caller's (normalised) entry that holds its value.
+struct Rows {
+    std::vector<int32_t> ptr, idx, src;
+};
+
+// Columns -> rows (a stable counting sort).
+static void transpose(int64_t n, const int32_t *ptr, const int32_t *idx, Rows &f)
+{
+    const int64_t nnz = ptr[n];
+    f.ptr.assign((size_t)n + 1, 0);
+    f.idx.resize((size_t)nnz);
+    f.src.resize((size_t)nnz);
+    for (int64_t k = 0; k < nnz; ++k)
+        f.ptr[idx[k] + 1]++;
+    for (int64_t i = 0; i < n; ++i)
+        f.ptr[i + 1] += f.ptr[i];
+    std::vector<int32_t> next(f.ptr.begin(), f.ptr.end() - 1);
+    for (int64_t j = 0; j < n; ++j)
+        for (int64_t k = ptr[j]; k < ptr[j + 1]; ++k) {
+            const int32_t q = next[idx[k]]++;
+            f.idx[q] = (int32_t)j;
+            f.src[q] = (int32_t)k;
+        }
+}
+
+// Upper triangle -> full rows: an off-diagonal entry at (i, j) and (j, i), row
+// i's mirrored entries first.  false: too many entries.
+static bool expand_triangle(int64_t n, const int32_t *ptr, const int32_t *idx, Rows &f)
+{
+    f.ptr.assign((size_t)n + 1, 0);
+    if ((int64_t)ptr[n] > INT32_MAX / 4)
+        return false;
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
+            f.ptr[i + 1]++;
+            if (idx[k] != i)
+                f.ptr[idx[k] + 1]++;
+        }
+    for (int64_t i = 0; i < n; ++i)
+        f.ptr[i + 1] += f.ptr[i];
+    f.idx.resize((size_t)f.ptr[n]);
+    f.src.resize((size_t)f.ptr[n]);
+    std::vector<int32_t> next(f.ptr.begin(), f.ptr.end() - 1);
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
+            const int32_t j = idx[k];
+            f.idx[next[i]] = j;
+            f.src[next[i]++] = (int32_t)k;
+            if (j != i) {
+                f.idx[next[j]] = (int32_t)i;
+                f.src[next[j]++] = (int32_t)k;
+            }
+        }
+    return true;
+}
+
 // Symmetric CSR on a small system (vector kernels of at most 256
 // workgroups, n <= 65 536): there the product is bound by its launch and
 // its chain of dependent steps, not by the bytes the triangle saves, and the
@@ -1071,32 +1129,41 @@ static bool plan_sym_expanded(Plan &p, const int32_t *ptr, const int32_t *idx)
         if (std::strcmp(e, "0") == 0)
             return false;
     const int64_t n = p.n;
-    std::vector<int32_t> fptr((size_t)n + 1, 0);
-    for (int64_t i = 0; i < n; ++i)
-        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
-            fptr[i + 1]++;
-            if (idx[k] != i)
-                fptr[idx[k] + 1]++;
-        }
-    for (int64_t i = 0; i < n; ++i)
-        fptr[i + 1] += fptr[i];
-    if (fptr[n] > INT32_MAX / 2)
+    Rows f;
+    if (!expand_triangle(n, ptr, idx, f) ||
+        !plan_slices(p, n, f.ptr.data(), f.idx.data(), f.src.data(), nullptr, slice_mode()))
         return false;
-    std::vector<int32_t> fcol((size_t)fptr[n]), fsrc((size_t)fptr[n]), next(fptr.begin(), fptr.end() - 1);
-    for (int64_t i = 0; i < n; ++i)
-        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
-            const int32_t j = idx[k];
-            fcol[next[i]] = j;
-            fsrc[next[i]++] = (int32_t)k;
-            if (j != i) {
-                fcol[next[j]] = (int32_t)i;
-                fsrc[next[j]++] = (int32_t)k;
-            }
-        }
-    if (!plan_slices(p, n, fptr.data(), fcol.data(), fsrc.data(), nullptr, slice_mode()))
-        return false;
-    plan_resident(p, fptr.data(), fcol.data());
+    plan_resident(p, f.ptr.data(), f.idx.data());
     p.sym_expanded = true;
+    return true;
+}
+
+bool build_row_plan(const Plan &p, const int32_t *ptr, const int32_t *idx, Plan &rows)
+{
+    rows = Plan{};
+    const int64_t n = p.n;
+    if (n == 0 || slice_mode() < 0 || !(p.panel || (p.sym_compact && n <= kRowsSolveMax)))
+        return false;
+    if (const char *e = std::getenv("CGMI_SYM_EXPAND"))
+        if (std::strcmp(e, "0") == 0)
+            return false;
+    Rows f;
+    if (p.panel)
+        transpose(n, ptr, idx, f);
+    else if (!expand_triangle(n, ptr, idx, f))
+        return false;
+    rows.format = kCsr;
+    rows.n = n;
+    rows.nnz = f.ptr[n];
+    rows.lanes = p.lanes;
+    plan_vectors(rows);
+    if (!plan_slices(rows, n, f.ptr.data(), f.idx.data(), f.src.data(), nullptr, 0)) {
+        rows = Plan{};
+        return false;
+    }
+    if (n <= kRowsSolveMax)
+        plan_resident(rows, f.ptr.data(), f.idx.data());
+    rows.cached = decide_cached(rows);
     return true;
 }
 

@@ -95,6 +95,9 @@ constexpr int kSliceRows = 64;          // slices: lines per slice (one wavefron
 constexpr int kWavesPerBlock = kBlock / kSliceRows;
 constexpr int kMaxSliceWgs = 4 * kMaxSpmvBlocks; // slice kernel workgroups (= dot partials)
 constexpr double kSliceMaxPadding = 0.125; // slices only while padding <= this fraction of nnz
+// ... or, up to this many positions (about 4000 grid rows), as much padding as
+// entries: 1000 rows then solve in one kernel (10^3 grid, 25 % padding)
+constexpr int64_t kSmallSlicePositions = 65536;
 // Sliced products read the matrix with ordinary (cache-allocating) loads
 // while the bytes of one iteration (matrix side + 40 B per row of vectors)
 // stay below this, so the matrix stays resident in the 256 MB Infinity Cache
@@ -242,6 +245,18 @@ int validate_and_normalise(int fmt, int64_t n, const int32_t *ptr, const int32_t
 // Builds the plan for 0-based arrays.  target_entries <= 0 selects the default.
 int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int target_entries, Plan &plan,
                std::string &err);
+
+// Second layout of a planned matrix that is not stored by rows: its full rows,
+// sliced like CSR.  CSC: lone products run on it (one sum per row; on the
+// panels a row's sum is in two parts, one of them parked and added by a second
+// kernel: 565 k rows 26.6 -> 17.4 us, 160^3 174 -> 124), and so do solves up to
+// kRowsSolveMax rows, which then can be resident.  Symmetric compact blocks up
+// to that size: both (216 000 rows: product 19.5 -> 7.7 us, solve 4.85 -> 2.38
+// ms; the bytes that the triangle saves do not matter in the caches).  Larger
+// solves keep the panels and the compact blocks.  false: no such layout (another plan, rows too ragged for
+// slices; experiments: CGMI_SYM_EXPAND=0, CGMI_ROW_LAYOUT=rows).
+constexpr int64_t kRowsSolveMax = 262144;
+bool build_row_plan(const Plan &plan, const int32_t *ptr0, const int32_t *idx0, Plan &rows);
 
 int lanes_for_mean_length(double mean_len);
 
