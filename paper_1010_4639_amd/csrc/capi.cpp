@@ -722,9 +722,11 @@ int read_state(cg_handle *h, DevState *st, DevState *out)
     return CG_OK;
 }
 
-// The iteration of an initialised solve as resident launches.  *status: where
-// it stopped, or kRun when a wait ran out (the solve is then lost).
-int run_resident(cg_handle *h, int32_t *status)
+// The iteration of an initialised solve as resident launches, each followed by
+// the end of the solve (x out unless the state says otherwise, the true
+// residual), so that the host waits once.  The state is in host_st[0]; kRun: a
+// wait ran out and the solve is lost.
+int run_resident(cg_handle *h, const double *b, double *x)
 {
     const DevMatrix &m = h->solver();
     ResidentArgs a;
@@ -743,24 +745,28 @@ int run_resident(cg_handle *h, int32_t *status)
     a.r = h->r;
     a.p = h->p;
     a.x = h->xw;
-    a.q = h->q;
     a.st = h->st;
     a.words = h->words;
     a.wait = 25000000; // 0.25 s; tests: CGMI_RESIDENT_WAIT
     if (const char *e = std::getenv("CGMI_RESIDENT_WAIT"))
         a.wait = std::atoll(e);
     DevState s;
-    do {
-        launch_resident(m, a, h->stream);
+    for (bool first = true;; first = false) {
+        launch_resident(m, a, first, h->stream);
+        launch_copy_out(m, h->st, h->xw, x, h->stream);
+        launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, h->stream);
+        launch_true_residual(m, b, h->q, h->bb, h->st, h->stream);
         const hipError_t e = hipGetLastError();
-        const int st = read_state(h, h->st, &s); // (waits for the launch in any case)
+        const int st = read_state(h, h->st, &s); // (waits for the launches in any case)
         if (e != hipSuccess)
             return hip_fail(h->err, e, "resident solve");
         if (st != CG_OK)
             return st;
-    } while (s.status == kRun && !s.aborted);
-    *status = s.aborted ? (int32_t)kRun : s.status;
-    return CG_OK;
+        if (s.aborted)
+            h->host_st[0].status = kRun;
+        if (s.aborted || s.status != kRun)
+            return CG_OK;
+    }
 }
 
 // Mixed precision: D^-1/2 and the FP32 copy of D^-1/2 A D^-1/2 from the
@@ -1197,47 +1203,50 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
     hipError_t e;
     // initialisation (b and x0 in the device row order)
     const double *bi = vec_into(h, m, b, h->bp);
-    auto start = [&](bool from_zero) {
+    auto start = [&] {
         const double *x0 = vec_into(h, m, x, h->xw);
         launch_spmv(m, x0, h->q, h->sig_spmv, IterCtx{}, s);
         launch_init_vec(m, bi, x0, h->q, h->r, h->p, h->xw, h->rho, h->bb, s);
         launch_init_state(m, h->st, h->bb, h->rho, tol, maxit, s);
-        if (from_zero) // the first step forms p_0 = r_0 + beta * 0
-            launch_fill(n, h->p, 0.0, s);
         return hipGetLastError();
     };
-    int32_t status = kRun;
+    bool solved = false;
     // the whole iteration in one kernel where it is planned and has a place
     if (const ResidentPlace place{h->device, m.rs_wgs, h->cus}) {
-        if ((e = start(true)) != hipSuccess)
+        if ((e = start()) != hipSuccess)
             return done(hip_fail(h->err, e, "launch"));
-        if ((st = run_resident(h, &status)) != CG_OK)
+        if ((st = run_resident(h, bi, x)) != CG_OK)
             return done(st);
-        if (status == kRun) // a wait ran out: launches from now on
+        solved = h->host_st[0].status != kRun;
+        if (!solved) // a wait ran out: launches from now on
             m.rs_wgs = 0;
     }
-    if (status == kRun) {
+    if (!solved) {
+        int32_t status = kRun;
         if ((st = build_graph(h)) != CG_OK)
             return done(st);
-        if ((e = start(h->fused)) != hipSuccess)
+        e = start();
+        if (h->fused) // the first fused step forms p_0 = r_0 + beta * 0
+            launch_fill(n, h->p, 0.0, s);
+        if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess)
             return done(hip_fail(h->err, e, "launch"));
         // two graph launches in flight, poll the older one's state
         if ((st = run_until_stop(h, h->gexec, h->st, &status)) != CG_OK)
             return done(st);
+        // finish: copy x out, true residual of the returned x
+        if (status == kConverged || status == kMaxit || status == kBreakdown) {
+            e = vec_out_of(h, m, h->xw, x);
+            if (e != hipSuccess)
+                return done(hip_fail(h->err, e, "copy-out"));
+            launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, s);
+            launch_true_residual(m, bi, h->q, h->bb, h->st, s);
+        } else if (status == kZeroRhs) {
+            launch_fill(n, x, 0.0, s);
+        }
+        if ((e = hipMemcpyAsync(&h->host_st[0], h->st, sizeof(DevState), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+            (e = hipStreamSynchronize(s)) != hipSuccess)
+            return done(hip_fail(h->err, e, "final state readback"));
     }
-    // finish: copy x out, true residual of the returned x
-    if (status == kConverged || status == kMaxit || status == kBreakdown) {
-        e = vec_out_of(h, m, h->xw, x);
-        if (e != hipSuccess)
-            return done(hip_fail(h->err, e, "copy-out"));
-        launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, s);
-        launch_true_residual(m, bi, h->q, h->bb, h->st, s);
-    } else if (status == kZeroRhs) {
-        launch_fill(n, x, 0.0, s);
-    }
-    if ((e = hipMemcpyAsync(&h->host_st[0], h->st, sizeof(DevState), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
-        return done(hip_fail(h->err, e, "final state readback"));
     const DevState &d = h->host_st[0];
     info->iters = d.iters;
     info->relres = d.nb > 0.0 ? std::sqrt(d.rho) / d.nb : 0.0;

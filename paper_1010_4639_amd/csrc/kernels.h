@@ -162,9 +162,9 @@ void launch_spmv(const DevMatrix &m, const double *x, double *y, double *sig_par
 // y = A32 x with the FP32 copy of the scaled values (FP64 arithmetic).
 void launch_spmv32(const DevMatrix &m, const float *x, double *y, double *sig_part, const IterCtx &c,
                    hipStream_t s);
-// A resident solve (resident.hip) from the state, r, p and x that the
-// initialisation left (p = 0, rho = rho_next = r'r), at most `iters`
-// iterations: then the state says kRun and the next launch goes on from r, p
+// A resident solve (resident.hip) from the state, r and x that the
+// initialisation left (rho = rho_next = r'r; `first` sets p = 0), at most
+// `iters` iterations: then the state says kRun and the next launch goes on from r, p
 // (the last direction), x, rho (the last but one r'r) and rho_next.
 // state->aborted: a wait ran out, r, p and x are lost.
 struct ResidentArgs {
@@ -174,7 +174,7 @@ struct ResidentArgs {
     const double *val;
     const int32_t *gptr, *gcol;
     const uint16_t *lcol, *lown;
-    double *r, *p, *x, *q;
+    double *r, *p, *x;
     DevState *st;
     unsigned long long *words; // resident_words
     int64_t wait;              // ticks of the 100 MHz clock a wait may take; < 0: none (tests)
@@ -184,7 +184,10 @@ constexpr int64_t resident_words(int64_t nsig, int64_t nvec, int64_t n) // two s
 {
     return kResidentRing * (nsig + nvec + 2 * n);
 }
-void launch_resident(const DevMatrix &m, const ResidentArgs &a, hipStream_t s);
+void launch_resident(const DevMatrix &m, const ResidentArgs &a, bool first, hipStream_t s);
+// x = xw where the solve of `st` stopped with an iterate, 0 where b was 0; else
+// (still running, given up, non-finite b) untouched
+void launch_copy_out(const DevMatrix &m, const DevState *st, const double *xw, double *x, hipStream_t s);
 // r -= alpha q with alpha = rho / sum(sig_part); rho_part <- partials of r'r.
 // rows_deferred: q came from a product launched with defer_rows, so each
 // q_i is finished here from the parked slot sums first.

@@ -419,11 +419,27 @@ __global__ __launch_bounds__(T) void k_resident_cg(ResidentArgs A)
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_empty_words(u64 *w, int64_t n)
+// Before a launch: all words empty; before the first one of a solve also p = 0
+// (the first step forms p_0 = r_0 + beta 0).
+__global__ __launch_bounds__(kBlock) void k_resident_begin(u64 *w, int64_t nw, double *p, int n)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n)
+    if (i < nw)
         w[i] = kEmpty;
+    if (i < n)
+        p[i] = 0.0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_copy_out(int n, const DevState *st, const double *__restrict__ xw,
+                                                     double *__restrict__ x)
+{
+    const int status = st->status;
+    const bool iterate = (status == kConverged || status == kMaxit || status == kBreakdown) && st->aborted == 0;
+    if (!iterate && status != kZeroRhs)
+        return;
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n)
+        x[i] = iterate ? xw[i] : 0.0;
 }
 
 template <int T, int S, int E, int C>
@@ -436,10 +452,11 @@ void resident_launch(const DevMatrix &m, const ResidentArgs &a, hipStream_t s)
 
 // The kernel of a planned resident solve: the smallest registers that hold its
 // lines and column lists (plan_resident keeps to the largest).
-void launch_resident(const DevMatrix &m, const ResidentArgs &a, hipStream_t s)
+void launch_resident(const DevMatrix &m, const ResidentArgs &a, bool first, hipStream_t s)
 {
     const int64_t nw = resident_words(a.nsig, a.nvec, m.n);
-    hipLaunchKernelGGL(k_empty_words, dim3((unsigned)((nw + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a.words, nw);
+    hipLaunchKernelGGL(k_resident_begin, dim3((unsigned)((nw + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a.words, nw,
+                       a.p, first ? m.n : 0); // (nw > n)
     const int cols = m.rs_cols, w = m.rs_width;
     if (m.rs_threads == kBlock) {
         if (cols <= 6 * 192 && w <= 8)
@@ -453,6 +470,12 @@ void launch_resident(const DevMatrix &m, const ResidentArgs &a, hipStream_t s)
     } else {
         resident_launch<512, 2, 16, 10>(m, a, s);
     }
+}
+
+void launch_copy_out(const DevMatrix &m, const DevState *st, const double *xw, double *x, hipStream_t s)
+{
+    if (m.n > 0)
+        hipLaunchKernelGGL(k_copy_out, dim3((m.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m.n, st, xw, x);
 }
 
 } // namespace cgmi
