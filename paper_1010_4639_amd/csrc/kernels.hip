@@ -562,15 +562,21 @@ __global__ __launch_bounds__(kBlock) void k_panel_rows(int nch, const int32_t *_
 // dst[k] = src[perm[k]] (0 where perm[k] < 0): values into the panel order
 // or the slice positions; with `order`, src holds the entries in the caller's
 // order (entry j of the normalised matrix is the caller's order[j]).
+// Neighbouring positions read the same cache lines of src again and again (a
+// transposed matrix uses one or two of a line's 16 values at a time), so each
+// XCD takes one contiguous range and finds them in its own L2, and the stores
+// pass it by: 14.8 M entries 85 -> 54 us, 295 MB at 5.4 TB/s.  (Dealt
+// round-robin, all eight L2s fetch every line; ordinary stores 85 as well; two
+// positions a thread 59, four 68.)
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_permute(int64_t nnz, const T *__restrict__ src,
                                                     const int32_t *__restrict__ perm,
                                                     const int32_t *__restrict__ order, T *__restrict__ dst)
 {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t k = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (k < nnz) {
         const int32_t j = perm[k];
-        dst[k] = j >= 0 ? src[order ? order[j] : j] : T(0);
+        __builtin_nontemporal_store(j >= 0 ? src[order ? order[j] : j] : T(0), dst + k);
     }
 }
 
@@ -579,9 +585,9 @@ __global__ __launch_bounds__(kBlock) void k_permute(int64_t nnz, const T *__rest
 // the run in LDS with coalesced loads and writes the positions from there,
 // two values per store, padding 0.  Bytes bound it: 8 read and 8 written per
 // entry, at the device-copy rate (14.8 M entries: 46 us, 5.2 TB/s).  The
-// permutation list of k_permute adds 4 and its gather touches a cache line
-// per lane, and the values were first copied into the handle: 41 + 85 us.  A slice of more than kFillEntries
-// entries reads them from memory instead (one line per lane).
+// permutation list of k_permute adds 4 (54 us), and the values were first
+// copied into the handle (41 us).  A slice of more than kFillEntries entries
+// reads them from memory instead (one line per lane).
 constexpr int kFillEntries = 1024; // 8 KB of LDS per wavefront: 16 a row, 20 waves per CU
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_fill_slices(int nl, int ns, const int32_t *__restrict__ ptr,
@@ -1590,10 +1596,13 @@ __global__ __launch_bounds__(kBlock) void k_mx_scale(int n, const int32_t *__res
 // whole cache lines, and learn each entry's line from a byte map in LDS (each
 // lane marks its own line's entries, a window of the run at a time); the
 // line's own lam / x come from that lane's register.  Bytes bound it: 12 per
-// entry (14.8 M entries: 54 us, 3.3 TB/s; one thread per line, writing 8 and
-// reading 4 bytes a cache line apart, took 280 us).
-constexpr int kGradWindow = 2048; // entries mapped at a time
-constexpr int kGradUnroll = 4;
+// entry (14.8 M entries: 45 us, 4.0 TB/s; one thread per line, writing 8 and
+// reading 4 bytes a cache line apart, took 280 us).  The loads of one pass are
+// in flight together, and a pass takes what 64 lines of a tetrahedral mesh
+// hold (15 entries a full line, 8 a triangle's): 45 us, where 4 a lane needed
+// four dependent passes and 54 us, 8 two and 48.5; a triangle, which gathers
+// twice, 33 us with 8 (35 with 4, 50 with 16: registers).
+constexpr int kGradWindow = 1024; // entries mapped at a time
 template <int FMT>
 __global__ __launch_bounds__(kBlock) void k_pattern_grad(int n, const int32_t *__restrict__ ptr,
                                                          const int32_t *__restrict__ idx,
@@ -1604,6 +1613,7 @@ __global__ __launch_bounds__(kBlock) void k_pattern_grad(int n, const int32_t *_
 #pragma clang fp contract(off)
     __shared__ uint8_t map[kWaves][kGradWindow];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int kGradUnroll = FMT == kSymCsr ? 8 : 16;
     const int l0 = (blockIdx.x * kWaves + wv) * 64;
     const int l = min(l0 + lane, n - 1);
     const bool has = l0 + lane < n;

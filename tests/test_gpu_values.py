@@ -1,6 +1,6 @@
 """New values and value gradients of a planned matrix, at the edges of the
 kernels that move them: 64-line groups (1, 63, 64, 65, 130 lines), runs longer
-than the staged 1024 entries of a slice or the 2048-entry map of a gradient
+than the staged 1024 entries of a slice or the 1024-entry map of a gradient
 window, empty lines, odd and even widths, every format and layout.  Both are
 exact: the product after cg_set_values has the bits of a handle made with those
 values, a gradient the bits of its rounded products.
