@@ -17,10 +17,12 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <future>
 #include <memory>
 #include <mutex>
 #include <new>
 #include <string>
+#include <system_error>
 #include <vector>
 
 #include "../../include/cgmi.h"
@@ -1064,10 +1066,23 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
                 pvals[k] = vals[perm[k]];
             vals = pvals.data();
         }
+        std::future<bool> ahead; // (joined by its destructor where a step below throws)
+        const auto by_rows = [&] { return build_row_plan(format, n, p0.data(), i0.data(), h->row_plan); };
+        if (st == CG_OK && n > 0 && row_plan_ahead(format, n, p0[n])) {
+            try {
+                ahead = std::async(std::launch::async, by_rows);
+            } catch (const std::system_error &) { // no thread: planned below
+            }
+        }
         if (st == CG_OK)
             st = build_plan(format, n, p0.data(), i0.data(), scatter_entries_override(), h->plan, h->err);
-        if (st == CG_OK)
-            build_row_plan(h->plan, p0.data(), i0.data(), h->row_plan);
+        const bool planned = ahead.valid();
+        if (planned)
+            ahead.get();
+        if (st == CG_OK && !takes_row_plan(h->plan))
+            h->row_plan = Plan{};
+        else if (st == CG_OK && !planned)
+            by_rows();
         h->mixed = (flags & CG_MIXED) != 0;
         if (st == CG_OK) {
             hipError_t e = hipGetDevice(&h->device);

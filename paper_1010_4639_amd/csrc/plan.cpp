@@ -1138,24 +1138,33 @@ static bool plan_sym_expanded(Plan &p, const int32_t *ptr, const int32_t *idx)
     return true;
 }
 
-bool build_row_plan(const Plan &p, const int32_t *ptr, const int32_t *idx, Plan &rows)
+bool takes_row_plan(const Plan &p)
+{
+    return p.panel || (p.sym_compact && p.n <= kRowsSolveMax);
+}
+
+bool row_plan_ahead(int fmt, int64_t n, int64_t nnz)
+{
+    return nnz > 65536 && (fmt == kCsc || (fmt == kSymCsr && n > 65536 && n <= kRowsSolveMax));
+}
+
+bool build_row_plan(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx, Plan &rows)
 {
     rows = Plan{};
-    const int64_t n = p.n;
-    if (n == 0 || slice_mode() < 0 || !(p.panel || (p.sym_compact && n <= kRowsSolveMax)))
+    if (n == 0 || slice_mode() < 0)
         return false;
     if (const char *e = std::getenv("CGMI_SYM_EXPAND"))
         if (std::strcmp(e, "0") == 0)
             return false;
     Rows f;
-    if (p.panel)
+    if (fmt == kCsc)
         transpose(n, ptr, idx, f);
     else if (!expand_triangle(n, ptr, idx, f))
         return false;
     rows.format = kCsr;
     rows.n = n;
     rows.nnz = f.ptr[n];
-    rows.lanes = p.lanes;
+    rows.lanes = lanes_for_mean_length((double)ptr[n] / (double)n);
     plan_vectors(rows);
     if (!plan_slices(rows, n, f.ptr.data(), f.idx.data(), f.src.data(), nullptr, 0)) {
         rows = Plan{};

@@ -253,10 +253,16 @@ int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int
 // kRowsSolveMax rows, which then can be resident.  Symmetric compact blocks up
 // to that size: both (216 000 rows: product 19.5 -> 7.7 us, solve 4.85 -> 2.38
 // ms; the bytes that the triangle saves do not matter in the caches).  Larger
-// solves keep the panels and the compact blocks.  false: no such layout (another plan, rows too ragged for
-// slices; experiments: CGMI_SYM_EXPAND=0, CGMI_ROW_LAYOUT=rows).
+// solves keep the panels and the compact blocks.  build_row_plan's false: no
+// such layout (rows too ragged for slices; experiments: CGMI_SYM_EXPAND=0,
+// CGMI_ROW_LAYOUT=rows).  It needs the matrix only, so where the main plan is
+// likely to take it (row_plan_ahead) and holds enough entries to pay for a
+// thread, the two are planned side by side: create of a 100^3 CSC system
+// 197 -> 115 ms, of a 60^3 symmetric one 132 -> 118.
 constexpr int64_t kRowsSolveMax = 262144;
-bool build_row_plan(const Plan &plan, const int32_t *ptr0, const int32_t *idx0, Plan &rows);
+bool takes_row_plan(const Plan &plan);
+bool row_plan_ahead(int fmt, int64_t n, int64_t nnz);
+bool build_row_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, Plan &rows);
 
 int lanes_for_mean_length(double mean_len);
 
