@@ -28,6 +28,7 @@
 #include "../../include/cgmi.h"
 #include "kernels.h"
 #include "plan.h"
+#include "poll.h"
 
 using namespace cgmi;
 
@@ -62,12 +63,13 @@ struct cg_handle {
     unsigned long long *words = nullptr; // resident solve (one kernel): the exchanged words
     double *sig = nullptr, *sig_spmv = nullptr, *rho = nullptr, *bb = nullptr;
     DevState *st = nullptr;
-    DevState *host_st = nullptr; // pinned, 2 entries
-    hipEvent_t ev[2] = {nullptr, nullptr};
+    DevState *host_st = nullptr; // pinned, 2 entries; behind them the report word
+    unsigned long long *word = nullptr;
+    uint32_t tick = 0;           // latest tick that a launched kernel may report
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     int batch = 32;
-    int graph_batch = 0;
+    int graph_batch = 0, graph_iters = 0;
     // mixed precision (CG_MIXED)
     bool mixed = false;
     DevState *st_in = nullptr; // state of the inner FP32 solves
@@ -75,7 +77,7 @@ struct cg_handle {
     double *rout = nullptr;    // outer residual b - A x, FP64
     hipGraph_t graph32 = nullptr;
     hipGraphExec_t gexec32 = nullptr;
-    int graph32_batch = 0;
+    int graph32_batch = 0, graph32_iters = 0;
     // caller entry order -> normalised order (lower-triangle input), device copy
     int32_t *perm = nullptr;
     int32_t *flag = nullptr; // device word for checks made by kernels
@@ -137,9 +139,6 @@ void release(cg_handle *h)
         (void)hipGraphExecDestroy(h->gexec32);
     if (h->graph32)
         (void)hipGraphDestroy(h->graph32);
-    for (auto &e : h->ev)
-        if (e)
-            (void)hipEventDestroy(e);
     if (h->host_st)
         (void)hipHostFree(h->host_st);
     for (void *p : h->allocs)
@@ -514,12 +513,12 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
         m.val32 = dv32;
         m.dscale = dsc;
     }
-    hipError_t e = hipHostMalloc((void **)&h->host_st, 2 * sizeof(DevState), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void **)&h->host_st, 2 * sizeof(DevState) + sizeof(*h->word),
+                                 hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess)
         return hip_fail(h->err, e, "hipHostMalloc");
-    std::memset(h->host_st, 0, 2 * sizeof(DevState));
-    for (auto &ev : h->ev)
-        HIP_TRY(h, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    std::memset(h->host_st, 0, 2 * sizeof(DevState) + sizeof(*h->word));
+    h->word = reinterpret_cast<unsigned long long *>(h->host_st + 2);
     HIP_TRY(h, hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking));
     return CG_OK;
 }
@@ -581,7 +580,7 @@ void enqueue_iteration(cg_handle *h, hipStream_t s, int parity)
     }
     launch_spmv(m, h->p, h->q, h->sig, c, s);
     launch_update_r(m, h->r, h->q, h->st, h->sig, h->rho, s, true);
-    launch_update_xp(m, h->xw, h->p, h->r, h->st, h->rho, s);
+    launch_update_xp(m, h->xw, h->p, h->r, h->st, h->rho, h->word, s);
 }
 
 // One inner (mixed-precision) iteration: FP32 product, FP64 r update, FP64 c
@@ -593,7 +592,16 @@ void enqueue_iteration32(cg_handle *h, hipStream_t s)
     c.defer_rows = true;
     launch_spmv32(h->dm, h->p32, h->q, h->sig, c, s);
     launch_update_r(h->dm, h->r, h->q, h->st_in, h->sig, h->rho, s, true);
-    launch_update_xp32(h->dm, h->p, h->p32, h->r, h->st_in, h->rho, s);
+    launch_update_xp32(h->dm, h->p, h->p32, h->r, h->st_in, h->rho, h->word, s);
+}
+
+// Reports of the handle's kernels; the state goes into entry `slot` of host_st.
+Report report_to(cg_handle *h, int slot)
+{
+    Report r;
+    r.word = h->word;
+    r.state = h->host_st + slot;
+    return r;
 }
 
 int build_graph_generic(cg_handle *h, bool mixed)
@@ -630,14 +638,14 @@ int build_graph_generic(cg_handle *h, bool mixed)
         else
             enqueue_iteration(h, h->capture, i & 1);
     }
-    // (the fused iteration records its stops in its own r update)
-    if (!fused)
-        launch_check(h->dm, mixed ? h->st_in : h->st, h->rho, h->capture);
+    if (fused)
+        launch_progress(h->st, h->word, h->capture);
     hipError_t e = hipStreamEndCapture(h->capture, &g);
     if (e != hipSuccess)
         return hip_fail(h->err, e, "hipStreamEndCapture");
     HIP_TRY(h, hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
     gb = h->batch;
+    (mixed ? h->graph32_iters : h->graph_iters) = nb;
     return CG_OK;
 }
 
@@ -646,31 +654,29 @@ int build_graph(cg_handle *h)
     return build_graph_generic(h, false);
 }
 
-// Replays `ge` (two launches in flight) until the device status of `st`
-// leaves kRun; returns the final status through *status.
-int run_until_stop(cg_handle *h, hipGraphExec_t ge, DevState *st, int32_t *status)
+// Replays `ge` (nb iterations) until the solve of `st`, initialised with
+// h->tick, stops; its status is then final on the stream, and the state on its
+// way to host_st[1].
+// The host follows the iterations themselves and launches the next graph when
+// kAhead are left of those launched: longer than a launch takes to arrive, and
+// all that runs past the stop besides the rest of the last graph.
+constexpr int kAhead = 6;
+int run_until_stop(cg_handle *h, hipGraphExec_t ge, int nb, DevState *st)
 {
     hipStream_t s = h->stream;
     hipError_t e;
-    auto launch = [&](int slot) -> hipError_t {
-        hipError_t r = hipGraphLaunch(ge, s);
-        if (r == hipSuccess)
-            r = hipMemcpyAsync(&h->host_st[slot], st, sizeof(DevState), hipMemcpyDeviceToHost, s);
-        if (r == hipSuccess)
-            r = hipEventRecord(h->ev[slot], s);
-        return r;
-    };
-    if ((e = launch(0)) != hipSuccess)
-        return hip_fail(h->err, e, "hipGraphLaunch");
-    for (int i = 0;; ++i) {
-        if ((e = launch((i + 1) & 1)) != hipSuccess)
+    const uint32_t first = h->tick;
+    uint32_t stop = 0;
+    while (stop == 0) {
+        if ((e = hipGraphLaunch(ge, s)) != hipSuccess)
             return hip_fail(h->err, e, "hipGraphLaunch");
-        if ((e = hipEventSynchronize(h->ev[i & 1])) != hipSuccess)
-            return hip_fail(h->err, e, "hipEventSynchronize");
-        *status = h->host_st[i & 1].status;
-        if (*status != kRun)
-            return CG_OK;
+        h->tick += (uint32_t)nb;
+        if ((e = wait_report(h->word, first, h->tick - kAhead, s, &stop)) != hipSuccess)
+            return hip_fail(h->err, e, "iteration");
     }
+    ++h->tick;
+    launch_check(st, report_to(h, 1), h->tick, s);
+    return CG_OK;
 }
 
 // Resident solves in flight on each device, in workgroups.  A solve is
@@ -724,6 +730,24 @@ int read_state(cg_handle *h, DevState *st, DevState *out)
     return CG_OK;
 }
 
+// The end of a solve whose status is final on the stream: x out as the state
+// says, the true residual, the state to host_st[0]; the host's one wait.
+int finish_solve(cg_handle *h, const double *b, double *x)
+{
+    const DevMatrix &m = h->solver();
+    ++h->tick;
+    launch_copy_out(m, h->st, h->xw, x, h->stream);
+    launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, h->stream);
+    launch_true_residual(m, b, h->q, h->bb, h->st, report_to(h, 0), h->tick, h->stream);
+    hipError_t e = hipGetLastError();
+    uint32_t now = 0;
+    if (e != hipSuccess) // (after the launches that were made)
+        (void)hipStreamSynchronize(h->stream);
+    else
+        e = wait_report(h->word, h->tick, h->tick, h->stream, &now);
+    return e == hipSuccess ? CG_OK : hip_fail(h->err, e, "solve");
+}
+
 // The iteration of an initialised solve as resident launches, each followed by
 // the end of the solve (x out unless the state says otherwise, the true
 // residual), so that the host waits once.  The state is in host_st[0]; kRun: a
@@ -752,20 +776,14 @@ int run_resident(cg_handle *h, const double *b, double *x)
     a.wait = 25000000; // 0.25 s; tests: CGMI_RESIDENT_WAIT
     if (const char *e = std::getenv("CGMI_RESIDENT_WAIT"))
         a.wait = std::atoll(e);
-    DevState s;
     for (bool first = true;; first = false) {
         launch_resident(m, a, first, h->stream);
-        launch_copy_out(m, h->st, h->xw, x, h->stream);
-        launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, h->stream);
-        launch_true_residual(m, b, h->q, h->bb, h->st, h->stream);
-        const hipError_t e = hipGetLastError();
-        const int st = read_state(h, h->st, &s); // (waits for the launches in any case)
-        if (e != hipSuccess)
-            return hip_fail(h->err, e, "resident solve");
+        const int st = finish_solve(h, b, x);
         if (st != CG_OK)
             return st;
+        DevState &s = h->host_st[0];
         if (s.aborted)
-            h->host_st[0].status = kRun;
+            s.status = kRun;
         if (s.aborted || s.status != kRun)
             return CG_OK;
     }
@@ -1222,7 +1240,7 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
         const double *x0 = vec_into(h, m, x, h->xw);
         launch_spmv(m, x0, h->q, h->sig_spmv, IterCtx{}, s);
         launch_init_vec(m, bi, x0, h->q, h->r, h->p, h->xw, h->rho, h->bb, s);
-        launch_init_state(m, h->st, h->bb, h->rho, tol, maxit, s);
+        launch_init_state(m, h->st, h->bb, h->rho, tol, maxit, ++h->tick, s);
         return hipGetLastError();
     };
     bool solved = false;
@@ -1237,7 +1255,6 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
             m.rs_wgs = 0;
     }
     if (!solved) {
-        int32_t status = kRun;
         if ((st = build_graph(h)) != CG_OK)
             return done(st);
         e = start();
@@ -1245,22 +1262,9 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
             launch_fill(n, h->p, 0.0, s);
         if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess)
             return done(hip_fail(h->err, e, "launch"));
-        // two graph launches in flight, poll the older one's state
-        if ((st = run_until_stop(h, h->gexec, h->st, &status)) != CG_OK)
+        if ((st = run_until_stop(h, h->gexec, h->graph_iters, h->st)) != CG_OK ||
+            (st = finish_solve(h, bi, x)) != CG_OK)
             return done(st);
-        // finish: copy x out, true residual of the returned x
-        if (status == kConverged || status == kMaxit || status == kBreakdown) {
-            e = vec_out_of(h, m, h->xw, x);
-            if (e != hipSuccess)
-                return done(hip_fail(h->err, e, "copy-out"));
-            launch_spmv(m, h->xw, h->q, h->sig_spmv, IterCtx{}, s);
-            launch_true_residual(m, bi, h->q, h->bb, h->st, s);
-        } else if (status == kZeroRhs) {
-            launch_fill(n, x, 0.0, s);
-        }
-        if ((e = hipMemcpyAsync(&h->host_st[0], h->st, sizeof(DevState), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-            (e = hipStreamSynchronize(s)) != hipSuccess)
-            return done(hip_fail(h->err, e, "final state readback"));
     }
     const DevState &d = h->host_st[0];
     info->iters = d.iters;
@@ -1314,7 +1318,7 @@ int cg_solve_mixed(cg_handle *h, const double *b, double *x, double tol, int32_t
     const double *x0 = vec_into(h, h->dm, x, h->xw);
     launch_spmv(h->dm, x0, h->q, h->sig_spmv, IterCtx{}, s);
     launch_init_vec(h->dm, bi, x0, h->q, h->rout, h->p, h->xw, h->rho, h->bb, s);
-    launch_init_state(h->dm, h->st, h->bb, h->rho, tol, maxit, s);
+    launch_init_state(h->dm, h->st, h->bb, h->rho, tol, maxit, ++h->tick, s);
     DevState out;
     if ((st = read_state(h, h->st, &out)) != CG_OK)
         return done(st);
@@ -1340,28 +1344,31 @@ int cg_solve_mixed(cg_handle *h, const double *b, double *x, double tol, int32_t
             break;
         // inner solve of (D^-1/2 A D^-1/2) c = D^-1/2 r in FP32 storage
         launch_mx_init(h->dm, h->rout, h->r, h->p32, h->p, h->rho, h->bb, s, keep_p && !restart_inner());
-        launch_init_state(h->dm, h->st_in, h->bb, h->rho, inner_tol, maxit - total, s);
-        int32_t status = kRun;
-        if ((st = run_until_stop(h, h->gexec32, h->st_in, &status)) != CG_OK)
+        launch_init_state(h->dm, h->st_in, h->bb, h->rho, inner_tol, maxit - total, ++h->tick, s);
+        if ((st = run_until_stop(h, h->gexec32, h->graph32_iters, h->st_in)) != CG_OK)
             return done(st);
-        DevState in;
-        if ((st = read_state(h, h->st_in, &in)) != CG_OK)
-            return done(st);
-        total += in.iters;
-        ++outer;
-        keep_p = in.status == kConverged && in.iters > 0;
-        if (in.status == kBreakdown && in.iters == 0) {
-            h->err = "inner FP32 solve broke down before any step";
-            code = CG_ERR_BREAKDOWN;
-            break;
-        }
         // x += D^-1/2 c; r = b - A x (FP64 product), true residual norm
         launch_mx_apply(h->dm, h->xw, h->p, s);
         launch_spmv(h->dm, h->xw, h->q, h->sig_spmv, IterCtx{}, s);
         launch_init_vec(h->dm, bi, h->xw, h->q, h->rout, h->p, h->xw, h->rho, h->bb, s);
-        launch_outer_norm(h->dm, h->st, h->rho, s);
-        if ((st = read_state(h, h->st, &out)) != CG_OK)
-            return done(st);
+        ++h->tick;
+        launch_outer_norm(h->dm, h->st, h->rho, report_to(h, 0), h->tick, s);
+        uint32_t now = 0;
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = wait_report(h->word, h->tick, h->tick, s, &now);
+        if (e != hipSuccess)
+            return done(hip_fail(h->err, e, "refinement"));
+        const DevState &in = h->host_st[1];
+        total += in.iters;
+        ++outer;
+        keep_p = in.status == kConverged && in.iters > 0;
+        if (in.status == kBreakdown && in.iters == 0) { // (c = 0: x and r as they were)
+            h->err = "inner FP32 solve broke down before any step";
+            code = CG_ERR_BREAKDOWN;
+            break;
+        }
+        out = h->host_st[0];
         relres = std::sqrt(out.rho) / nb;
         if (!std::isfinite(relres)) {
             h->err = "refinement produced a non-finite residual";

@@ -44,6 +44,17 @@ struct DevState {
     double rho_next; // r'r after the latest r update (published for the next iteration's gate)
     int32_t conv_next; // sqrt(rho_next) <= tol_nb
     int32_t aborted;   // a resident solve gave up waiting (resident.hip)
+    uint32_t tick;     // progress reports: tick + k (Report)
+    uint32_t pad;
+};
+
+// Where kernels tell the waiting host how far they are: a word in pinned host
+// memory, (tick << 32) | payload.  Ticks count up along the stream, whatever
+// is reported: every iteration its number (payload 1: the solve stops here),
+// single kernels theirs, after they copied the state (poll.h).
+struct Report {
+    unsigned long long *word = nullptr;
+    DevState *state = nullptr;
 };
 
 // Device image of a planned matrix.
@@ -195,10 +206,10 @@ void launch_update_r(const DevMatrix &m, double *r, const double *q, DevState *s
                      double *rho_part, hipStream_t s, bool rows_deferred = false, bool fused = false);
 // x += alpha p; p = r + beta p (unless converged) with beta = sum(rho_part) / rho.
 void launch_update_xp(const DevMatrix &m, double *x, double *p, const double *r, DevState *st,
-                      const double *rho_part, hipStream_t s);
+                      const double *rho_part, unsigned long long *word, hipStream_t s);
 // mixed precision: the same update with p stored in FP32
 void launch_update_xp32(const DevMatrix &m, double *x, float *p, const double *r, DevState *st,
-                        const double *rho_part, hipStream_t s);
+                      const double *rho_part, unsigned long long *word, hipStream_t s);
 // mixed precision: rh = D^-1/2 r_out, p = fl32(rh) (unless keep_p: the
 // direction of the previous inner solve carries over), c = 0, partials of rh'rh
 void launch_mx_init(const DevMatrix &m, const double *r_out, double *rh, float *p, double *c, double *rho_part,
@@ -206,17 +217,20 @@ void launch_mx_init(const DevMatrix &m, const double *r_out, double *rh, float *
 // mixed precision: x += D^-1/2 c
 void launch_mx_apply(const DevMatrix &m, double *x, const double *c, hipStream_t s);
 // st->rho = sum(rho_part), st->res_true = sqrt(st->rho) / st->nb (one workgroup)
-void launch_outer_norm(const DevMatrix &m, DevState *st, const double *rho_part, hipStream_t s);
+// These report the state with the given tick (rep.word null: no report).
+void launch_outer_norm(const DevMatrix &m, DevState *st, const double *rho_part, const Report &rep, uint32_t tick,
+                       hipStream_t s);
 // convergence / maxit test of the current residual (one workgroup).
-void launch_check(const DevMatrix &m, DevState *st, const double *rho_part, hipStream_t s);
+void launch_check(DevState *st, const Report &rep, uint32_t tick, hipStream_t s);
+void launch_progress(const DevState *st, unsigned long long *word, hipStream_t s);
 // r = b - q, p = r, xw = x0; partials of r'r and b'b.
 void launch_init_vec(const DevMatrix &m, const double *b, const double *x0, const double *q, double *r, double *p,
                      double *xw, double *rho_part, double *bb_part, hipStream_t s);
 void launch_init_state(const DevMatrix &m, DevState *st, const double *bb_part, const double *rho_part, double tol,
-                       int32_t maxit, hipStream_t s);
+                       int32_t maxit, uint32_t tick, hipStream_t s);
 // res_true = ||b - q|| / ||b|| into st (two launches)
 void launch_true_residual(const DevMatrix &m, const double *b, const double *q, double *part, DevState *st,
-                          hipStream_t s);
+                          const Report &rep, uint32_t tick, hipStream_t s);
 void launch_fill(int n, double *x, double v, hipStream_t s);
 // dst[k] = src[perm[k]] for k < nnz, 0 where perm[k] < 0; with `order`,
 // src[order[perm[k]]]

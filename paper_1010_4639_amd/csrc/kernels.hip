@@ -1348,21 +1348,43 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *_
         rho_part[blk] = acc;
 }
 
+// One thread's reports to the host (Report): progress alone, in one store that
+// nothing waits for; or the state and then the word.
+__device__ __forceinline__ void report_word(unsigned long long *word, uint32_t tick, uint32_t payload)
+{
+    __hip_atomic_store(word, ((unsigned long long)tick << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ void report_state(const DevState *st, const Report &rep, uint32_t tick)
+{
+    if (rep.word == nullptr)
+        return;
+    static_assert(sizeof(DevState) % 8 == 0, "copied in words");
+    const unsigned long long *src = reinterpret_cast<const unsigned long long *>(st);
+    unsigned long long *dst = reinterpret_cast<unsigned long long *>(rep.state);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(DevState) / 8); ++i)
+        __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(rep.word, ((unsigned long long)tick << 32) | 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // x += alpha p and p = r + beta p; workgroup 0 publishes r'r and the
 // convergence decision for the next iteration's gate (no workgroup of this
-// kernel reads those two fields).
+// kernel reads those two fields) and tells the host how far the solve is.
 // PT: storage type of p (double; float for the inner solves of mixed
 // precision, where p is rounded to FP32 after the FP64 update).
 template <class PT, int PPT, int KP>
 __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, double *__restrict__ x,
                                                       PT *__restrict__ p, const double *__restrict__ r,
                                                       DevState *st, const double *__restrict__ rho_part,
-                                                      int n_rho)
+                                                      int n_rho, unsigned long long *word)
 {
     __shared__ double red[kWaves];
     // the gate, the partials and the first vector elements are loaded
     // together (one memory round trip); nothing is stored before the gate
-    const int status = st->status;
+    const int status = st->status, done = st->k;
+    const uint32_t tick = st->tick + (uint32_t)done;
+    const bool last = done >= st->maxit;
     const double alpha = st->alpha, rho = st->rho;
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int i0 = blk * chunk, i1 = min(n, i0 + chunk);
@@ -1378,8 +1400,11 @@ __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, double *
         xv[u] = ok ? x[i] : 0.0;
         rv[u] = ok ? r[i] : 0.0;
     }
-    if (status != kRun)
+    if (status != kRun) {
+        if (blockIdx.x == 0 && t == 0)
+            report_word(word, tick, 1);
         return;
+    }
     const double rho_new = partials_sum(part, n_rho, red);
     const double beta = rho_new / rho;
     // last step: x only -- except for the FP32 directions of the mixed inner
@@ -1387,7 +1412,9 @@ __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, double *
     const bool conv = sqrt(rho_new) <= st->tol_nb && sizeof(PT) == 8;
     if (blockIdx.x == 0 && t == 0) {
         st->rho_next = rho_new;
-        st->conv_next = sqrt(rho_new) <= st->tol_nb ? 1 : 0;
+        const int stop = sqrt(rho_new) <= st->tol_nb ? 1 : 0;
+        st->conv_next = stop;
+        report_word(word, tick, stop | (last ? 1 : 0));
     }
 #pragma unroll
     for (int u = 0; u < KP; ++u) {
@@ -1444,19 +1471,30 @@ __global__ __launch_bounds__(kBlock) void k_mx_apply(int n, double *__restrict__
 }
 
 // Outer residual norm: st->rho = sum of partials, st->res_true = sqrt / nb.
-__global__ __launch_bounds__(kBlock) void k_outer_norm(DevState *st, const double *__restrict__ part, int m)
+__global__ __launch_bounds__(kBlock) void k_outer_norm(DevState *st, const double *__restrict__ part, int m,
+                                                       Report rep, uint32_t tick)
 {
     __shared__ double red[kWaves];
     const double rho = reduce_partials(part, m, red);
     if (threadIdx.x == 0) {
         st->rho = rho;
         st->res_true = st->nb > 0.0 ? sqrt(rho) / st->nb : 0.0;
+        report_state(st, rep, tick);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_check(DevState *st)
+// After the last iteration of a solve: the pending stop decision, the state to
+// the host where it is asked for.
+__global__ void k_check(DevState *st, Report rep, uint32_t tick)
 {
     iter_gate(st);
+    report_state(st, rep, tick);
+}
+
+// Progress of the fused iteration, whose r update records its stops itself.
+__global__ void k_progress(const DevState *st, unsigned long long *word)
+{
+    report_word(word, st->tick + (uint32_t)st->k, st->status != kRun ? 1 : 0);
 }
 
 __global__ __launch_bounds__(kBlock) void k_init_vec(int n, int chunk, const double *__restrict__ b,
@@ -1488,7 +1526,7 @@ __global__ __launch_bounds__(kBlock) void k_init_vec(int n, int chunk, const dou
 
 __global__ __launch_bounds__(kBlock) void k_init_state(DevState *st, const double *__restrict__ bb_part,
                                                        const double *__restrict__ rho_part, int m, double tol,
-                                                       int maxit)
+                                                       int maxit, uint32_t tick)
 {
     __shared__ double red[kWaves];
     const double nb = sqrt(reduce_partials(bb_part, m, red));
@@ -1506,6 +1544,7 @@ __global__ __launch_bounds__(kBlock) void k_init_state(DevState *st, const doubl
         st->rho_next = rho;
         st->conv_next = sqrt(rho) <= tol * nb ? 1 : 0;
         st->aborted = 0;
+        st->tick = tick;
         st->status = !isfinite(nb) ? kNonfinite : (nb == 0.0 ? kZeroRhs : kRun);
     }
 }
@@ -1526,12 +1565,15 @@ __global__ __launch_bounds__(kBlock) void k_resid_part(int n, int chunk, const d
         part[blk] = a;
 }
 
-__global__ __launch_bounds__(kBlock) void k_resid_finish(DevState *st, const double *__restrict__ part, int m)
+__global__ __launch_bounds__(kBlock) void k_resid_finish(DevState *st, const double *__restrict__ part, int m,
+                                                         Report rep, uint32_t tick)
 {
     __shared__ double red[kWaves];
     const double s = reduce_partials(part, m, red);
-    if (threadIdx.x == 0)
-        st->res_true = st->nb > 0.0 ? sqrt(s) / st->nb : 0.0;
+    if (threadIdx.x == 0) {
+        st->res_true = st->nb > 0.0 && st->status != kNonfinite ? sqrt(s) / st->nb : 0.0;
+        report_state(st, rep, tick);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill(int n, double *__restrict__ x, double v)
@@ -2002,13 +2044,14 @@ void launch_update_r(const DevMatrix &m, double *r, const double *q, DevState *s
 // covers the vector kernels' workgroups
 template <class PT>
 void update_xp_launch(const DevMatrix &m, double *x, PT *p, const double *r, DevState *st, const double *rho_part,
-                      hipStream_t s)
+                      unsigned long long *word, hipStream_t s)
 {
     static_assert(kMaxVecBlocks <= 8 * kBlock, "vector partials fit eight per thread");
     const dim3 grid(m.vec_blocks), blk(kBlock);
     const int kp = prefetch_depth(m.vec_chunk);
 #define CGMI_UPDATE_XP_KP(P, K)                                                                              \
-    hipLaunchKernelGGL((k_update_xp<PT, P, K>), grid, blk, 0, s, m.n, m.vec_chunk, x, p, r, st, rho_part, m.vec_blocks)
+    hipLaunchKernelGGL((k_update_xp<PT, P, K>), grid, blk, 0, s, m.n, m.vec_chunk, x, p, r, st, rho_part,       \
+                       m.vec_blocks, word)
 #define CGMI_UPDATE_XP(P)                                                                                    \
     do {                                                                                                     \
         switch (kp) {                                                                                        \
@@ -2031,15 +2074,15 @@ void update_xp_launch(const DevMatrix &m, double *x, PT *p, const double *r, Dev
 }
 
 void launch_update_xp(const DevMatrix &m, double *x, double *p, const double *r, DevState *st,
-                      const double *rho_part, hipStream_t s)
+                      const double *rho_part, unsigned long long *word, hipStream_t s)
 {
-    update_xp_launch(m, x, p, r, st, rho_part, s);
+    update_xp_launch(m, x, p, r, st, rho_part, word, s);
 }
 
 void launch_update_xp32(const DevMatrix &m, double *x, float *p, const double *r, DevState *st,
-                        const double *rho_part, hipStream_t s)
+                        const double *rho_part, unsigned long long *word, hipStream_t s)
 {
-    update_xp_launch(m, x, p, r, st, rho_part, s);
+    update_xp_launch(m, x, p, r, st, rho_part, word, s);
 }
 
 void launch_mx_init(const DevMatrix &m, const double *r_out, double *rh, float *p, double *c, double *rho_part,
@@ -2055,14 +2098,20 @@ void launch_mx_apply(const DevMatrix &m, double *x, const double *c, hipStream_t
         hipLaunchKernelGGL(k_mx_apply, dim3((m.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m.n, x, m.dscale, c);
 }
 
-void launch_outer_norm(const DevMatrix &m, DevState *st, const double *rho_part, hipStream_t s)
+void launch_outer_norm(const DevMatrix &m, DevState *st, const double *rho_part, const Report &rep, uint32_t tick,
+                       hipStream_t s)
 {
-    hipLaunchKernelGGL(k_outer_norm, dim3(1), dim3(kBlock), 0, s, st, rho_part, m.vec_blocks);
+    hipLaunchKernelGGL(k_outer_norm, dim3(1), dim3(kBlock), 0, s, st, rho_part, m.vec_blocks, rep, tick);
 }
 
-void launch_check(const DevMatrix &m, DevState *st, const double *rho_part, hipStream_t s)
+void launch_check(DevState *st, const Report &rep, uint32_t tick, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_check, dim3(1), dim3(kBlock), 0, s, st);
+    hipLaunchKernelGGL(k_check, dim3(1), dim3(1), 0, s, st, rep, tick);
+}
+
+void launch_progress(const DevState *st, unsigned long long *word, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_progress, dim3(1), dim3(1), 0, s, st, word);
 }
 
 void launch_init_vec(const DevMatrix &m, const double *b, const double *x0, const double *q, double *r, double *p,
@@ -2073,16 +2122,17 @@ void launch_init_vec(const DevMatrix &m, const double *b, const double *x0, cons
 }
 
 void launch_init_state(const DevMatrix &m, DevState *st, const double *bb_part, const double *rho_part, double tol,
-                       int32_t maxit, hipStream_t s)
+                       int32_t maxit, uint32_t tick, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(kBlock), 0, s, st, bb_part, rho_part, m.vec_blocks, tol, maxit);
+    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(kBlock), 0, s, st, bb_part, rho_part, m.vec_blocks, tol, maxit,
+                       tick);
 }
 
 void launch_true_residual(const DevMatrix &m, const double *b, const double *q, double *part, DevState *st,
-                          hipStream_t s)
+                          const Report &rep, uint32_t tick, hipStream_t s)
 {
     hipLaunchKernelGGL(k_resid_part, dim3(m.vec_blocks), dim3(kBlock), 0, s, m.n, m.vec_chunk, b, q, part);
-    hipLaunchKernelGGL(k_resid_finish, dim3(1), dim3(kBlock), 0, s, st, part, m.vec_blocks);
+    hipLaunchKernelGGL(k_resid_finish, dim3(1), dim3(kBlock), 0, s, st, part, m.vec_blocks, rep, tick);
 }
 
 void launch_fill(int n, double *x, double v, hipStream_t s)

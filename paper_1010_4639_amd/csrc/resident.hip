@@ -431,7 +431,7 @@ __global__ __launch_bounds__(kBlock) void k_resident_begin(u64 *w, int64_t nw, d
 }
 
 __global__ __launch_bounds__(kBlock) void k_copy_out(int n, const DevState *st, const double *__restrict__ xw,
-                                                     double *__restrict__ x)
+                                                     const int32_t *__restrict__ inv, double *__restrict__ x)
 {
     const int status = st->status;
     const bool iterate = (status == kConverged || status == kMaxit || status == kBreakdown) && st->aborted == 0;
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(kBlock) void k_copy_out(int n, const DevState *st, 
         return;
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n)
-        x[i] = iterate ? xw[i] : 0.0;
+        x[i] = iterate ? xw[inv != nullptr ? inv[i] : i] : 0.0;
 }
 
 template <int T, int S, int E, int C>
@@ -475,7 +475,7 @@ void launch_resident(const DevMatrix &m, const ResidentArgs &a, bool first, hipS
 void launch_copy_out(const DevMatrix &m, const DevState *st, const double *xw, double *x, hipStream_t s)
 {
     if (m.n > 0)
-        hipLaunchKernelGGL(k_copy_out, dim3((m.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m.n, st, xw, x);
+        hipLaunchKernelGGL(k_copy_out, dim3((m.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m.n, st, xw, m.vinv, x);
 }
 
 } // namespace cgmi
