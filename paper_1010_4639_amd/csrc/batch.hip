@@ -17,7 +17,8 @@
 // p = r + beta p; the system's lead workgroup publishes r'r and the stop
 // decision), as in the single-system solver.  Instances that stopped are
 // skipped; a system whose instances have all stopped costs only early
-// returns.  k_bcheck counts the running instances after each graph launch.
+// returns.  Every iteration is reported to the host with the decision
+// whether any instance still runs (kernels.h, Report).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,6 +35,7 @@
 #include "devutil.h"
 #include "kernels.h"
 #include "plan.h"
+#include "poll.h"
 
 using namespace cgmi;
 using namespace cgmi::dev;
@@ -45,6 +47,11 @@ struct Inst {
     int32_t conv_next, pad0, pad1, pad2;
     double tol_nb, nb, rho, alpha, sigma, rho_next, res_true, pad3;
 };
+
+// The entry before the first instance belongs to the batch: `iters` counts the
+// instances still running, `k` the ticks reported.  (Four entries ahead keep
+// the instances of a system on whole cache lines.)
+constexpr int kInstAhead = 4;
 
 // Workgroups (= dot partials) of one system at most.  Every update workgroup
 // reads all partials of its system: 1024 x R doubles stay small beside its
@@ -60,8 +67,9 @@ struct WgDesc {
 };
 
 
-__device__ __forceinline__ bool inst_gate(Inst *I, bool lead)
+__device__ __forceinline__ bool inst_gate(Inst *inst, int i, bool lead)
 {
+    Inst *I = inst + i;
     if (I->status != kRun)
         return false;
     const int k = I->k;
@@ -70,6 +78,7 @@ __device__ __forceinline__ bool inst_gate(Inst *I, bool lead)
             I->rho = I->rho_next;
             I->iters = k;
             I->status = kConverged;
+            atomicAdd(&inst[-1].iters, -1);
         }
         return false;
     }
@@ -78,6 +87,7 @@ __device__ __forceinline__ bool inst_gate(Inst *I, bool lead)
             I->rho = I->rho_next;
             I->iters = k;
             I->status = kMaxit;
+            atomicAdd(&inst[-1].iters, -1);
         }
         return false;
     }
@@ -111,7 +121,7 @@ __global__ __launch_bounds__(kBlock) void k_bspmm_lanes(const WgDesc *__restrict
     bool any = true;
     if (inst != nullptr) {
         if (t < R)
-            act_s[t] = inst_gate(&inst[Wd.sys * R + t], Wd.lead != 0) ? 1 : 0;
+            act_s[t] = inst_gate(inst, Wd.sys * R + t, Wd.lead != 0) ? 1 : 0;
         __syncthreads();
         any = false;
 #pragma unroll
@@ -207,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void k_bspmm(const WgDesc *__restrict__ wgs
     bool any = true;
     if (inst != nullptr) {
         if (t < R)
-            act_s[t] = inst_gate(&inst[W.sys * R + t], W.lead != 0) ? 1 : 0;
+            act_s[t] = inst_gate(inst, W.sys * R + t, W.lead != 0) ? 1 : 0;
         __syncthreads();
         any = false;
 #pragma unroll
@@ -331,7 +341,7 @@ __global__ __launch_bounds__(kBlock) void k_bspmm_slices(const WgDesc *__restric
     bool any = true;
     if (inst != nullptr) {
         if (t < R)
-            act_s[t] = inst_gate(&inst[W.sys * R + t], W.lead != 0) ? 1 : 0;
+            act_s[t] = inst_gate(inst, W.sys * R + t, W.lead != 0) ? 1 : 0;
         __syncthreads();
         any = false;
 #pragma unroll
@@ -535,6 +545,7 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_r(const WgDesc *__restrict__
                 I->iters = I->k;
                 I->sigma = sg[r];
                 I->status = kBreakdown;
+                atomicAdd(&inst[-1].iters, -1);
             }
         } else {
             al[r] = rho[r] / sg[r];
@@ -603,16 +614,34 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_r(const WgDesc *__restrict__
     }
 }
 
+// Reports to the host (kernels.h): every kReportStep iterations, by a workgroup
+// of its own, so that no other one waits for the counts.  (A check kernel, a
+// copy and an event after each graph of 16 instead: 17 systems of 25^3..35^3
+// 5.30 -> 5.07 ms, 24 of 8^3..20^3 with 2 right-hand sides 1.98 -> 1.78.)
+constexpr int kReportStep = 4;
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_bupdate_xp(const WgDesc *__restrict__ wgs, double *__restrict__ X,
                                                        double *__restrict__ P, const double *__restrict__ Rv,
-                                                       Inst *inst, const double *__restrict__ rho_part)
+                                                       Inst *inst, const double *__restrict__ rho_part,
+                                                       Inst *__restrict__ head, unsigned long long *word)
 {
     constexpr int V = BVec<R>::V;
     typedef typename BVec<R>::type vec;
     __shared__ double red[kWaves][R];
-    const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x;
+    if (word != nullptr && blockIdx.x == gridDim.x - 1) { // one more workgroup: the report
+        if (t == 0) {
+            const uint32_t tick = (uint32_t)head->k + kReportStep;
+            head->k = (int32_t)tick;
+            // (volatile: goes to host memory at once.  An atomic store counts as a
+            // change of all memory, and the kernel's scalar loads become vector ones:
+            // 74 -> 88 registers at R = 2, 1 % of a solve)
+            *const_cast<volatile unsigned long long *>(word) =
+                ((unsigned long long)tick << 32) | (head->iters > 0 ? 0 : 1);
+        }
+        return;
+    }
+    const WgDesc W = wgs[blockIdx.x];
     const vec *rv = reinterpret_cast<const vec *>(Rv + (size_t)W.i0 * R);
     vec *x = reinterpret_cast<vec *>(X + (size_t)W.i0 * R), *p = reinterpret_cast<vec *>(P + (size_t)W.i0 * R);
     const int m = (W.i1 - W.i0) * (R / V);
@@ -687,31 +716,18 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_xp(const WgDesc *__restrict_
         step(p[j], x[j], rv[j], j);
 }
 
-// After each graph launch: apply the pending stop decisions and count the
-// instances still running (one workgroup).
-__global__ __launch_bounds__(kBlock) void k_bcheck(Inst *inst, int ninst, double *running)
+// Start of a solve (one workgroup): instances that run, ticks from `tick` on.
+__global__ __launch_bounds__(kBlock) void k_bstart(Inst *inst, int ninst, uint32_t tick)
 {
     __shared__ double red[kWaves];
     double c = 0.0;
-    for (int i = threadIdx.x; i < ninst; i += kBlock) {
-        Inst *I = &inst[i];
-        if (I->status != kRun)
-            continue;
-        if (I->conv_next) {
-            I->rho = I->rho_next;
-            I->iters = I->k;
-            I->status = kConverged;
-        } else if (I->k >= I->maxit) {
-            I->rho = I->rho_next;
-            I->iters = I->k;
-            I->status = kMaxit;
-        } else {
-            c += 1.0;
-        }
-    }
+    for (int i = threadIdx.x; i < ninst; i += kBlock)
+        c += inst[i].status == kRun ? 1.0 : 0.0;
     c = block_sum(c, red);
-    if (threadIdx.x == 0)
-        running[0] = c;
+    if (threadIdx.x == 0) {
+        inst[-1].iters = (int32_t)c;
+        inst[-1].k = (int32_t)tick;
+    }
 }
 
 template <int R>
@@ -855,10 +871,10 @@ struct cg_batch {
     WgDesc *wgs = nullptr;
     Inst *inst = nullptr;
     double *P = nullptr, *Rv = nullptr, *Q = nullptr, *Xw = nullptr;
-    double *sig = nullptr, *rho = nullptr, *bb = nullptr, *running = nullptr;
-    double *host_run = nullptr; // pinned [2]
+    double *sig = nullptr, *rho = nullptr, *bb = nullptr;
+    unsigned long long *word = nullptr; // pinned: reports (kernels.h)
+    uint32_t tick = 0;          // latest tick that a launched kernel may report
     Inst *host_inst = nullptr;  // pinned [ninst]
-    hipEvent_t ev[2] = {nullptr, nullptr};
     hipStream_t stream = nullptr, capture = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
@@ -1193,21 +1209,22 @@ void spmm(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
 }
 
 template <int R>
-void iteration_r(cg_batch *h, hipStream_t s)
+void iteration_r(cg_batch *h, bool report, hipStream_t s)
 {
     spmm_any<R>(h, h->P, h->Q, h->inst, s);
     hipLaunchKernelGGL(k_bupdate_r<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->Rv, h->Q, h->inst, h->sig, h->rho);
-    hipLaunchKernelGGL(k_bupdate_xp<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->Xw, h->P, h->Rv, h->inst, h->rho);
+    hipLaunchKernelGGL(k_bupdate_xp<R>, dim3(h->G + (report ? 1 : 0)), dim3(kBlock), 0, s, h->wgs, h->Xw, h->P, h->Rv, h->inst, h->rho,
+                       h->inst - 1, report ? h->word : nullptr);
 }
 
-void iteration(cg_batch *h, hipStream_t s)
+void iteration(cg_batch *h, bool report, hipStream_t s)
 {
     if (h->R == 1)
-        iteration_r<1>(h, s);
+        iteration_r<1>(h, report, s);
     else if (h->R == 2)
-        iteration_r<2>(h, s);
+        iteration_r<2>(h, report, s);
     else
-        iteration_r<4>(h, s);
+        iteration_r<4>(h, report, s);
 }
 
 template <int R>
@@ -1237,8 +1254,7 @@ int build_graph(cg_batch *h)
     if (e != hipSuccess)
         return bfail(h, e, "hipStreamBeginCapture");
     for (int i = 0; i < h->batch; ++i)
-        iteration(h, h->capture);
-    hipLaunchKernelGGL(k_bcheck, dim3(1), dim3(kBlock), 0, h->capture, h->inst, h->nsys * h->R, h->running);
+        iteration(h, (i + 1) % kReportStep == 0, h->capture);
     if ((e = hipStreamEndCapture(h->capture, &h->graph)) != hipSuccess)
         return bfail(h, e, "hipStreamEndCapture");
     if ((e = hipGraphInstantiate(&h->gexec, h->graph, nullptr, nullptr, 0)) != hipSuccess)
@@ -1250,11 +1266,8 @@ int build_graph(cg_batch *h)
 void release(cg_batch *h)
 {
     drop_graph(h);
-    for (auto &e : h->ev)
-        if (e)
-            (void)hipEventDestroy(e);
-    if (h->host_run)
-        (void)hipHostFree(h->host_run);
+    if (h->word)
+        (void)hipHostFree(h->word);
     if (h->host_inst)
         (void)hipHostFree(h->host_inst);
     free_list(h->plan_allocs);
@@ -1322,24 +1335,24 @@ int cg_batch_create(cg_batch **out, int32_t nsys, const int64_t *sys_off, const 
         if ((st = bupload(h.get(), h->allocs, &h->ptr, p0.data(), p0.size())) != CG_OK ||
             (st = bupload(h.get(), h->allocs, &h->idx, i0.data(), i0.size())) != CG_OK ||
             (st = bupload(h.get(), h->allocs, &h->val, vals, i0.size())) != CG_OK ||
-            (st = balloc(h.get(), h->allocs, &h->inst, (size_t)nsys * nrhs)) != CG_OK ||
+            (st = balloc(h.get(), h->allocs, &h->inst, (size_t)nsys * nrhs + kInstAhead)) != CG_OK ||
             (st = balloc(h.get(), h->allocs, &h->P, nv)) != CG_OK ||
             (st = balloc(h.get(), h->allocs, &h->Rv, nv)) != CG_OK ||
             (st = balloc(h.get(), h->allocs, &h->Q, nv)) != CG_OK ||
-            (st = balloc(h.get(), h->allocs, &h->Xw, nv)) != CG_OK ||
-            (st = balloc(h.get(), h->allocs, &h->running, 1)) != CG_OK) {
+            (st = balloc(h.get(), h->allocs, &h->Xw, nv)) != CG_OK) {
             g_berr = h->err;
             release(h.get());
             return st;
         }
+        h->inst += kInstAhead;
         h->hptr.swap(p0);
         h->hidx.swap(i0);
-        hipError_t e = hipHostMalloc((void **)&h->host_run, 2 * sizeof(double), hipHostMallocDefault);
+        hipError_t e =
+            hipHostMalloc((void **)&h->word, sizeof(*h->word), hipHostMallocMapped | hipHostMallocCoherent);
+        if (e == hipSuccess)
+            *h->word = 0;
         if (e == hipSuccess)
             e = hipHostMalloc((void **)&h->host_inst, (size_t)nsys * nrhs * sizeof(Inst), hipHostMallocDefault);
-        for (auto &ev : h->ev)
-            if (e == hipSuccess)
-                e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking);
         if (e != hipSuccess) {
@@ -1490,24 +1503,17 @@ int cg_batch_solve(cg_batch *h, const double *B, double *X, double tol, int32_t 
         init_r<2>(h, B, X, tol, maxit, s);
     else
         init_r<4>(h, B, X, tol, maxit, s);
+    // the next graph when kAhead iterations are left of those launched
+    constexpr int kAhead = 6;
     hipError_t e;
-    auto launch = [&](int slot) -> hipError_t {
-        hipError_t r = hipGraphLaunch(h->gexec, s);
-        if (r == hipSuccess)
-            r = hipMemcpyAsync(&h->host_run[slot], h->running, sizeof(double), hipMemcpyDeviceToHost, s);
-        if (r == hipSuccess)
-            r = hipEventRecord(h->ev[slot], s);
-        return r;
-    };
-    if ((e = launch(0)) != hipSuccess)
-        return done(bfail(h, e, "hipGraphLaunch"));
-    for (int i = 0;; ++i) {
-        if ((e = launch((i + 1) & 1)) != hipSuccess)
+    const uint32_t first = ++h->tick;
+    hipLaunchKernelGGL(k_bstart, dim3(1), dim3(kBlock), 0, s, h->inst, h->nsys * h->R, first);
+    for (uint32_t stop = 0; stop == 0;) {
+        if ((e = hipGraphLaunch(h->gexec, s)) != hipSuccess)
             return done(bfail(h, e, "hipGraphLaunch"));
-        if ((e = hipEventSynchronize(h->ev[i & 1])) != hipSuccess)
-            return done(bfail(h, e, "hipEventSynchronize"));
-        if (h->host_run[i & 1] == 0.0)
-            break;
+        h->tick += (uint32_t)h->batch;
+        if ((e = wait_report(h->word, first, h->tick - kAhead, s, &stop)) != hipSuccess)
+            return done(bfail(h, e, "iteration"));
     }
     if (h->R == 1)
         finish_r<1>(h, B, X, s);

@@ -1354,9 +1354,7 @@ int cg_solve_mixed(cg_handle *h, const double *b, double *x, double tol, int32_t
         ++h->tick;
         launch_outer_norm(h->dm, h->st, h->rho, report_to(h, 0), h->tick, s);
         uint32_t now = 0;
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = wait_report(h->word, h->tick, h->tick, s, &now);
+        const hipError_t e = wait_report(h->word, h->tick, h->tick, s, &now);
         if (e != hipSuccess)
             return done(hip_fail(h->err, e, "refinement"));
         const DevState &in = h->host_st[1];

@@ -32,6 +32,8 @@ inline hipError_t wait_report(const unsigned long long *word, uint32_t first, ui
             std::this_thread::yield();
         if ((spin & 0xfffff) == 0) {
             const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady)
+                (void)hipGetLastError(); // (not an error of the caller's)
             if (e != hipSuccess && e != hipErrorNotReady)
                 return e;
             idle = e == hipSuccess;
