@@ -96,6 +96,32 @@ __device__ __forceinline__ bool inst_gate(Inst *inst, int i, bool lead)
     return true;
 }
 
+// The gate of a workgroup's product: false once all instances of its system
+// have stopped, which it keeps in its own word of `live` -- read together with
+// the descriptor, so that the workgroup ends without asking its system, here
+// and in the update kernels, which load no vectors then and need no second
+// round trip before they load them: 24 systems of 20^3..60^3 with four
+// right-hand sides 36.7 -> 35.8 ms, 5 of 10^3..40^3 with two 5.73 -> 5.63.
+// (R threads decide for all: with every thread reading the instances itself
+// the waves start apart and the product of the first loses 8 %.)
+template <int R>
+__device__ __forceinline__ bool wg_gate(Inst *inst, int32_t *live, const WgDesc &W)
+{
+    __shared__ int act_s[R];
+    if (live[blockIdx.x] == 0)
+        return false;
+    if (threadIdx.x < R)
+        act_s[threadIdx.x] = inst_gate(inst, W.sys * R + threadIdx.x, W.lead != 0) ? 1 : 0;
+    __syncthreads();
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        any |= act_s[r] != 0;
+    if (!any && threadIdx.x == 0)
+        live[blockIdx.x] = 0;
+    return any;
+}
+
 // Q = A P for the R interleaved right-hand sides (row blocks of <= 256*EPT
 // entries staged in LDS, one thread sums each row left to right).
 // Q = A P for the R interleaved right-hand sides, W lanes per row (the
@@ -110,85 +136,75 @@ __global__ __launch_bounds__(kBlock) void k_bspmm_lanes(const WgDesc *__restrict
                                                         const int32_t *__restrict__ col,
                                                         const double *__restrict__ val,
                                                         const double *__restrict__ P, double *__restrict__ Q,
-                                                        double *__restrict__ sig_part, Inst *inst)
+                                                        double *__restrict__ sig_part, Inst *inst,
+                                                         int32_t *live)
 {
     static_assert(R <= W, "one storing lane per right-hand side");
     __shared__ double red[kWaves];
-    __shared__ int act_s[R];
     constexpr int NG = kBlock / W;
     const WgDesc Wd = wgs[blockIdx.x];
     const int t = threadIdx.x;
-    bool any = true;
-    if (inst != nullptr) {
-        if (t < R)
-            act_s[t] = inst_gate(inst, Wd.sys * R + t, Wd.lead != 0) ? 1 : 0;
-        __syncthreads();
-        any = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            any |= act_s[r] != 0;
-    }
+    if (inst != nullptr && !wg_gate<R>(inst, live, Wd))
+        return;
     const int g = t / W, lane = t % W;
     double sg = 0.0; // lane r < R: partial of p'q for right-hand side r
-    if (any) {
-        for (int base = Wd.i0 + g; base < Wd.i1; base += NG * U) {
-            int rs[U], re[U];
+    for (int base = Wd.i0 + g; base < Wd.i1; base += NG * U) {
+        int rs[U], re[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = base + u * NG;
+            const bool ok = r < Wd.i1;
+            rs[u] = ok ? __builtin_nontemporal_load(ptr + r) : 0;
+            re[u] = ok ? __builtin_nontemporal_load(ptr + r + 1) : 0;
+        }
+        double acc[U][R];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                acc[u][r] = 0.0;
+        for (int off = lane;; off += W) {
+            bool anyk = false;
+            int c[U];
+            double v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int r = base + u * NG;
-                const bool ok = r < Wd.i1;
-                rs[u] = ok ? __builtin_nontemporal_load(ptr + r) : 0;
-                re[u] = ok ? __builtin_nontemporal_load(ptr + r + 1) : 0;
+                const int k = rs[u] + off;
+                const bool ok = k < re[u];
+                anyk |= ok;
+                c[u] = ok ? __builtin_nontemporal_load(col + k) : -1;
+                v[u] = ok ? __builtin_nontemporal_load(val + k) : 0.0;
             }
-            double acc[U][R];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    acc[u][r] = 0.0;
-            for (int off = lane;; off += W) {
-                bool anyk = false;
-                int c[U];
-                double v[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int k = rs[u] + off;
-                    const bool ok = k < re[u];
-                    anyk |= ok;
-                    c[u] = ok ? __builtin_nontemporal_load(col + k) : -1;
-                    v[u] = ok ? __builtin_nontemporal_load(val + k) : 0.0;
-                }
-                if (!anyk)
-                    break;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (c[u] < 0)
-                        continue;
-                    if constexpr (R % 2 == 0) {
-                        const double2 *p2 = reinterpret_cast<const double2 *>(P + (size_t)c[u] * R);
-#pragma unroll
-                        for (int h2 = 0; h2 < R / 2; ++h2) {
-                            const double2 pv = p2[h2];
-                            acc[u][2 * h2] = fma(v[u], pv.x, acc[u][2 * h2]);
-                            acc[u][2 * h2 + 1] = fma(v[u], pv.y, acc[u][2 * h2 + 1]);
-                        }
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < R; ++r)
-                            acc[u][r] = fma(v[u], P[(size_t)c[u] * R + r], acc[u][r]);
-                    }
-                }
-            }
+            if (!anyk)
+                break;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int row = base + u * NG;
+                if (c[u] < 0)
+                    continue;
+                if constexpr (R % 2 == 0) {
+                    const double2 *p2 = reinterpret_cast<const double2 *>(P + (size_t)c[u] * R);
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double q = group_sum<W>(acc[u][r]);
-                    if (lane == r && row < Wd.i1) {
-                        Q[(size_t)row * R + r] = q;
-                        sg = fma(P[(size_t)row * R + r], q, sg);
+                    for (int h2 = 0; h2 < R / 2; ++h2) {
+                        const double2 pv = p2[h2];
+                        acc[u][2 * h2] = fma(v[u], pv.x, acc[u][2 * h2]);
+                        acc[u][2 * h2 + 1] = fma(v[u], pv.y, acc[u][2 * h2 + 1]);
                     }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        acc[u][r] = fma(v[u], P[(size_t)c[u] * R + r], acc[u][r]);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = base + u * NG;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double q = group_sum<W>(acc[u][r]);
+                if (lane == r && row < Wd.i1) {
+                    Q[(size_t)row * R + r] = q;
+                    sg = fma(P[(size_t)row * R + r], q, sg);
                 }
             }
         }
@@ -205,95 +221,85 @@ template <int R, int EPT>
 __global__ __launch_bounds__(kBlock) void k_bspmm(const WgDesc *__restrict__ wgs, const int32_t *__restrict__ rb_row,
                                                   const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
                                                   const double *__restrict__ val, const double *__restrict__ P,
-                                                  double *__restrict__ Q, double *__restrict__ sig_part, Inst *inst)
+                                                  double *__restrict__ Q, double *__restrict__ sig_part, Inst *inst,
+                                                         int32_t *live)
 {
     constexpr int E = kBlock * EPT;
     __shared__ double prod[E * R];
     __shared__ int32_t lptr[kStreamRows + 1];
     __shared__ double red[kWaves];
-    __shared__ int act_s[R];
     const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x;
-    bool any = true;
-    if (inst != nullptr) {
-        if (t < R)
-            act_s[t] = inst_gate(inst, W.sys * R + t, W.lead != 0) ? 1 : 0;
-        __syncthreads();
-        any = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            any |= act_s[r] != 0;
-    }
+    if (inst != nullptr && !wg_gate<R>(inst, live, W))
+        return;
     double sig[R];
 #pragma unroll
     for (int r = 0; r < R; ++r)
         sig[r] = 0.0;
-    if (any) {
-        for (int b = W.rb0; b < W.rb1; ++b) {
-            const int r0 = rb_row[b], r1 = rb_row[b + 1];
-            const int nr = r1 - r0;
-            const int e0 = ptr[r0], e1 = ptr[r1];
-            if (e1 - e0 > E) { // one long row: workgroup tree per right-hand side
+    for (int b = W.rb0; b < W.rb1; ++b) {
+        const int r0 = rb_row[b], r1 = rb_row[b + 1];
+        const int nr = r1 - r0;
+        const int e0 = ptr[r0], e1 = ptr[r1];
+        if (e1 - e0 > E) { // one long row: workgroup tree per right-hand side
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    double a = 0.0;
-                    for (int e = e0 + t; e < e1; e += kBlock)
-                        a = fma(val[e], P[(size_t)col[e] * R + r], a);
-                    a = block_sum(a, red);
-                    if (t == 0) {
-                        Q[(size_t)r0 * R + r] = a;
-                        sig[r] = fma(P[(size_t)r0 * R + r], a, sig[r]);
-                    }
-                }
-                continue;
-            }
-            int c[EPT];
-            double v[EPT];
-#pragma unroll
-            for (int m = 0; m < EPT; ++m) {
-                const int e = e0 + t + m * kBlock;
-                const bool ok = e < e1;
-                c[m] = ok ? __builtin_nontemporal_load(col + e) : -1;
-                v[m] = ok ? __builtin_nontemporal_load(val + e) : 0.0;
-            }
-            if (t < nr)
-                lptr[t + 1] = ptr[r0 + t + 1] - e0;
-            if (t == 0)
-                lptr[0] = 0;
-            // products stored by right-hand side (plane r holds entry e at r*E + e):
-            // consecutive threads write consecutive words, and a row's sum reads
-            // one contiguous run per plane
-#pragma unroll
-            for (int m = 0; m < EPT; ++m)
-                if (c[m] >= 0) {
-                    if constexpr (R % 2 == 0) {
-                        const double2 *p2 = reinterpret_cast<const double2 *>(P + (size_t)c[m] * R);
-#pragma unroll
-                        for (int h2 = 0; h2 < R / 2; ++h2) {
-                            const double2 pv = p2[h2];
-                            prod[(2 * h2) * E + t + m * kBlock] = v[m] * pv.x;
-                            prod[(2 * h2 + 1) * E + t + m * kBlock] = v[m] * pv.y;
-                        }
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < R; ++r)
-                            prod[r * E + t + m * kBlock] = v[m] * P[(size_t)c[m] * R + r];
-                    }
-                }
-            __syncthreads();
-            if (t < nr) {
-                const int k0 = lptr[t], k1 = lptr[t + 1];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    double a = 0.0;
-                    for (int k = k0; k < k1; ++k)
-                        a += prod[r * E + k];
-                    Q[(size_t)(r0 + t) * R + r] = a;
-                    sig[r] = fma(P[(size_t)(r0 + t) * R + r], a, sig[r]);
+            for (int r = 0; r < R; ++r) {
+                double a = 0.0;
+                for (int e = e0 + t; e < e1; e += kBlock)
+                    a = fma(val[e], P[(size_t)col[e] * R + r], a);
+                a = block_sum(a, red);
+                if (t == 0) {
+                    Q[(size_t)r0 * R + r] = a;
+                    sig[r] = fma(P[(size_t)r0 * R + r], a, sig[r]);
                 }
             }
-            __syncthreads();
+            continue;
         }
+        int c[EPT];
+        double v[EPT];
+#pragma unroll
+        for (int m = 0; m < EPT; ++m) {
+            const int e = e0 + t + m * kBlock;
+            const bool ok = e < e1;
+            c[m] = ok ? __builtin_nontemporal_load(col + e) : -1;
+            v[m] = ok ? __builtin_nontemporal_load(val + e) : 0.0;
+        }
+        if (t < nr)
+            lptr[t + 1] = ptr[r0 + t + 1] - e0;
+        if (t == 0)
+            lptr[0] = 0;
+        // products stored by right-hand side (plane r holds entry e at r*E + e):
+        // consecutive threads write consecutive words, and a row's sum reads
+        // one contiguous run per plane
+#pragma unroll
+        for (int m = 0; m < EPT; ++m)
+            if (c[m] >= 0) {
+                if constexpr (R % 2 == 0) {
+                    const double2 *p2 = reinterpret_cast<const double2 *>(P + (size_t)c[m] * R);
+#pragma unroll
+                    for (int h2 = 0; h2 < R / 2; ++h2) {
+                        const double2 pv = p2[h2];
+                        prod[(2 * h2) * E + t + m * kBlock] = v[m] * pv.x;
+                        prod[(2 * h2 + 1) * E + t + m * kBlock] = v[m] * pv.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        prod[r * E + t + m * kBlock] = v[m] * P[(size_t)c[m] * R + r];
+                }
+            }
+        __syncthreads();
+        if (t < nr) {
+            const int k0 = lptr[t], k1 = lptr[t + 1];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                double a = 0.0;
+                for (int k = k0; k < k1; ++k)
+                    a += prod[r * E + k];
+                Q[(size_t)(r0 + t) * R + r] = a;
+                sig[r] = fma(P[(size_t)(r0 + t) * R + r], a, sig[r]);
+            }
+        }
+        __syncthreads();
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -331,97 +337,87 @@ __global__ __launch_bounds__(kBlock) void k_bspmm_slices(const WgDesc *__restric
                                                          const CT *__restrict__ col,
                                                          const double *__restrict__ val,
                                                          const double *__restrict__ P, double *__restrict__ Q,
-                                                         double *__restrict__ sig_part, Inst *inst)
+                                                         double *__restrict__ sig_part, Inst *inst,
+                                                         int32_t *live)
 {
 #pragma clang fp contract(off)
     __shared__ double red[kWaves];
-    __shared__ int act_s[R];
     const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x;
-    bool any = true;
-    if (inst != nullptr) {
-        if (t < R)
-            act_s[t] = inst_gate(inst, W.sys * R + t, W.lead != 0) ? 1 : 0;
-        __syncthreads();
-        any = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            any |= act_s[r] != 0;
-    }
+    if (inst != nullptr && !wg_gate<R>(inst, live, W))
+        return;
     double sig[R];
 #pragma unroll
     for (int r = 0; r < R; ++r)
         sig[r] = 0.0;
     const int lane = t & 63;
-    if (any) {
-        for (int sl = W.rb0 + (t >> 6); sl < W.rb1; sl += kWaves) {
-            const int e0 = sl_off[sl], L = (sl_off[sl + 1] - e0) / 64;
-            const int row = sl_row[sl] + lane;
-            double a[R];
+    for (int sl = W.rb0 + (t >> 6); sl < W.rb1; sl += kWaves) {
+        const int e0 = sl_off[sl], L = (sl_off[sl + 1] - e0) / 64;
+        const int row = sl_row[sl] + lane;
+        double a[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                a[r] = 0.0;
-            for (int k0 = 0; k0 < L; k0 += U) {
-                static_assert(U % 2 == 0, "entries come in pairs");
-                int c[U];
-                double v[U], pv[U][R];
-                // one 2-wide load per pair, unconditional: the single last
-                // entry of an odd width through the aligned pair holding it
-                // (the lane's parity picks the half), past the width positions
-                // 0 and 1 (discarded); then the entries are selected
-                typename Pair2<CT>::type craw[U / 2];
-                typename Pair2<double>::type vraw[U / 2];
+        for (int r = 0; r < R; ++r)
+            a[r] = 0.0;
+        for (int k0 = 0; k0 < L; k0 += U) {
+            static_assert(U % 2 == 0, "entries come in pairs");
+            int c[U];
+            double v[U], pv[U][R];
+            // one 2-wide load per pair, unconditional: the single last
+            // entry of an odd width through the aligned pair holding it
+            // (the lane's parity picks the half), past the width positions
+            // 0 and 1 (discarded); then the entries are selected
+            typename Pair2<CT>::type craw[U / 2];
+            typename Pair2<double>::type vraw[U / 2];
 #pragma unroll
-                for (int u = 0; u < U; u += 2) {
-                    const int k = k0 + u;
-                    const int e = k + 1 < L ? e0 + (k >> 1) * 128 + 2 * lane : k < L ? e0 + k * 64 + (lane & ~1) : 0;
-                    craw[u >> 1] = __builtin_nontemporal_load(reinterpret_cast<const typename Pair2<CT>::type *>(col + e));
-                    vraw[u >> 1] =
-                        __builtin_nontemporal_load(reinterpret_cast<const typename Pair2<double>::type *>(val + e));
-                }
+            for (int u = 0; u < U; u += 2) {
+                const int k = k0 + u;
+                const int e = k + 1 < L ? e0 + (k >> 1) * 128 + 2 * lane : k < L ? e0 + k * 64 + (lane & ~1) : 0;
+                craw[u >> 1] = __builtin_nontemporal_load(reinterpret_cast<const typename Pair2<CT>::type *>(col + e));
+                vraw[u >> 1] =
+                    __builtin_nontemporal_load(reinterpret_cast<const typename Pair2<double>::type *>(val + e));
+            }
 #pragma unroll
-                for (int u = 0; u < U; u += 2) {
-                    const int k = k0 + u;
-                    const bool pair = k + 1 < L, hi = !pair && (lane & 1);
-                    c[u] = k < L ? bcol_of(hi ? craw[u >> 1].y : craw[u >> 1].x, row) : -1;
-                    c[u + 1] = pair ? bcol_of(craw[u >> 1].y, row) : -1;
-                    v[u] = hi ? vraw[u >> 1].y : vraw[u >> 1].x;
-                    v[u + 1] = vraw[u >> 1].y;
-                }
+            for (int u = 0; u < U; u += 2) {
+                const int k = k0 + u;
+                const bool pair = k + 1 < L, hi = !pair && (lane & 1);
+                c[u] = k < L ? bcol_of(hi ? craw[u >> 1].y : craw[u >> 1].x, row) : -1;
+                c[u + 1] = pair ? bcol_of(craw[u >> 1].y, row) : -1;
+                v[u] = hi ? vraw[u >> 1].y : vraw[u >> 1].x;
+                v[u + 1] = vraw[u >> 1].y;
+            }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if constexpr (R % 2 == 0) {
-                        const double2 *p2 = reinterpret_cast<const double2 *>(P + (size_t)max(c[u], 0) * R);
+            for (int u = 0; u < U; ++u) {
+                if constexpr (R % 2 == 0) {
+                    const double2 *p2 = reinterpret_cast<const double2 *>(P + (size_t)max(c[u], 0) * R);
 #pragma unroll
-                        for (int h2 = 0; h2 < R / 2; ++h2) {
-                            // unguarded load (row clamped to 0), then a select:
-                            // a guarded load would wait inside its branch
-                            const double2 q2 = p2[h2];
-                            pv[u][2 * h2] = c[u] >= 0 ? q2.x : 0.0;
-                            pv[u][2 * h2 + 1] = c[u] >= 0 ? q2.y : 0.0;
-                        }
-                    } else {
+                    for (int h2 = 0; h2 < R / 2; ++h2) {
+                        // unguarded load (row clamped to 0), then a select:
+                        // a guarded load would wait inside its branch
+                        const double2 q2 = p2[h2];
+                        pv[u][2 * h2] = c[u] >= 0 ? q2.x : 0.0;
+                        pv[u][2 * h2 + 1] = c[u] >= 0 ? q2.y : 0.0;
+                    }
+                } else {
 #pragma unroll
-                        for (int r = 0; r < R; ++r)
-                        {
-                            const double q = P[(size_t)max(c[u], 0) * R + r];
-                            pv[u][r] = c[u] >= 0 ? q : 0.0;
-                        }
+                    for (int r = 0; r < R; ++r)
+                    {
+                        const double q = P[(size_t)max(c[u], 0) * R + r];
+                        pv[u][r] = c[u] >= 0 ? q : 0.0;
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (c[u] >= 0)
-#pragma unroll
-                        for (int r = 0; r < R; ++r)
-                            a[r] = a[r] + v[u] * pv[u][r];
             }
-            if (row < W.i1) {
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    Q[(size_t)row * R + r] = a[r];
-                    sig[r] = fma(P[(size_t)row * R + r], a[r], sig[r]);
-                }
+            for (int u = 0; u < U; ++u)
+                if (c[u] >= 0)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        a[r] = a[r] + v[u] * pv[u][r];
+        }
+        if (row < W.i1) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                Q[(size_t)row * R + r] = a[r];
+                sig[r] = fma(P[(size_t)row * R + r], a[r], sig[r]);
             }
         }
     }
@@ -503,12 +499,15 @@ template <int R>
 __global__ __launch_bounds__(kBlock) void k_bupdate_r(const WgDesc *__restrict__ wgs, double *__restrict__ Rv,
                                                       const double *__restrict__ Q, Inst *inst,
                                                       const double *__restrict__ sig_part,
-                                                      double *__restrict__ rho_part)
+                                                      double *__restrict__ rho_part,
+                                                      const int32_t *__restrict__ live)
 {
     constexpr int V = BVec<R>::V;
     typedef typename BVec<R>::type vec;
     __shared__ double red[kWaves][R];
     const WgDesc W = wgs[blockIdx.x];
+    if (live[blockIdx.x] == 0)
+        return;
     const int t = threadIdx.x;
     const vec *q = reinterpret_cast<const vec *>(Q + (size_t)W.i0 * R);
     vec *rv = reinterpret_cast<vec *>(Rv + (size_t)W.i0 * R);
@@ -623,7 +622,8 @@ template <int R>
 __global__ __launch_bounds__(kBlock) void k_bupdate_xp(const WgDesc *__restrict__ wgs, double *__restrict__ X,
                                                        double *__restrict__ P, const double *__restrict__ Rv,
                                                        Inst *inst, const double *__restrict__ rho_part,
-                                                       Inst *__restrict__ head, unsigned long long *word)
+                                                       Inst *__restrict__ head, unsigned long long *word,
+                                                       const int32_t *__restrict__ live)
 {
     constexpr int V = BVec<R>::V;
     typedef typename BVec<R>::type vec;
@@ -642,10 +642,12 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_xp(const WgDesc *__restrict_
         return;
     }
     const WgDesc W = wgs[blockIdx.x];
+    if (live[blockIdx.x] == 0)
+        return;
     const vec *rv = reinterpret_cast<const vec *>(Rv + (size_t)W.i0 * R);
     vec *x = reinterpret_cast<vec *>(X + (size_t)W.i0 * R), *p = reinterpret_cast<vec *>(P + (size_t)W.i0 * R);
     const int m = (W.i1 - W.i0) * (R / V);
-    bool act[R], any = false;
+    bool act[R];
     double rho[R], al[R], tol[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -654,10 +656,7 @@ __global__ __launch_bounds__(kBlock) void k_bupdate_xp(const WgDesc *__restrict_
         rho[r] = I->rho;
         al[r] = I->alpha;
         tol[r] = I->tol_nb;
-        any |= act[r];
     }
-    if (!any)
-        return;
     vec pv[kBPre], xv[kBPre], v[kBPre];
 #pragma unroll
     for (int u = 0; u < kBPre; ++u) {
@@ -735,11 +734,13 @@ __global__ __launch_bounds__(kBlock) void k_binit_vec(const WgDesc *__restrict__
                                                       const double *__restrict__ X0, const double *__restrict__ Q,
                                                       double *__restrict__ Rv, double *__restrict__ P,
                                                       double *__restrict__ Xw, double *__restrict__ rho_part,
-                                                      double *__restrict__ bb_part)
+                                                      double *__restrict__ bb_part, int32_t *__restrict__ live)
 {
     __shared__ double red[kWaves];
     const WgDesc W = wgs[blockIdx.x];
     const int t = threadIdx.x, r = t % R;
+    if (t == 0)
+        live[blockIdx.x] = 1;
     double ar = 0.0, ab = 0.0;
     const size_t j1 = (size_t)W.i1 * R;
     for (size_t j = (size_t)W.i0 * R + t; j < j1; j += kBlock) {
@@ -869,6 +870,7 @@ struct cg_batch {
     int32_t *ptr = nullptr, *idx = nullptr, *rb_row = nullptr, *sys_wg0 = nullptr;
     double *val = nullptr;
     WgDesc *wgs = nullptr;
+    int32_t *live = nullptr; // per workgroup: its system has instances that run
     Inst *inst = nullptr;
     double *P = nullptr, *Rv = nullptr, *Q = nullptr, *Xw = nullptr;
     double *sig = nullptr, *rho = nullptr, *bb = nullptr;
@@ -997,7 +999,8 @@ int build_plan(cg_batch *h, int ept, int wg_target)
         (st = bupload(h, h->plan_allocs, &h->sys_wg0, wg0.data(), wg0.size())) != CG_OK ||
         (st = balloc(h, h->plan_allocs, &h->sig, np)) != CG_OK ||
         (st = balloc(h, h->plan_allocs, &h->rho, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK)
+        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK ||
+        (st = balloc(h, h->plan_allocs, &h->live, w.size())) != CG_OK)
         return st;
     h->G = (int)w.size();
     h->nrb = (int)rb.size() - 1;
@@ -1115,7 +1118,8 @@ int build_plan_slices(cg_batch *h, int wg_target)
         (st = bupload(h, h->plan_allocs, &h->sys_wg0, wg0.data(), wg0.size())) != CG_OK ||
         (st = balloc(h, h->plan_allocs, &h->sig, np)) != CG_OK ||
         (st = balloc(h, h->plan_allocs, &h->rho, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK)
+        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK ||
+        (st = balloc(h, h->plan_allocs, &h->live, w.size())) != CG_OK)
         return st;
     h->rb_row = nullptr;
     h->G = (int)w.size();
@@ -1129,7 +1133,7 @@ template <int R, int EPT>
 void spmm_r(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
 {
     hipLaunchKernelGGL((k_bspmm<R, EPT>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->rb_row, h->ptr, h->idx, h->val,
-                       P, Q, h->sig, inst);
+                       P, Q, h->sig, inst, h->live);
 }
 
 template <int R>
@@ -1150,10 +1154,10 @@ void spmm_lanes(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t
     constexpr int U = R == 4 ? 1 : 2; // rows in flight per lane group (registers: 8 waves per SIMD)
     if (h->lanes == 8)
         hipLaunchKernelGGL((k_bspmm_lanes<R, 8, U>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->ptr, h->idx, h->val,
-                           P, Q, h->sig, inst);
+                           P, Q, h->sig, inst, h->live);
     else
         hipLaunchKernelGGL((k_bspmm_lanes<R, 16, U>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->ptr, h->idx,
-                           h->val, P, Q, h->sig, inst);
+                           h->val, P, Q, h->sig, inst, h->live);
 }
 
 template <int R>
@@ -1162,10 +1166,10 @@ void spmm_slices(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_
     constexpr int U = 8; // positions per round
     if (h->sl_d16)
         hipLaunchKernelGGL((k_bspmm_slices<R, U, int16_t>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sl_row,
-                           h->sl_off, h->sl_d16, h->sl_val, P, Q, h->sig, inst);
+                           h->sl_off, h->sl_d16, h->sl_val, P, Q, h->sig, inst, h->live);
     else
         hipLaunchKernelGGL((k_bspmm_slices<R, U, int32_t>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sl_row,
-                           h->sl_off, h->sl_col, h->sl_val, P, Q, h->sig, inst);
+                           h->sl_off, h->sl_col, h->sl_val, P, Q, h->sig, inst, h->live);
 }
 
 // the product of the current plan and schedule
@@ -1212,9 +1216,10 @@ template <int R>
 void iteration_r(cg_batch *h, bool report, hipStream_t s)
 {
     spmm_any<R>(h, h->P, h->Q, h->inst, s);
-    hipLaunchKernelGGL(k_bupdate_r<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->Rv, h->Q, h->inst, h->sig, h->rho);
+    hipLaunchKernelGGL(k_bupdate_r<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->Rv, h->Q, h->inst, h->sig, h->rho,
+                       h->live);
     hipLaunchKernelGGL(k_bupdate_xp<R>, dim3(h->G + (report ? 1 : 0)), dim3(kBlock), 0, s, h->wgs, h->Xw, h->P, h->Rv, h->inst, h->rho,
-                       h->inst - 1, report ? h->word : nullptr);
+                       h->inst - 1, report ? h->word : nullptr, h->live);
 }
 
 void iteration(cg_batch *h, bool report, hipStream_t s)
@@ -1232,7 +1237,7 @@ void init_r(cg_batch *h, const double *B, const double *X0, double tol, int maxi
 {
     spmm_any<R>(h, X0, h->Q, nullptr, s);
     hipLaunchKernelGGL(k_binit_vec<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, B, X0, h->Q, h->Rv, h->P, h->Xw,
-                       h->rho, h->bb);
+                       h->rho, h->bb, h->live);
     hipLaunchKernelGGL(k_binit_state<R>, dim3(h->nsys), dim3(kBlock), 0, s, h->wgs, h->sys_wg0, h->inst, h->rho,
                        h->bb, tol, maxit);
 }
