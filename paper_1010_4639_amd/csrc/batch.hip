@@ -482,8 +482,13 @@ __device__ __forceinline__ void sys_sums(double s, double (&red)[kWaves][R], dou
 // right-hand sides of one row where R is even: 16 bytes, aligned, since a row
 // starts at a multiple of R elements), the first kBPre loads of a thread
 // before the system's partials are summed.  A thread keeps its right-hand
-// sides, because the stride kBlock * V is a multiple of R.
-constexpr int kBPre = 4;
+// sides, because the stride kBlock * V is a multiple of R.  One load ahead is
+// enough: the plans give a workgroup one or two elements a thread, a deeper
+// prefetch mostly loads its last element again and holds registers that
+// further workgroups need (kBPre 1 / 2 / 4: 24 systems of 20^3..60^3 with four
+// right-hand sides 34.7 / 34.7 / 35.9 ms, 17 of 25^3..35^3 4.65 / 4.75 / 5.02,
+// one of 40^3 2.90 / 2.97 / 3.17).
+constexpr int kBPre = 1;
 template <int R>
 struct BVec {
     static constexpr int V = R % 2 == 0 ? 2 : 1;
