@@ -870,6 +870,7 @@ struct cg_batch {
     int32_t *sl_row = nullptr, *sl_off = nullptr, *sl_col = nullptr;
     int16_t *sl_d16 = nullptr; // columns as 16-bit offsets from the row (every one within 32767), else null
     double *sl_val = nullptr;
+    bool deep = false; // the slices are read with 16 positions in flight (kDeepBytes)
     // device
     std::vector<void *> allocs, plan_allocs;
     int32_t *ptr = nullptr, *idx = nullptr, *rb_row = nullptr, *sys_wg0 = nullptr;
@@ -1014,6 +1015,10 @@ int build_plan(cg_batch *h, int ept, int wg_target)
     return CG_OK;
 }
 
+// Bytes of sliced values and columns beyond which a product reads them with
+// more positions in flight (spmm_slices).
+constexpr int64_t kDeepBytes = 128ll << 20;
+
 // The sliced layout of the block-diagonal matrix, once: each system's rows
 // in slices of 64 (the last one of a system may be short), entries paired as
 // in k_bspmm_slices (slice_position), padded with column -1 / value 0.
@@ -1081,6 +1086,9 @@ int ensure_slices(cg_batch *h)
         return bfail(h, e, "sliced values");
     h->hsl_row.swap(row0);
     h->hsl_sys0.swap(sys0);
+    h->deep = (int64_t)npos * (8 + (c16 ? 2 : 4)) > kDeepBytes;
+    if (const char *ev = std::getenv("CGMI_BATCH_DEEP")) // (tests, experiments)
+        h->deep = std::atoi(ev) != 0;
     return CG_OK;
 }
 
@@ -1165,16 +1173,33 @@ void spmm_lanes(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t
                            h->val, P, Q, h->sig, inst, h->live);
 }
 
-template <int R>
-void spmm_slices(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+// U: positions of a row in flight.  16 take a tetrahedral row in one round and
+// keep the memory busy where the matrix comes from there; while it stays in the
+// last-level cache (256 MB, shared with the vectors), the registers cost more
+// waves than the second round costs time, and with four right-hand sides
+// always.  Solves, 8 / 16: matrix of 74 MB (17 systems of 25^3..35^3, two
+// right-hand sides) 5.63 / 5.91 ms, 120 MB (17 of 29^3..44^3) 10.3 / 10.2, 170
+// MB (24 of those) 16.0 / 14.7, 213 MB (24 of 30^3..48^3, one) 17.9 / 16.0; 260
+// MB with four 34.8 / 35.7.
+template <int R, int U>
+void spmm_slices_u(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
 {
-    constexpr int U = 8; // positions per round
     if (h->sl_d16)
         hipLaunchKernelGGL((k_bspmm_slices<R, U, int16_t>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sl_row,
                            h->sl_off, h->sl_d16, h->sl_val, P, Q, h->sig, inst, h->live);
     else
         hipLaunchKernelGGL((k_bspmm_slices<R, U, int32_t>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sl_row,
                            h->sl_off, h->sl_col, h->sl_val, P, Q, h->sig, inst, h->live);
+}
+
+template <int R>
+void spmm_slices(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+{
+    if constexpr (R <= 2) {
+        if (h->deep)
+            return spmm_slices_u<R, 16>(h, P, Q, inst, s);
+    }
+    spmm_slices_u<R, 8>(h, P, Q, inst, s);
 }
 
 // the product of the current plan and schedule
