@@ -50,7 +50,7 @@ KERNEL_SRC = os.path.join(ROOT, "paper_1010_4639_amd", "csrc", "kernels.hip")
 # them; CSR and CSC slices differ in their first template argument)
 PRODUCT_KERNELS = {"csr": ("k_spmv_slices<false", "k_spmv_csr"),
                    "symcsr": ("k_scatter_",),
-                   "csc": ("k_spmv_slices<true", "k_panel_")}
+                   "csc": ("k_spmv_slices<", "k_panel_")}  # rows of the transpose, or panels
 EXTRAS = ("formats", "mixed", "small", "batch", "adjoint", "cpu")
 T_START = time.time()
 
@@ -551,7 +551,7 @@ def parse_counters(a):
                                     f"--spmv-reps {a.spmv_reps} --counter-dirs {show[0]},{show[1]}"]),
                note="HBM bytes per product launch (mean over its launches), each counter scaled by what it reads "
                     "for a 1 GiB device copy in the same run (FETCH_SIZE counts 64-byte requests, hence the factor "
-                    "~2); symcsr and csc include their row-pass kernel (k_scatter_gather / k_panel_gather) of the "
+                    "~2); symcsr includes its row-pass kernel (k_scatter_gather; csc on panels k_panel_gather) of the "
                     "lone product, which inside CG is folded into the r update; detail.<format>.kernels splits the "
                     "bytes by kernel")
     with open(traffic_file(a.workload), "w") as f:
@@ -638,7 +638,7 @@ def main():
     del c
     kernel = {"csr": "k_spmv_slices (CSR product, 64-row slices)" if prod["sliced"] else "k_spmv_csr_rows",
               "symcsr": "symmetric-CSR product (scatter kernel + row pass)",
-              "csc": "CSC product on column panels (slot kernel + row pass)"}[a.format]
+              "csc": "CSC product (rows of the transposed arrays in slices, or column panels + row pass)"}[a.format]
     # a matrix that stays in the Infinity Cache between products is priced
     # against HBM on its cold launches (after the 1 GiB read); its warm rate
     # is an effective cache rate, reported beside it

@@ -157,7 +157,7 @@ int cg_set_batch(cg_handle *h, int32_t iters_per_launch);
  * r -= alpha Ap, beta = r'r / r_old'r_old, p = r + beta p), with the one
  * product Ap per iteration of that section and every scalar kept on the
  * device -- the paper moves only the scalars between host and GPU; here the
- * host reads a status word once per launched group of iterations.  Systems of
+ * host follows them in a word of pinned memory, written each iteration.  Systems of
  * at most 262 144 rows whose rows are sliced run the whole iteration in one
  * kernel where a workgroup per compute unit has a place on the device (same
  * bits as the launches it takes otherwise).

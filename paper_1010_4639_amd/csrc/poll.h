@@ -26,6 +26,11 @@ inline hipError_t wait_report(const unsigned long long *word, uint32_t first, ui
         }
         if (idle) // all work of the stream is done, and no report
             return hipErrorUnknown;
+        if (spin == 4096) { // (in a capture nothing runs, so nothing reports)
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            if (s != nullptr && hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+                return hipErrorStreamCaptureUnsupported;
+        }
         if (spin < 4096)
             _mm_pause();
         else
