@@ -353,6 +353,25 @@ int cg_get_stats(const cg_handle *h, cg_plan_stats *stats);
  * to solution -- section III.) */
 void cg_destroy(cg_handle *h);
 
+/*
+ * How the handle's last cg_solve or cg_solve_mixed ran.  The paths give the
+ * same bits; they differ in time only (30 720 rows: an iteration 4.9 us
+ * resident, 8.5 by launches).
+ */
+enum {
+    CG_PATH_NONE = 0,     /* no solve yet */
+    CG_PATH_RESIDENT = 1, /* one kernel for the whole solve */
+    CG_PATH_LAUNCHES = 2, /* graphs of launches: no resident kernel is planned, or it found no place */
+    CG_PATH_REPEATED = 3  /* a wait of the resident kernel ran out: the solve was repeated by launches */
+};
+typedef struct {
+    int32_t path;         /* CG_PATH_* */
+    int32_t resident_wgs; /* workgroups of the resident kernel that cg_solve may take on this handle; 0: none */
+    int32_t graphs;       /* graphs of iterations launched */
+    int32_t ahead;        /* those launched while iterations of the graph before were still to come */
+} cg_solve_report;
+int cg_get_solve_report(const cg_handle *h, cg_solve_report *report);
+
 /* Static text for a status code. */
 const char *cg_status_string(int status);
 
@@ -432,6 +451,39 @@ int cg_analyze_compact(int64_t n, const int32_t *ptr, const int32_t *idx, int in
 int cg_analyze_panels(int64_t n, const int32_t *ptr, const int32_t *idx, int index_base, int64_t *width,
                       int32_t *entry_src, int32_t *slot_target, int32_t *slot_ptr, int32_t *slot_panel,
                       int32_t *chunk_slot, int32_t *first_parked);
+
+/*
+ * Host-only export of the plan of a resident solve (the whole iteration of
+ * cg_solve in one kernel) for the rows that cg_create would lay out, so it can
+ * be checked independently.  The rows are cut into slices of 64 and the slices
+ * into `product_wgs` runs; resident workgroup b stands for runs
+ * [b * product_wgs / wgs, (b + 1) * product_wgs / wgs), run g for slices
+ * [g * slices / product_wgs, (g + 1) * slices / product_wgs), and, per 256 of
+ * its threads, for one of `vec_wgs` runs of `vec_chunk` rows.  wgs == 0: no
+ * resident solve is planned (too many rows, lines too long, a workgroup with
+ * too many columns, rows not sliced).
+ *   slice_off  [slices+1] int32: first position of each slice
+ *   col_ptr    [wgs+1] int32: the columns of workgroup b are
+ *              [col_ptr[b], col_ptr[b+1]) of
+ *   col        [columns] int32: ascending; every column of its rows, and the rows
+ *   entry      [positions] uint16: entry k of lane l of a slice, at
+ *              slice_off + 64 k + l, is 8 times the place of its column in the
+ *              list; 65535 = no entry
+ *   own        [n] uint16: place of each row in its workgroup's list
+ * Any output array may be NULL.  Same errors as cg_analyze.
+ */
+typedef struct {
+    int32_t wgs, threads;            /* workgroups, threads of each */
+    int32_t slices_per_wave;         /* slices of a wavefront = vector rows of a thread, at most */
+    int32_t width, max_columns;      /* longest line, longest column list */
+    int32_t slices, product_wgs;
+    int32_t vec_wgs, vec_chunk;
+    int32_t reserved;
+    int64_t columns, positions;      /* sizes of col and entry */
+} cg_resident_plan;
+int cg_analyze_resident(int format, int64_t n, const int32_t *ptr, const int32_t *idx, int index_base,
+                        cg_resident_plan *plan, int32_t *slice_off, int32_t *col_ptr, int32_t *col, uint16_t *entry,
+                        uint16_t *own);
 
 #ifdef __cplusplus
 }

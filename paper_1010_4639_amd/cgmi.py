@@ -30,7 +30,9 @@ EXPORTS = ("cg_create", "cg_set_stream", "cg_set_batch", "cg_solve", "cg_solve_m
            "cg_batch_create", "cg_batch_set_stream", "cg_batch_spmm", "cg_batch_autotune", "cg_batch_solve",
            "cg_batch_destroy", "cg_batch_last_error", "cg_set_values", "cg_pattern_grad", "cg_fem_create",
            "cg_fem_set_stream", "cg_fem_pattern", "cg_fem_assemble", "cg_fem_nu_grad", "cg_fem_destroy",
-           "cg_fem_last_error", "cg_analyze_panels", "cg_analyze_compact", "cg_spmv_static")
+           "cg_fem_last_error", "cg_analyze_panels", "cg_analyze_compact", "cg_spmv_static", "cg_get_solve_report",
+           "cg_analyze_resident")
+CG_PATH_NONE, CG_PATH_RESIDENT, CG_PATH_LAUNCHES, CG_PATH_REPEATED = 0, 1, 2, 3
 
 
 class cg_info(ctypes.Structure):
@@ -50,6 +52,22 @@ class cg_plan_stats(ctypes.Structure):
                 ("slices", ctypes.c_int32),
                 ("cached_loads", ctypes.c_int32), ("compact", ctypes.c_int32), ("slots", ctypes.c_int64),
                 ("plan_bytes", ctypes.c_int64), ("parked", ctypes.c_int64), ("device_bytes", ctypes.c_int64)]
+
+    def as_dict(self):
+        return {f: getattr(self, f) for f, _ in self._fields_ if f != "reserved"}
+
+
+class cg_solve_report(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("path", "resident_wgs", "graphs", "ahead")]
+
+    def as_dict(self):
+        return {f: getattr(self, f) for f, _ in self._fields_}
+
+
+class cg_resident_plan(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("wgs", "threads", "slices_per_wave", "width", "max_columns", "slices",
+                                              "product_wgs", "vec_wgs", "vec_chunk", "reserved")] + \
+               [("columns", ctypes.c_int64), ("positions", ctypes.c_int64)]
 
     def as_dict(self):
         return {f: getattr(self, f) for f, _ in self._fields_ if f != "reserved"}
@@ -108,6 +126,9 @@ def load():
     lib.cg_batch_last_error.restype = ctypes.c_char_p
     lib.cg_analyze_panels.argtypes = [i64, _VP, _VP, ctypes.c_int] + [_VP] * 7
     lib.cg_analyze_compact.argtypes = [i64, _VP, _VP, ctypes.c_int] + [_VP] * 5
+    lib.cg_get_solve_report.argtypes = [_VP, ctypes.POINTER(cg_solve_report)]
+    lib.cg_analyze_resident.argtypes = [ctypes.c_int, i64, _VP, _VP, ctypes.c_int,
+                                        ctypes.POINTER(cg_resident_plan)] + [_VP] * 5
     lib.cg_set_values.argtypes = [_VP, _VP]
     lib.cg_pattern_grad.argtypes = [_VP, _VP, _VP, _VP]
     lib.cg_fem_create.argtypes = [ctypes.POINTER(_VP), i64, _VP, i64, _VP, _VP, i64]
@@ -121,7 +142,8 @@ def load():
     lib.cg_fem_last_error.restype = ctypes.c_char_p
     for nm in ("cg_batch_create", "cg_batch_set_stream", "cg_batch_spmm", "cg_batch_autotune", "cg_batch_solve",
                "cg_set_values", "cg_pattern_grad", "cg_fem_create", "cg_fem_set_stream", "cg_fem_pattern",
-               "cg_fem_assemble", "cg_fem_nu_grad", "cg_analyze_panels", "cg_analyze_compact"):
+               "cg_fem_assemble", "cg_fem_nu_grad", "cg_analyze_panels", "cg_analyze_compact",
+               "cg_get_solve_report", "cg_analyze_resident"):
         getattr(lib, nm).restype = ctypes.c_int
     for nm in ("cg_create", "cg_set_stream", "cg_set_batch", "cg_solve", "cg_solve_mixed", "cg_spmv",
                "cg_spmv_static", "cg_get_stats",
@@ -218,6 +240,13 @@ def cg_get_stats(handle):
     return st, s.as_dict()
 
 
+def cg_get_solve_report(handle):
+    """How the handle's last solve ran: (status, dict)."""
+    r = cg_solve_report()
+    st = load().cg_get_solve_report(handle, ctypes.byref(r))
+    return st, r.as_dict()
+
+
 def cg_destroy(handle):
     if handle:
         load().cg_destroy(handle)
@@ -287,6 +316,23 @@ def cg_analyze_panels(n, ptr, idx, index_base=0):
                                _np_ptr(out["chunk_slot"]), ctypes.byref(fp))
     out["entry_src"], out["target"], out["panel"] = out["entry_src"][:nnz], out["target"][:ns], out["panel"][:ns]
     out["width"], out["first_parked"] = w.value, fp.value
+    return st, out
+
+
+def cg_analyze_resident(fmt, n, ptr, idx, index_base=0):
+    """Host-only plan of a resident solve; returns (status, dict): the sizes and,
+    where one is planned (wgs > 0), the arrays."""
+    lib = load()
+    p, i, r = _host_i32(ptr), _host_i32(idx), cg_resident_plan()
+    args = (_fmt(fmt), int(n), _np_ptr(p), _np_ptr(i), int(index_base), ctypes.byref(r))
+    st = lib.cg_analyze_resident(*args, *[None] * 5)
+    out = r.as_dict()
+    if st == CG_OK and r.wgs > 0:
+        out.update(slice_off=np.empty(r.slices + 1, np.int32), col_ptr=np.empty(r.wgs + 1, np.int32),
+                   col=np.empty(r.columns, np.int32), entry=np.empty(r.positions, np.uint16),
+                   own=np.empty(int(n), np.uint16))
+        st = lib.cg_analyze_resident(*args, *[_np_ptr(out[k]) for k in ("slice_off", "col_ptr", "col", "entry",
+                                                                        "own")])
     return st, out
 
 
@@ -388,6 +434,10 @@ class Solver:
 
     def stats(self):
         return cg_get_stats(self.h)[1]
+
+    def report(self):
+        """How the last solve ran (CG_PATH_*), and the resident kernel's size."""
+        return cg_get_solve_report(self.h)[1]
 
     def close(self):
         if self.h:

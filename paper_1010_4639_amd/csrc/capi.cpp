@@ -79,6 +79,7 @@ struct cg_handle {
     hipGraph_t graph32 = nullptr;
     hipGraphExec_t gexec32 = nullptr;
     int graph32_batch = 0, graph32_iters = 0;
+    cg_solve_report report{}; // of the last solve
     // caller entry order -> normalised order (lower-triangle input), device copy
     int32_t *perm = nullptr;
     int32_t *flag = nullptr; // device word for checks made by kernels
@@ -673,8 +674,11 @@ int run_until_stop(cg_handle *h, hipGraphExec_t ge, int nb, DevState *st)
     const uint32_t first = h->tick;
     uint32_t stop = 0;
     while (stop == 0) {
+        if (h->tick != first && (uint32_t)(__atomic_load_n(h->word, __ATOMIC_RELAXED) >> 32) != h->tick)
+            ++h->report.ahead;
         if ((e = hipGraphLaunch(ge, s)) != hipSuccess)
             return hip_fail(h->err, e, "hipGraphLaunch");
+        ++h->report.graphs;
         h->tick += (uint32_t)nb;
         if ((e = wait_report(h->word, first, h->tick - kAhead, s, &stop)) != hipSuccess)
             return hip_fail(h->err, e, "iteration");
@@ -908,6 +912,30 @@ hipError_t vec_out_of(cg_handle *h, const DevMatrix &m, const double *src, doubl
     return hipGetLastError();
 }
 
+// The plans of a handle: the storage format's, and the second one by rows
+// (row_plan.n = 0: none), side by side where that pays (plan.h).
+int build_plans(int format, int64_t n, const std::vector<int32_t> &p0, const std::vector<int32_t> &i0, Plan &plan,
+                Plan &row_plan, std::string &err)
+{
+    std::future<bool> ahead; // (joined by its destructor where a step below throws)
+    const auto by_rows = [&] { return build_row_plan(format, n, p0.data(), i0.data(), row_plan); };
+    if (n > 0 && row_plan_ahead(format, n, p0[n])) {
+        try {
+            ahead = std::async(std::launch::async, by_rows);
+        } catch (const std::system_error &) { // no thread: planned below
+        }
+    }
+    const int st = build_plan(format, n, p0.data(), i0.data(), scatter_entries_override(), plan, err);
+    const bool planned = ahead.valid();
+    if (planned)
+        ahead.get();
+    if (st != CG_OK || !takes_row_plan(plan))
+        row_plan = Plan{};
+    else if (!planned)
+        by_rows();
+    return st;
+}
+
 int status_to_code(int32_t s)
 {
     switch (s) {
@@ -1065,6 +1093,50 @@ int cg_analyze_panels(int64_t n, const int32_t *ptr, const int32_t *idx, int ind
     return st;
 }
 
+int cg_analyze_resident(int format, int64_t n, const int32_t *ptr, const int32_t *idx, int index_base,
+                        cg_resident_plan *plan, int32_t *slice_off, int32_t *col_ptr, int32_t *col, uint16_t *entry,
+                        uint16_t *own)
+{
+    std::vector<int32_t> p0, i0;
+    std::string err;
+    int st;
+    try {
+        st = validate_and_normalise(format, n, ptr, idx, nullptr, index_base, 0, p0, i0, err);
+        Plan main, rows;
+        if (st == CG_OK)
+            st = build_plans(format, n, p0, i0, main, rows, err);
+        if (st == CG_OK) {
+            const Plan &p = rows.rs_wgs > 0 ? rows : main;
+            cg_resident_plan r{};
+            if (p.rs_wgs > 0) {
+                r.wgs = p.rs_wgs;
+                r.threads = p.rs_threads;
+                r.slices_per_wave = p.rs_slices;
+                r.width = p.rs_width;
+                r.max_columns = p.rs_cols;
+                r.slices = (int32_t)p.sl_off.size() - 1;
+                r.product_wgs = p.csr_blocks;
+                r.vec_wgs = p.vec_blocks;
+                r.vec_chunk = p.vec_chunk;
+                r.columns = (int64_t)p.rs_gcol.size();
+                r.positions = (int64_t)p.rs_lcol.size();
+                if (slice_off) std::memcpy(slice_off, p.sl_off.data(), p.sl_off.size() * 4);
+                if (col_ptr) std::memcpy(col_ptr, p.rs_gptr.data(), p.rs_gptr.size() * 4);
+                if (col) std::memcpy(col, p.rs_gcol.data(), p.rs_gcol.size() * 4);
+                if (entry) std::memcpy(entry, p.rs_lcol.data(), p.rs_lcol.size() * 2);
+                if (own) std::memcpy(own, p.rs_lown.data(), p.rs_lown.size() * 2);
+            }
+            if (plan)
+                *plan = r;
+        }
+    } catch (const std::bad_alloc &) {
+        err = "host allocation failed";
+        st = CG_ERR_NOMEM;
+    }
+    g_err = st == CG_OK ? std::string() : err;
+    return st;
+}
+
 int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const int32_t *idx, const double *vals,
               int index_base, uint32_t flags)
 {
@@ -1089,23 +1161,8 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
                 pvals[k] = vals[perm[k]];
             vals = pvals.data();
         }
-        std::future<bool> ahead; // (joined by its destructor where a step below throws)
-        const auto by_rows = [&] { return build_row_plan(format, n, p0.data(), i0.data(), h->row_plan); };
-        if (st == CG_OK && n > 0 && row_plan_ahead(format, n, p0[n])) {
-            try {
-                ahead = std::async(std::launch::async, by_rows);
-            } catch (const std::system_error &) { // no thread: planned below
-            }
-        }
         if (st == CG_OK)
-            st = build_plan(format, n, p0.data(), i0.data(), scatter_entries_override(), h->plan, h->err);
-        const bool planned = ahead.valid();
-        if (planned)
-            ahead.get();
-        if (st == CG_OK && !takes_row_plan(h->plan))
-            h->row_plan = Plan{};
-        else if (st == CG_OK && !planned)
-            by_rows();
+            st = build_plans(format, n, p0, i0, h->plan, h->row_plan, h->err);
         h->mixed = (flags & CG_MIXED) != 0;
         if (st == CG_OK) {
             hipError_t e = hipGetDevice(&h->device);
@@ -1239,6 +1296,7 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
     hipStream_t s = h->stream;
     int st;
     hipError_t e;
+    h->report = cg_solve_report{};
     // initialisation (b and x0 in the device row order)
     const double *bi = vec_into(h, m, b, h->bp);
     auto start = [&] {
@@ -1256,10 +1314,13 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
         if ((st = run_resident(h, bi, x)) != CG_OK)
             return done(st);
         solved = h->host_st[0].status != kRun;
+        h->report.path = solved ? CG_PATH_RESIDENT : CG_PATH_REPEATED;
         if (!solved) // a wait ran out: launches from now on
             m.rs_wgs = 0;
     }
     if (!solved) {
+        if (h->report.path == CG_PATH_NONE)
+            h->report.path = CG_PATH_LAUNCHES;
         if ((st = build_graph(h)) != CG_OK)
             return done(st);
         e = start();
@@ -1315,6 +1376,8 @@ int cg_solve_mixed(cg_handle *h, const double *b, double *x, double tol, int32_t
         return done(CG_ERR_ARG);
     }
     hipStream_t s = h->stream;
+    h->report = cg_solve_report{};
+    h->report.path = CG_PATH_LAUNCHES;
     int st = build_graph_generic(h, true);
     if (st != CG_OK)
         return done(st);
@@ -1422,6 +1485,15 @@ int cg_pattern_grad(cg_handle *h, const double *lam, const double *x, double *gr
     }
     launch_pattern_grad(h->dm, lam, x, h->perm, grad, h->stream);
     HIP_TRY(h, hipGetLastError());
+    return CG_OK;
+}
+
+int cg_get_solve_report(const cg_handle *h, cg_solve_report *report)
+{
+    if (!h || !report)
+        return CG_ERR_ARG;
+    *report = h->report;
+    report->resident_wgs = (h->rows_solve ? h->rows : h->dm).rs_wgs;
     return CG_OK;
 }
 
