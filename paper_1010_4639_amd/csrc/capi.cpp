@@ -6,8 +6,9 @@
 // planned and has a place (run_resident), else from a HIP graph holding `batch`
 // iterations (product + fused p'q, r update + fused r'r, x/p update).  All
 // scalars stay on the device; every kernel reads the device status at entry and
-// returns at once when the loop has stopped.  The x/p update tells the host the
-// iteration and whether the loop stops, in a word of pinned memory, so the next
+// returns at once when the loop has stopped.  The x/p update (with two kernels
+// an iteration: the r update) tells the host the iteration and whether the loop
+// stops, in a word of pinned memory, so the next
 // graph is launched shortly before the last one ends: the GPU never waits for
 // the host, and what runs past the stop costs only early returns.
 #include <hip/hip_runtime.h>
@@ -577,7 +578,7 @@ void enqueue_iteration(cg_handle *h, hipStream_t s, int parity)
         c.r = h->r;
         c.x = h->xw;
         launch_spmv(m, c.pold, h->q, h->sig, c, s);
-        launch_update_r(m, h->r, h->q, h->st, h->sig, h->rho, s, true, true);
+        launch_update_r(m, h->r, h->q, h->st, h->sig, h->rho, s, true, true, h->word);
         return;
     }
     launch_spmv(m, h->p, h->q, h->sig, c, s);
@@ -640,8 +641,6 @@ int build_graph_generic(cg_handle *h, bool mixed)
         else
             enqueue_iteration(h, h->capture, i & 1);
     }
-    if (fused)
-        launch_progress(h->st, h->word, h->capture);
     hipError_t e = hipStreamEndCapture(h->capture, &g);
     if (e != hipSuccess)
         return hip_fail(h->err, e, "hipStreamEndCapture");

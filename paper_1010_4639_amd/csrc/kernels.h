@@ -201,9 +201,11 @@ void launch_resident(const DevMatrix &m, const ResidentArgs &a, bool first, hipS
 void launch_copy_out(const DevMatrix &m, const DevState *st, const double *xw, double *x, hipStream_t s);
 // r -= alpha q with alpha = rho / sum(sig_part); rho_part <- partials of r'r.
 // rows_deferred: q came from a product launched with defer_rows, so each
-// q_i is finished here from the parked slot sums first.
+// q_i is finished here from the parked slot sums first.  fused: the r update of
+// the two-kernel iteration, which reports to `word`.
 void launch_update_r(const DevMatrix &m, double *r, const double *q, DevState *st, const double *sig_part,
-                     double *rho_part, hipStream_t s, bool rows_deferred = false, bool fused = false);
+                     double *rho_part, hipStream_t s, bool rows_deferred = false, bool fused = false,
+                     unsigned long long *word = nullptr);
 // x += alpha p; p = r + beta p (unless converged) with beta = sum(rho_part) / rho.
 void launch_update_xp(const DevMatrix &m, double *x, double *p, const double *r, DevState *st,
                       const double *rho_part, unsigned long long *word, hipStream_t s);
@@ -222,7 +224,6 @@ void launch_outer_norm(const DevMatrix &m, DevState *st, const double *rho_part,
                        hipStream_t s);
 // convergence / maxit test of the current residual (one workgroup).
 void launch_check(DevState *st, const Report &rep, uint32_t tick, hipStream_t s);
-void launch_progress(const DevState *st, unsigned long long *word, hipStream_t s);
 // r = b - q, p = r, xw = x0; partials of r'r and b'b.
 void launch_init_vec(const DevMatrix &m, const double *b, const double *x0, const double *q, double *r, double *p,
                      double *xw, double *rho_part, double *bb_part, hipStream_t s);

@@ -1269,10 +1269,18 @@ __device__ __forceinline__ void row_values(const double *__restrict__ q, const d
     }
 }
 
+// One thread's reports to the host (Report): progress alone, in one store that
+// nothing waits for; or the state and then the word.
+__device__ __forceinline__ void report_word(unsigned long long *word, uint32_t tick, uint32_t payload)
+{
+    __hip_atomic_store(word, ((unsigned long long)tick << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // PPT: dot partials per thread (n_sig <= PPT * 256).  FUSED: the r update
 // of the two-kernel iteration: r'r of the current residual is the one the
-// product published (rho_next), and a stop the product decided (conv_next)
-// is recorded here.
+// product published (rho_next), a stop the product decided (conv_next) is
+// recorded here, and each iteration reported to the host, which then launches
+// the next graph before this one ends.
 // KP: elements per thread loaded up front (the chunk's, up to 8 x 256;
 // registers sized to the chunk, so small chunks keep more waves resident).
 // through: r written through (store_through); the launch decides.
@@ -1280,7 +1288,8 @@ template <int GATHER, int PPT, bool FUSED, int KP>
 __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *__restrict__ r,
                                                      const double *__restrict__ q, DevState *st,
                                                      const double *__restrict__ sig_part, int n_sig,
-                                                     double *__restrict__ rho_part, RowPass g, bool through)
+                                                     double *__restrict__ rho_part, RowPass g, bool through,
+                                                     unsigned long long *word)
 {
     __shared__ double red[kWaves];
     // the gate, the partials and the first vector elements are loaded
@@ -1295,14 +1304,18 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *_
     partials_load(sig_part, n_sig, pv);
     double qv[KP], rv[KP];
     row_values<GATHER, KP>(q, r, g, n, i0 + t, i1, qv, rv);
-    if (status != kRun)
-        return;
     const bool lead = blockIdx.x == 0 && t == 0;
+    if (status != kRun) {
+        if (FUSED && lead)
+            report_word(word, st->tick + (uint32_t)st->k, 1);
+        return;
+    }
     if (FUSED && stop != 0) {
         if (lead) {
             st->rho = rho;
             st->iters = st->k;
             st->status = stop == 1 ? kConverged : kMaxit;
+            report_word(word, st->tick + (uint32_t)st->k, 1);
         }
         return;
     }
@@ -1314,6 +1327,8 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *_
             st->iters = st->k;
             st->sigma = sigma;
             st->status = kBreakdown;
+            if (FUSED)
+                report_word(word, st->tick + (uint32_t)st->k, 1);
         }
         return;
     }
@@ -1321,9 +1336,12 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *_
     if (lead) {
         st->alpha = alpha;
         st->sigma = sigma;
-        st->k = st->k + 1;
-        if (FUSED)
+        const int k = st->k + 1;
+        st->k = k;
+        if (FUSED) {
             st->rho = rho; // r'r of the residual this step starts from (the next beta's denominator)
+            report_word(word, st->tick + (uint32_t)k, 0);
+        }
     }
     double acc = 0.0;
 #pragma unroll
@@ -1346,13 +1364,6 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, double *_
     acc = block_sum(acc, red);
     if (t == 0)
         rho_part[blk] = acc;
-}
-
-// One thread's reports to the host (Report): progress alone, in one store that
-// nothing waits for; or the state and then the word.
-__device__ __forceinline__ void report_word(unsigned long long *word, uint32_t tick, uint32_t payload)
-{
-    __hip_atomic_store(word, ((unsigned long long)tick << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __device__ void report_state(const DevState *st, const Report &rep, uint32_t tick)
@@ -1489,12 +1500,6 @@ __global__ void k_check(DevState *st, Report rep, uint32_t tick)
 {
     iter_gate(st);
     report_state(st, rep, tick);
-}
-
-// Progress of the fused iteration, whose r update records its stops itself.
-__global__ void k_progress(const DevState *st, unsigned long long *word)
-{
-    report_word(word, st->tick + (uint32_t)st->k, st->status != kRun ? 1 : 0);
 }
 
 __global__ __launch_bounds__(kBlock) void k_init_vec(int n, int chunk, const double *__restrict__ b,
@@ -1976,7 +1981,7 @@ static int prefetch_depth(int chunk)
 }
 
 void launch_update_r(const DevMatrix &m, double *r, const double *q, DevState *st, const double *sig_part,
-                     double *rho_part, hipStream_t s, bool rows_deferred, bool fused)
+                     double *rho_part, hipStream_t s, bool rows_deferred, bool fused, unsigned long long *word)
 {
     static_assert(kMaxSliceWgs <= 4 * kPartPerThread * kBlock, "slice partials fit four times the registers");
     // slices: up to kMaxSliceWgs dot partials (one slice per wavefront); the
@@ -2002,7 +2007,7 @@ void launch_update_r(const DevMatrix &m, double *r, const double *q, DevState *s
     const int kp = prefetch_depth(m.vec_chunk);
 #define CGMI_UPDATE_R_KP(G, P, F, K)                                                                         \
     hipLaunchKernelGGL((k_update_r<G, P, F, K>), grid, blk, 0, s, m.n, m.vec_chunk, r, q, st, sig_part, nsig,   \
-                       rho_part, g, through)
+                       rho_part, g, through, word)
 #define CGMI_UPDATE_R(G, P, F)                                                                               \
     do {                                                                                                     \
         switch (kp) {                                                                                        \
@@ -2107,11 +2112,6 @@ void launch_outer_norm(const DevMatrix &m, DevState *st, const double *rho_part,
 void launch_check(DevState *st, const Report &rep, uint32_t tick, hipStream_t s)
 {
     hipLaunchKernelGGL(k_check, dim3(1), dim3(1), 0, s, st, rep, tick);
-}
-
-void launch_progress(const DevState *st, unsigned long long *word, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_progress, dim3(1), dim3(1), 0, s, st, word);
 }
 
 void launch_init_vec(const DevMatrix &m, const double *b, const double *x0, const double *q, double *r, double *p,
