@@ -361,8 +361,11 @@ void cg_destroy(cg_handle *h);
 enum {
     CG_PATH_NONE = 0,     /* no solve yet */
     CG_PATH_RESIDENT = 1, /* one kernel for the whole solve */
-    CG_PATH_LAUNCHES = 2, /* graphs of launches: no resident kernel is planned, or it found no place */
-    CG_PATH_REPEATED = 3  /* a wait of the resident kernel ran out: the solve was repeated by launches */
+    CG_PATH_LAUNCHES = 2, /* graphs of launches: no resident kernel is planned, it found no place, or
+                             one gave up a short time ago */
+    CG_PATH_REPEATED = 3  /* a wait of the resident kernel ran out (0.25 s: other work held its compute
+                             units): the solve was repeated by launches, and so are the handle's solves
+                             for 100 times the time that was lost; then it is tried again */
 };
 typedef struct {
     int32_t path;         /* CG_PATH_* */

@@ -81,6 +81,7 @@ struct cg_handle {
     hipGraphExec_t gexec32 = nullptr;
     int graph32_batch = 0, graph32_iters = 0;
     cg_solve_report report{}; // of the last solve
+    std::chrono::steady_clock::time_point resident_from{}; // no resident solve is tried before
     // caller entry order -> normalised order (lower-triangle input), device copy
     int32_t *perm = nullptr;
     int32_t *flag = nullptr; // device word for checks made by kernels
@@ -723,6 +724,12 @@ public:
     explicit operator bool() const { return count_ != nullptr; }
 };
 
+// After a wait of a resident solve that ran out -- another process or a long
+// kernel held its compute units -- solves take the launches for this many times
+// the time that was lost, then try again: such attempts stay below 1 % of the
+// time, however long the others keep the device.
+constexpr int kResidentPause = 100;
+
 // Iterations of one resident launch: bounds the time a kernel runs (a few
 // milliseconds); the next launch goes on from the vectors it left.
 constexpr int kResidentIters = 1024;
@@ -1307,15 +1314,18 @@ int cg_solve(cg_handle *h, const double *b, double *x, double tol, int32_t maxit
     };
     bool solved = false;
     // the whole iteration in one kernel where it is planned and has a place
-    if (const ResidentPlace place{h->device, m.rs_wgs, h->cus}) {
+    const bool due = std::chrono::steady_clock::now() >= h->resident_from;
+    if (const ResidentPlace place{h->device, due ? m.rs_wgs : 0, h->cus}) {
         if ((e = start()) != hipSuccess)
             return done(hip_fail(h->err, e, "launch"));
         if ((st = run_resident(h, bi, x)) != CG_OK)
             return done(st);
         solved = h->host_st[0].status != kRun;
         h->report.path = solved ? CG_PATH_RESIDENT : CG_PATH_REPEATED;
-        if (!solved) // a wait ran out: launches from now on
-            m.rs_wgs = 0;
+        if (!solved) { // a wait ran out: launches, for a while
+            const auto now = std::chrono::steady_clock::now();
+            h->resident_from = now + kResidentPause * (now - t0);
+        }
     }
     if (!solved) {
         if (h->report.path == CG_PATH_NONE)

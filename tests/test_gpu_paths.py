@@ -87,3 +87,28 @@ def test_two_solves_share_the_device():
     assert set(paths[0] + paths[1]) <= {RESIDENT, LAUNCHES}
     assert RESIDENT in paths[0] + paths[1]
     assert np.all([len(p) == 20 for p in paths.values()])
+
+
+def test_resident_again_after_a_wait_that_ran_out(monkeypatch):
+    """One missed wait costs some solves by launches, not the handle's life; and
+    while waits go on running out, most solves do not try."""
+    import time  # (a repeated solve loses some 0.1 ms, so the solves are kept shorter than the pause after it)
+    s = W.fem_p1_system(16, 15, 14, seed=8)
+    b = to_dev(s.b)
+    with cgmi.Solver("csr", s.rowptr, s.col, s.val) as S:
+        ref = S.solve(b, tol=1e-10, maxit=20)
+        assert S.report()["path"] == RESIDENT
+        monkeypatch.setenv("CGMI_RESIDENT_WAIT", "-1")
+        paths = []
+        for _ in range(50):
+            x, info = S.solve(b, tol=1e-10, maxit=20)
+            paths.append(S.report()["path"])
+        say(f"paths while waits run out: {paths}")
+        assert paths[0] == REPEATED and set(paths) == {REPEATED, LAUNCHES}
+        assert paths.count(REPEATED) <= len(paths) // 2
+        monkeypatch.delenv("CGMI_RESIDENT_WAIT")
+        end = time.monotonic() + 30
+        while S.report()["path"] != RESIDENT and time.monotonic() < end:
+            x, info = S.solve(b, tol=1e-10, maxit=20)
+        assert S.report()["path"] == RESIDENT
+        assert np.array_equal(x.cpu().numpy(), ref[0].cpu().numpy()) and info["iters"] == ref[1]["iters"]
