@@ -173,6 +173,8 @@ int upload_slices(cg_handle *h, const Plan &p, DevMatrix &m, bool val32)
     m.sl_d16 = d16;
     m.sl_src = src;
     m.sl_val = sv;
+    if ((p.rs_wgs > 0 || &p == &h->row_plan) && choice_fails("device"))
+        return CG_ERR_NOMEM;
     if (p.rs_wgs > 0) {
         int32_t *gp, *gc;
         uint16_t *lc, *lo;
@@ -865,6 +867,22 @@ int drop_entry_values(cg_handle *h)
     return CG_OK;
 }
 
+// The device side of a planned handle.
+int fill_handle(cg_handle *h, const std::vector<int32_t> &p0, const std::vector<int32_t> &i0, const double *vals,
+                const std::vector<int32_t> &perm)
+{
+    int st = upload_all(h, p0, i0, vals);
+    if (st == CG_OK && !perm.empty())
+        st = upload(h, &h->perm, perm.data(), perm.size());
+    if (st == CG_OK)
+        st = dalloc(h, &h->flag, 1);
+    if (st == CG_OK)
+        st = refresh_values(h, h->dm.val, nullptr);
+    if (st == CG_OK)
+        st = drop_entry_values(h);
+    return st;
+}
+
 // Scratch of cg_spmv_static (dot partials and parked sums of one product):
 // a fixed array in device memory, one copy on every GPU the library runs on,
 // held until the process ends.  Host code never uses the name itself as an
@@ -919,12 +937,22 @@ hipError_t vec_out_of(cg_handle *h, const DevMatrix &m, const double *src, doubl
 }
 
 // The plans of a handle: the storage format's, and the second one by rows
-// (row_plan.n = 0: none), side by side where that pays (plan.h).
+// (row_plan.n = 0: none, or no host memory for it), side by side where that
+// pays (plan.h).
 int build_plans(int format, int64_t n, const std::vector<int32_t> &p0, const std::vector<int32_t> &i0, Plan &plan,
                 Plan &row_plan, std::string &err)
 {
     std::future<bool> ahead; // (joined by its destructor where a step below throws)
-    const auto by_rows = [&] { return build_row_plan(format, n, p0.data(), i0.data(), row_plan); };
+    const auto by_rows = [&] {
+        try {
+            if (choice_fails("host"))
+                throw std::bad_alloc();
+            return build_row_plan(format, n, p0.data(), i0.data(), row_plan);
+        } catch (const std::bad_alloc &) {
+            row_plan = Plan{};
+            return false;
+        }
+    };
     if (n > 0 && row_plan_ahead(format, n, p0[n])) {
         try {
             ahead = std::async(std::launch::async, by_rows);
@@ -1174,16 +1202,20 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
             hipError_t e = hipGetDevice(&h->device);
             if (e == hipSuccess)
                 e = hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device);
-            st = e == hipSuccess ? upload_all(h.get(), p0, i0, vals) : hip_fail(h->err, e, "hipGetDevice");
+            st = e == hipSuccess ? fill_handle(h.get(), p0, i0, vals, perm) : hip_fail(h->err, e, "hipGetDevice");
         }
-        if (st == CG_OK && !perm.empty())
-            st = upload(h.get(), &h->perm, perm.data(), perm.size());
-        if (st == CG_OK)
-            st = dalloc(h.get(), &h->flag, 1);
-        if (st == CG_OK)
-            st = refresh_values(h.get(), h->dm.val, nullptr);
-        if (st == CG_OK)
-            st = drop_entry_values(h.get());
+        if (st == CG_ERR_NOMEM && (h->row_plan.n > 0 || h->plan.rs_wgs > 0)) { // without what is a choice
+            (void)hipGetLastError();
+            release(h.get());
+            std::unique_ptr<cg_handle> less(new cg_handle());
+            less->plan = std::move(h->plan);
+            less->plan.rs_wgs = 0;
+            less->mixed = h->mixed;
+            less->device = h->device;
+            less->cus = h->cus;
+            h = std::move(less);
+            st = fill_handle(h.get(), p0, i0, vals, perm);
+        }
         if (st != CG_OK) {
             g_err = h->err;
             release(h.get());

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 
 #include "../../include/cgmi.h"
 
@@ -984,7 +985,7 @@ static bool plan_sym_compact(Plan &p, const int32_t *ptr, const int32_t *idx)
 // rows (n <= 262 144): a larger matrix does not fit the registers.  Lines and
 // column lists have to fit what the kernels hold.  Experiments:
 // CGMI_RESIDENT=0, never; CGMI_RESIDENT=256, the small form only.
-static void plan_resident(Plan &p, const int32_t *ptr, const int32_t *idx)
+static void plan_resident_rows(Plan &p, const int32_t *ptr, const int32_t *idx)
 {
     bool wide_allowed = true;
     if (const char *e = std::getenv("CGMI_RESIDENT")) {
@@ -1054,6 +1055,24 @@ static void plan_resident(Plan &p, const int32_t *ptr, const int32_t *idx)
     p.rs_gcol.swap(gcol);
     p.rs_lcol.swap(lcol);
     p.rs_lown.swap(lown);
+}
+
+bool choice_fails(const char *where)
+{
+    const char *e = std::getenv("CGMI_CHOICE_FAILS");
+    return e && std::strcmp(e, where) == 0;
+}
+
+// (without host memory for it: no resident solve)
+static void plan_resident(Plan &p, const int32_t *ptr, const int32_t *idx)
+{
+    try {
+        if (choice_fails("host"))
+            throw std::bad_alloc();
+        plan_resident_rows(p, ptr, idx);
+    } catch (const std::bad_alloc &) {
+        p.rs_wgs = 0;
+    }
 }
 
 // Full rows of a matrix given otherwise: columns ascending, and for each entry

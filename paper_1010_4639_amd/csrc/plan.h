@@ -255,7 +255,9 @@ int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int
 // ms; the bytes that the triangle saves do not matter in the caches).  Larger
 // solves keep the panels and the compact blocks.  build_row_plan's false: no
 // such layout (rows too ragged for slices; experiments: CGMI_SYM_EXPAND=0,
-// CGMI_ROW_LAYOUT=rows).  It needs the matrix only, so where the main plan is
+// CGMI_ROW_LAYOUT=rows).  Where the host or the device has no memory for it, or
+// for a resident solve, a handle does without (tests: CGMI_CHOICE_FAILS=host,
+// =device).  It needs the matrix only, so where the main plan is
 // likely to take it (row_plan_ahead) and holds enough entries to pay for a
 // thread, the two are planned side by side: create of a 100^3 CSC system
 // 197 -> 115 ms, of a 60^3 symmetric one 132 -> 118.
@@ -263,6 +265,7 @@ constexpr int64_t kRowsSolveMax = 262144;
 bool takes_row_plan(const Plan &plan);
 bool row_plan_ahead(int fmt, int64_t n, int64_t nnz);
 bool build_row_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, Plan &rows);
+bool choice_fails(const char *where);
 
 int lanes_for_mean_length(double mean_len);
 

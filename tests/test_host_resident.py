@@ -131,3 +131,12 @@ def test_errors():
     assert cgmi.cg_analyze_resident("csr", -1, *a)[0] == cgmi.CG_ERR_ARG
     assert cgmi.cg_analyze_resident("csr", 10, a[0], a[1][::-1].copy())[0] == cgmi.CG_ERR_STRUCTURE
     assert cgmi.cg_analyze_resident("csr", 0, np.zeros(1, np.int32), np.zeros(0, np.int32))[1]["wgs"] == 0
+
+
+def test_no_host_memory(monkeypatch):
+    s = W.fem_p1_system(43, 41, 40, seed=2, with_rhs=False)
+    up = W.upper_triangle(s.rowptr, s.col, s.val)[:2]
+    monkeypatch.setenv("CGMI_CHOICE_FAILS", "host")
+    for fmt, a in (("csr", (s.rowptr, s.col)), ("csc", (s.rowptr, s.col)), ("symcsr", up)):
+        st, p = cgmi.cg_analyze_resident(fmt, s.n, *a)
+        assert st == 0 and p["wgs"] == 0, fmt
