@@ -85,7 +85,15 @@ typedef struct {
     int32_t reserved;
 } cg_info;
 
-/* Plan summary (host-side description of how the product is executed). */
+/*
+ * Plan summary (host-side description of how the product is executed).
+ * cg_analyze describes the storage format's own plan.  A handle whose product
+ * runs on full rows laid out beside it (cg_spmv) says so in lanes_per_line,
+ * spmv_blocks, slices, cached_loads and plan_bytes; the fields of the
+ * format's blocks (scatter_blocks, max_block_entries, colors, compact, slots,
+ * parked) are then those that solves and refinements run on, and 0 where
+ * everything runs by rows.
+ */
 typedef struct {
     int64_t n;
     int64_t nnz;             /* stored entries */
@@ -344,7 +352,7 @@ void cg_fem_destroy(cg_fem *f);
  * failed cg_fem_create.  Never NULL. */
 const char *cg_fem_last_error(const cg_fem *f);
 
-/* Plan summary of a handle. */
+/* Plan summary of a handle (see cg_plan_stats). */
 int cg_get_stats(const cg_handle *h, cg_plan_stats *stats);
 
 /* Frees every device and host resource of the handle (NULL is a no-op).

@@ -549,6 +549,27 @@ void fill_stats(const Plan &p, cg_plan_stats *s)
     s->plan_bytes = p.device_bytes();
 }
 
+// The summary of a handle: its product's layout where that is the second one
+// by rows, and nothing of the storage format's own where it is not kept.
+void handle_stats(const cg_handle *h, cg_plan_stats *s)
+{
+    fill_stats(h->plan, s);
+    if (h->rows.n > 0) {
+        cg_plan_stats r;
+        fill_stats(h->row_plan, &r);
+        s->lanes_per_line = r.lanes_per_line;
+        s->spmv_blocks = r.spmv_blocks;
+        s->slices = r.slices;
+        s->cached_loads = r.cached_loads;
+        s->plan_bytes = r.plan_bytes;
+        if (h->lean) {
+            s->colors = s->scatter_blocks = s->max_block_entries = s->compact = 0;
+            s->slots = s->parked = 0;
+        }
+    }
+    s->device_bytes = (int64_t)h->dev_bytes;
+}
+
 // experiments: CGMI_MIXED_RESTART=1 restarts every inner solve from p = r
 // instead of keeping the previous inner solve's next direction
 bool restart_inner()
@@ -1542,8 +1563,7 @@ int cg_get_stats(const cg_handle *h, cg_plan_stats *stats)
 {
     if (!h || !stats)
         return CG_ERR_ARG;
-    fill_stats(h->plan, stats);
-    stats->device_bytes = (int64_t)h->dev_bytes;
+    handle_stats(h, stats);
     return CG_OK;
 }
 
