@@ -41,9 +41,13 @@ struct cg_handle {
     Plan plan;
     DevMatrix dm;
     // second layout by rows (plan.h: build_row_plan; rows.n = 0: none): lone
-    // products, and with rows_solve the iteration of cg_solve
+    // products, and with rows_solve the iteration of cg_solve.  Its plan is
+    // given back once it is on the device; what is read later: the summary and
+    // the number of positions.
     Plan row_plan;
     DevMatrix rows;
+    cg_plan_stats row_stats{};
+    int64_t row_positions = 0;
     bool rows_solve = false;
     // products and solves all run by rows: the storage format's own layout is
     // planned (its summary is the handle's) but not kept on the device
@@ -199,6 +203,26 @@ int upload_slices(cg_handle *h, const Plan &p, DevMatrix &m, bool val32)
     return CG_OK;
 }
 
+void fill_stats(const Plan &p, cg_plan_stats *s)
+{
+    std::memset(s, 0, sizeof(*s));
+    s->n = p.n;
+    s->nnz = p.nnz;
+    s->format = p.format;
+    s->lanes_per_line = p.lanes;
+    s->spmv_blocks = p.spmv_blocks();
+    s->scatter_blocks = p.nblocks;
+    s->vec_blocks = p.vec_blocks;
+    s->colors = p.ncolors;
+    s->max_block_entries = p.max_entries;
+    s->slices = !p.sl_d16.empty() ? 2 : p.slices || p.sym_slices || p.sym_compact ? 1 : 0;
+    s->compact = p.sym_compact ? 1 : 0;
+    s->parked = p.sym_compact ? p.cp_parked : 0;
+    s->cached_loads = p.matrix_cached() ? 1 : 0;
+    s->slots = p.panel ? (int64_t)p.pn_slot_target.size() : (int64_t)p.slot_target.size();
+    s->plan_bytes = p.device_bytes();
+}
+
 // The second layout by rows (plan.h): the fields that its products and its
 // iteration read.
 int upload_rows(cg_handle *h)
@@ -213,6 +237,8 @@ int upload_rows(cg_handle *h)
     m.vec_chunk = p.vec_chunk;
     m.matrix_cached = p.matrix_cached();
     h->rows_solve = p.rs_wgs > 0;
+    h->row_positions = (int64_t)p.sl_src.size();
+    fill_stats(p, &h->row_stats);
     return upload_slices(h, p, m, false);
 }
 
@@ -529,34 +555,13 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
     return CG_OK;
 }
 
-void fill_stats(const Plan &p, cg_plan_stats *s)
-{
-    std::memset(s, 0, sizeof(*s));
-    s->n = p.n;
-    s->nnz = p.nnz;
-    s->format = p.format;
-    s->lanes_per_line = p.lanes;
-    s->spmv_blocks = p.spmv_blocks();
-    s->scatter_blocks = p.nblocks;
-    s->vec_blocks = p.vec_blocks;
-    s->colors = p.ncolors;
-    s->max_block_entries = p.max_entries;
-    s->slices = !p.sl_d16.empty() ? 2 : p.slices || p.sym_slices || p.sym_compact ? 1 : 0;
-    s->compact = p.sym_compact ? 1 : 0;
-    s->parked = p.sym_compact ? p.cp_parked : 0;
-    s->cached_loads = p.matrix_cached() ? 1 : 0;
-    s->slots = p.panel ? (int64_t)p.pn_slot_target.size() : (int64_t)p.slot_target.size();
-    s->plan_bytes = p.device_bytes();
-}
-
 // The summary of a handle: its product's layout where that is the second one
 // by rows, and nothing of the storage format's own where it is not kept.
 void handle_stats(const cg_handle *h, cg_plan_stats *s)
 {
     fill_stats(h->plan, s);
     if (h->rows.n > 0) {
-        cg_plan_stats r;
-        fill_stats(h->row_plan, &r);
+        const cg_plan_stats &r = h->row_stats;
         s->lanes_per_line = r.lanes_per_line;
         s->spmv_blocks = r.spmv_blocks;
         s->slices = r.slices;
@@ -860,7 +865,7 @@ int refresh_values(cg_handle *h, const double *src, const int32_t *order)
     const int64_t nnz = h->plan.nnz, np = (int64_t)h->plan.sl_src.size();
     launch_fill_layout(m, nnz, np, src, order, h->stream);
     if (h->rows.n > 0)
-        launch_fill_layout(h->rows, 0, (int64_t)h->row_plan.sl_src.size(), src, order, h->stream);
+        launch_fill_layout(h->rows, 0, h->row_positions, src, order, h->stream);
     HIP_TRY(h, hipGetLastError());
     if (h->mixed && m.n > 0) {
         const int st = mixed_rescale(h);
@@ -1237,6 +1242,7 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
             h = std::move(less);
             st = fill_handle(h.get(), p0, i0, vals, perm);
         }
+        h->row_plan = Plan{};
         if (st != CG_OK) {
             g_err = h->err;
             release(h.get());
