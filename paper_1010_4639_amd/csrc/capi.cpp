@@ -19,12 +19,10 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <future>
 #include <memory>
 #include <mutex>
 #include <new>
 #include <string>
-#include <system_error>
 #include <vector>
 
 #include "../../include/cgmi.h"
@@ -49,8 +47,7 @@ struct cg_handle {
     cg_plan_stats row_stats{};
     int64_t row_positions = 0;
     bool rows_solve = false;
-    // products and solves all run by rows: the storage format's own layout is
-    // planned (its summary is the handle's) but not kept on the device
+    // products and solves all run by rows: `plan` is an outline (plan.h)
     bool lean = false;
     const DevMatrix &product() const { return rows.n > 0 ? rows : dm; }
     DevMatrix &solver() { return rows_solve ? rows : dm; }
@@ -180,23 +177,21 @@ int upload_slices(cg_handle *h, const Plan &p, DevMatrix &m, bool val32)
     if ((p.rs_wgs > 0 || &p == &h->row_plan) && choice_fails("device"))
         return CG_ERR_NOMEM;
     if (p.rs_wgs > 0) {
-        int32_t *gp, *gc;
-        uint16_t *lc, *lo;
-        if ((st = upload(h, &gp, p.rs_gptr.data(), p.rs_gptr.size())) != CG_OK ||
-            (st = upload(h, &gc, p.rs_gcol.data(), p.rs_gcol.size())) != CG_OK ||
-            (st = upload(h, &lc, p.rs_lcol.data(), p.rs_lcol.size())) != CG_OK ||
-            (st = upload(h, &lo, p.rs_lown.data(), p.rs_lown.size())) != CG_OK ||
-            (st = dalloc(h, &h->words, (size_t)resident_words(p.csr_blocks, p.vec_blocks, p.n))) != CG_OK)
+        // one allocation and one copy (a small handle is created in 0.4 ms)
+        const size_t nw = (size_t)resident_words(p.csr_blocks, p.vec_blocks, p.n), bytes = p.rs_data.size() * 4;
+        if ((st = dalloc(h, &h->words, nw + (bytes + 7) / 8)) != CG_OK)
             return st;
+        int32_t *dev = reinterpret_cast<int32_t *>(h->words + nw);
+        HIP_TRY(h, hipMemcpy(dev, p.rs_data.data(), bytes, hipMemcpyHostToDevice));
         m.rs_wgs = p.rs_wgs;
         m.rs_threads = p.rs_threads;
         m.rs_slices = p.rs_slices;
         m.rs_width = p.rs_width;
         m.rs_cols = p.rs_cols;
-        m.rs_gptr = gp;
-        m.rs_gcol = gc;
-        m.rs_lcol = lc;
-        m.rs_lown = lo;
+        m.rs_lcol = reinterpret_cast<const uint16_t *>(dev);
+        m.rs_lown = m.rs_lcol + p.sl_src.size();
+        m.rs_gptr = dev + p.rs_first();
+        m.rs_gcol = m.rs_gptr + p.rs_wgs + 1;
     }
     if (val32 && (st = dalloc(h, &m.sl_val32, std::max<size_t>(p.sl_src.size(), 1))) != CG_OK)
         return st;
@@ -530,10 +525,18 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
     if (h->fused && (st = dalloc(h, &h->p2, nv)) != CG_OK)
         return st;
     const size_t ns = (size_t)std::max({1, p.spmv_blocks(), p.vec_blocks, h->rows.csr_blocks});
-    if ((st = dalloc(h, &h->sig, ns)) != CG_OK || (st = dalloc(h, &h->sig_spmv, ns)) != CG_OK ||
-        (st = dalloc(h, &h->rho, ns)) != CG_OK || (st = dalloc(h, &h->bb, ns)) != CG_OK ||
-        (st = dalloc(h, &h->st, 1)) != CG_OK)
+    static_assert(sizeof(DevState) <= 4096, "a page");
+    // the partials, the state and the flag in one allocation, a page each at least
+    const size_t page = 4096 / sizeof(double), part = (ns + page - 1) / page * page;
+    double *small;
+    if ((st = dalloc(h, &small, 4 * part + 2 * page)) != CG_OK)
         return st;
+    h->sig = small;
+    h->sig_spmv = small + part;
+    h->rho = small + 2 * part;
+    h->bb = small + 3 * part;
+    h->st = reinterpret_cast<DevState *>(small + 4 * part);
+    h->flag = reinterpret_cast<int32_t *>(small + 4 * part + page);
     if (h->mixed && n > 0) {
         // FP32 copy of D^-1/2 A D^-1/2 and D^-1/2 itself: filled by mixed_rescale
         float *dv32;
@@ -878,11 +881,13 @@ int refresh_values(cg_handle *h, const double *src, const int32_t *order)
 }
 
 // After creation: the values in entry order are given back where nothing
-// reads them again (waits for the work that still does).
+// reads them again (waits for the work that still does).  A few megabytes are
+// not worth the wait and the call (40 to 140 us of a create of 0.4 to 6 ms).
+constexpr size_t kKeepBytes = 16u << 20;
 int drop_entry_values(cg_handle *h)
 {
     DevMatrix &m = h->dm;
-    if (m.n == 0 || (m.keeps_val() && !h->lean))
+    if (m.n == 0 || (m.keeps_val() && !h->lean) || (size_t)h->plan.nnz * sizeof(double) <= kKeepBytes)
         return CG_OK;
     void *p = const_cast<double *>(m.val);
     HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -900,8 +905,6 @@ int fill_handle(cg_handle *h, const std::vector<int32_t> &p0, const std::vector<
     int st = upload_all(h, p0, i0, vals);
     if (st == CG_OK && !perm.empty())
         st = upload(h, &h->perm, perm.data(), perm.size());
-    if (st == CG_OK)
-        st = dalloc(h, &h->flag, 1);
     if (st == CG_OK)
         st = refresh_values(h, h->dm.val, nullptr);
     if (st == CG_OK)
@@ -960,40 +963,6 @@ hipError_t vec_out_of(cg_handle *h, const DevMatrix &m, const double *src, doubl
         return hipMemcpyAsync(dst, src, sizeof(double) * (size_t)m.n, hipMemcpyDeviceToDevice, h->stream);
     launch_permute(m.n, src, m.vinv, dst, h->stream);
     return hipGetLastError();
-}
-
-// The plans of a handle: the storage format's, and the second one by rows
-// (row_plan.n = 0: none, or no host memory for it), side by side where that
-// pays (plan.h).
-int build_plans(int format, int64_t n, const std::vector<int32_t> &p0, const std::vector<int32_t> &i0, Plan &plan,
-                Plan &row_plan, std::string &err)
-{
-    std::future<bool> ahead; // (joined by its destructor where a step below throws)
-    const auto by_rows = [&] {
-        try {
-            if (choice_fails("host"))
-                throw std::bad_alloc();
-            return build_row_plan(format, n, p0.data(), i0.data(), row_plan);
-        } catch (const std::bad_alloc &) {
-            row_plan = Plan{};
-            return false;
-        }
-    };
-    if (n > 0 && row_plan_ahead(format, n, p0[n])) {
-        try {
-            ahead = std::async(std::launch::async, by_rows);
-        } catch (const std::system_error &) { // no thread: planned below
-        }
-    }
-    const int st = build_plan(format, n, p0.data(), i0.data(), scatter_entries_override(), plan, err);
-    const bool planned = ahead.valid();
-    if (planned)
-        ahead.get();
-    if (st != CG_OK || !takes_row_plan(plan))
-        row_plan = Plan{};
-    else if (!planned)
-        by_rows();
-    return st;
 }
 
 int status_to_code(int32_t s)
@@ -1164,7 +1133,7 @@ int cg_analyze_resident(int format, int64_t n, const int32_t *ptr, const int32_t
         st = validate_and_normalise(format, n, ptr, idx, nullptr, index_base, 0, p0, i0, err);
         Plan main, rows;
         if (st == CG_OK)
-            st = build_plans(format, n, p0, i0, main, rows, err);
+            st = build_plans(format, n, p0.data(), i0.data(), scatter_entries_override(), false, main, rows, err);
         if (st == CG_OK) {
             const Plan &p = rows.rs_wgs > 0 ? rows : main;
             cg_resident_plan r{};
@@ -1178,13 +1147,14 @@ int cg_analyze_resident(int format, int64_t n, const int32_t *ptr, const int32_t
                 r.product_wgs = p.csr_blocks;
                 r.vec_wgs = p.vec_blocks;
                 r.vec_chunk = p.vec_chunk;
-                r.columns = (int64_t)p.rs_gcol.size();
-                r.positions = (int64_t)p.rs_lcol.size();
+                const int32_t *first = p.rs_data.data() + p.rs_first();
+                r.columns = first[r.wgs];
+                r.positions = (int64_t)p.sl_src.size();
                 if (slice_off) std::memcpy(slice_off, p.sl_off.data(), p.sl_off.size() * 4);
-                if (col_ptr) std::memcpy(col_ptr, p.rs_gptr.data(), p.rs_gptr.size() * 4);
-                if (col) std::memcpy(col, p.rs_gcol.data(), p.rs_gcol.size() * 4);
-                if (entry) std::memcpy(entry, p.rs_lcol.data(), p.rs_lcol.size() * 2);
-                if (own) std::memcpy(own, p.rs_lown.data(), p.rs_lown.size() * 2);
+                if (col_ptr) std::memcpy(col_ptr, first, ((size_t)r.wgs + 1) * 4);
+                if (col) std::memcpy(col, first + r.wgs + 1, (size_t)r.columns * 4);
+                if (entry) std::memcpy(entry, p.rs_entry(), (size_t)r.positions * 2);
+                if (own) std::memcpy(own, p.rs_own(), (size_t)n * 2);
             }
             if (plan)
                 *plan = r;
@@ -1221,9 +1191,10 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
                 pvals[k] = vals[perm[k]];
             vals = pvals.data();
         }
-        if (st == CG_OK)
-            st = build_plans(format, n, p0, i0, h->plan, h->row_plan, h->err);
         h->mixed = (flags & CG_MIXED) != 0;
+        if (st == CG_OK)
+            st = build_plans(format, n, p0.data(), i0.data(), scatter_entries_override(), h->mixed, h->plan,
+                             h->row_plan, h->err);
         if (st == CG_OK) {
             hipError_t e = hipGetDevice(&h->device);
             if (e == hipSuccess)
@@ -1234,13 +1205,18 @@ int cg_create(cg_handle **out, int format, int64_t n, const int32_t *ptr, const 
             (void)hipGetLastError();
             release(h.get());
             std::unique_ptr<cg_handle> less(new cg_handle());
-            less->plan = std::move(h->plan);
-            less->plan.rs_wgs = 0;
             less->mixed = h->mixed;
             less->device = h->device;
             less->cus = h->cus;
+            if (h->lean) // (an outline)
+                st = build_plan(format, n, p0.data(), i0.data(), scatter_entries_override(), less->plan, less->err);
+            else
+                less->plan = std::move(h->plan);
+            less->plan.rs_wgs = 0;
+            const bool planned = !h->lean || st == CG_OK;
             h = std::move(less);
-            st = fill_handle(h.get(), p0, i0, vals, perm);
+            if (planned)
+                st = fill_handle(h.get(), p0, i0, vals, perm);
         }
         h->row_plan = Plan{};
         if (st != CG_OK) {

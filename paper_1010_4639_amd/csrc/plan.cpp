@@ -2,10 +2,14 @@
 #include "plan.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <future>
 #include <new>
+#include <system_error>
+#include <vector>
 
 #include "../../include/cgmi.h"
 
@@ -64,6 +68,21 @@ int lanes_for_mean_length(double mean_len)
     while (w < 64 && w < mean_len)
         w *= 2;
     return w;
+}
+
+// No exponent of all ones, which one more would carry into the sign (no branch
+// a value: 0.3 ns instead of 1, of some 4 ns that an entry's validation and
+// planning take).
+static bool all_finite(const double *v, int64_t m)
+{
+    constexpr uint64_t one = 1ull << 52, mask = 0x7ffull << 52;
+    uint64_t carry = 0;
+    for (int64_t k = 0; k < m; ++k) {
+        uint64_t u;
+        std::memcpy(&u, v + k, sizeof(u));
+        carry |= (u & mask) + one;
+    }
+    return (carry >> 63) == 0;
 }
 
 int validate_and_normalise(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx, const double *vals,
@@ -136,13 +155,12 @@ int validate_and_normalise(int fmt, int64_t n, const int32_t *ptr, const int32_t
             return CG_ERR_STRUCTURE;
         }
     }
-    if (vals) {
+    if (vals && !all_finite(vals, nnz))
         for (int64_t k = 0; k < nnz; ++k)
             if (!std::isfinite(vals[k])) {
                 err = "non-finite value at entry " + std::to_string(k);
                 return CG_ERR_NONFINITE;
             }
-    }
     if (fmt == kSymCsr && (flags & CG_LOWER)) {
         // lower triangle by rows == upper triangle by columns: transpose the
         // structure (stable counting sort) into the upper-by-rows layout;
@@ -221,6 +239,31 @@ static void plan_vectors(Plan &p)
     p.vec_chunk = (int)((n + g - 1) / g);
 }
 
+// part(t) for t in [0, parts), side by side where threads can be had: 65 536
+// entries or more each (create of a 30 720-row system 1.65 ms; with 131 072 1.7,
+// with 262 144, one thread, 2.0).
+static int64_t parts_for(int64_t nnz)
+{
+    return std::max<int64_t>(1, std::min<int64_t>(8, nnz / 65536));
+}
+
+template <class F>
+static void side_by_side(int64_t parts, const F &part)
+{
+    std::vector<std::future<void>> ahead; // (joined by their destructors where a part throws)
+    ahead.reserve((size_t)parts);
+    int64_t t = parts - 1;
+    try {
+        for (; t >= 1; --t)
+            ahead.push_back(std::async(std::launch::async, [&part, t] { part(t); }));
+    } catch (const std::system_error &) { // no thread: these parts here
+    }
+    for (; t >= 0; --t)
+        part(t);
+    for (auto &f : ahead)
+        f.get();
+}
+
 // Whether 16-bit offsets hold the columns of the slices (plan.h): each within
 // 32767 of the row its line adds to (line_row: the row of each line; null: the
 // line itself, CSR).  Columns ascend along a line, so its ends decide.
@@ -273,18 +316,21 @@ static bool plan_slices(Plan &p, int64_t nl, const int32_t *seg_ptr, const int32
         p.sl_d16.assign((size_t)padded, kPad16);
     else
         p.sl_col.assign((size_t)padded, -1);
-    for (int64_t r = 0; r < nl; ++r) {
-        const int64_t sl = r / kSliceRows, lane = r % kSliceRows;
-        const int64_t w = (off[sl + 1] - off[sl]) / kSliceRows, row = line_row ? line_row[r] : r;
-        for (int64_t k = seg_ptr[r]; k < seg_ptr[r + 1]; ++k) {
-            const int64_t q = off[sl] + slice_position(k - seg_ptr[r], lane, w);
-            p.sl_src[q] = seg_src ? seg_src[k] : (int32_t)k;
-            if (banded)
-                p.sl_d16[q] = (int16_t)(seg_col[k] - row);
-            else
-                p.sl_col[q] = seg_col[k];
+    const int64_t parts = parts_for(nnz);
+    side_by_side(parts, [&](int64_t t) {
+        for (int64_t r = t * nl / parts; r < (t + 1) * nl / parts; ++r) {
+            const int64_t sl = r / kSliceRows, lane = r % kSliceRows;
+            const int64_t w = (off[sl + 1] - off[sl]) / kSliceRows, row = line_row ? line_row[r] : r;
+            for (int64_t k = seg_ptr[r]; k < seg_ptr[r + 1]; ++k) {
+                const int64_t q = off[sl] + slice_position(k - seg_ptr[r], lane, w);
+                p.sl_src[q] = seg_src ? seg_src[k] : (int32_t)k;
+                if (banded)
+                    p.sl_d16[q] = (int16_t)(seg_col[k] - row);
+                else
+                    p.sl_col[q] = seg_col[k];
+            }
         }
-    }
+    });
     // one slice per wavefront up to kMaxSliceWgs workgroups, then each wave
     // takes several (contiguous per workgroup)
     const int64_t g = (ns + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -346,20 +392,28 @@ static void plan_csr(Plan &p, const int32_t *ptr, const int32_t *idx)
     p.csr_rows_per_block = (int)((n + g - 1) / g);
 }
 
-// CSC column panels (see plan.h).
-static int plan_panels(Plan &p, const int32_t *ptr, const int32_t *idx, std::string &err)
+// Columns of a CSC panel; bw: the largest |i - j| of an entry (rows ascend
+// along a column, so its ends decide).
+static int64_t panel_width(int64_t n, const int32_t *ptr, const int32_t *idx, int64_t &bw)
 {
-    const int64_t n = p.n, nnz = p.nnz;
-    int64_t bw = 0;
+    bw = 0;
     for (int64_t j = 0; j < n; ++j)
-        for (int64_t k = ptr[j]; k < ptr[j + 1]; ++k)
-            bw = std::max<int64_t>(bw, std::llabs((int64_t)idx[k] - j));
+        if (ptr[j] < ptr[j + 1])
+            bw = std::max<int64_t>({bw, std::llabs((int64_t)idx[ptr[j]] - j), std::llabs((int64_t)idx[ptr[j + 1] - 1] - j)});
     int64_t W = std::max<int64_t>(2 * bw + 1, kPanelMinWidth);
     // experiments: a wider panel (never narrower than 2 bw + 1, which the
     // two-colour guarantee needs); at n the product is one row-ordered panel
     if (const char *e = std::getenv("CGMI_PANEL_WIDTH"))
         W = std::max<int64_t>(W, std::atoll(e));
-    W = std::min<int64_t>(n, W);
+    return std::min<int64_t>(n, W);
+}
+
+// CSC column panels (see plan.h).
+static int plan_panels(Plan &p, const int32_t *ptr, const int32_t *idx, std::string &err)
+{
+    const int64_t n = p.n, nnz = p.nnz;
+    int64_t bw;
+    const int64_t W = panel_width(n, ptr, idx, bw);
     const int64_t np = (n + W - 1) / W;
     p.panel = true;
     p.pn_width = W;
@@ -906,10 +960,6 @@ static bool plan_sym_compact(Plan &p, const int32_t *ptr, const int32_t *idx)
                     contrib.push_back({local[idx[k]], q});
             }
         }
-        std::stable_sort(contrib.begin(), contrib.end(),
-                         [](const std::pair<int32_t, int32_t> &a, const std::pair<int32_t, int32_t> &c) {
-                             return a.first < c.first;
-                         });
         CompactBlock &cb = p.cp_blocks[b];
         cb.pos0 = (int32_t)pos;
         cb.len = len;
@@ -934,9 +984,10 @@ static bool plan_sym_compact(Plan &p, const int32_t *ptr, const int32_t *idx)
             p.seg.push_back(0);
         for (int32_t s = 0; s < ns; ++s)
             p.slot_count.push_back(cs[s + 1] - cs[s]);
-        for (size_t r = 0; r < contrib.size(); ++r) { // LDS place = rank in the slot-grouped order
-            const int32_t q = contrib[r].second, t = q % nl, k = q / nl;
-            p.cp_rank[(size_t)(l0 + t) * kStreamPerThread + k] = (uint16_t)r;
+        // (cs: next place of each slot from here on)
+        for (const auto &c : contrib) { // LDS place = rank in the slot-grouped order
+            const int32_t q = c.second, t = q % nl, k = q / nl;
+            p.cp_rank[(size_t)(l0 + t) * kStreamPerThread + k] = (uint16_t)cs[c.first]++;
         }
         // positions: entries k and k + 1 of line t side by side (pairs, as in
         // the slices with nl lines), padding -1; every block starts at an
@@ -985,76 +1036,133 @@ static bool plan_sym_compact(Plan &p, const int32_t *ptr, const int32_t *idx)
 // rows (n <= 262 144): a larger matrix does not fit the registers.  Lines and
 // column lists have to fit what the kernels hold.  Experiments:
 // CGMI_RESIDENT=0, never; CGMI_RESIDENT=256, the small form only.
-static void plan_resident_rows(Plan &p, const int32_t *ptr, const int32_t *idx)
+struct ResidentShape {
+    int64_t G = 0, waves = 0, slices = 0, width = 0, cols = 0; // workgroups (0: none), wavefronts; most of each
+    int64_t ns = 0, nsig = 0;
+    // the first slice of workgroup b: that of its first product workgroup
+    int64_t first_slice(int64_t b) const { return (b * nsig / G) * ns / nsig; }
+};
+
+// (of the number of rows alone: vectors and slices planned)
+static ResidentShape resident_shape(const Plan &p, int64_t ns, int64_t nsig)
 {
+    ResidentShape s;
     bool wide_allowed = true;
     if (const char *e = std::getenv("CGMI_RESIDENT")) {
         if (std::strcmp(e, "0") == 0)
-            return;
+            return s;
         wide_allowed = std::strcmp(e, "256") != 0;
     }
-    const int64_t n = p.n, ns = (int64_t)p.sl_off.size() - 1, nsig = p.csr_blocks, nvec = p.vec_blocks;
-    if (!p.slices || ns > nsig * kWavesPerBlock || nsig > 4 * kBlock)
-        return;
+    const int64_t nvec = p.vec_blocks;
+    if (ns > nsig * kWavesPerBlock || nsig > 4 * kBlock)
+        return s;
     const bool wide = nvec > kResidentWgs;
-    const int64_t G = wide ? (nvec + 1) / 2 : nvec, waves = wide ? 8 : 4;
-    if (G > kResidentWgs || (wide && !wide_allowed))
+    if ((wide ? (nvec + 1) / 2 : nvec) > kResidentWgs || (wide && !wide_allowed))
+        return s;
+    s.G = wide ? (nvec + 1) / 2 : nvec;
+    s.waves = wide ? 8 : 4;
+    s.ns = ns;
+    s.nsig = nsig;
+    s.slices = (p.vec_chunk + kBlock - 1) / kBlock; // slices per wavefront = vector rows per thread
+    for (int64_t b = 0; b < s.G; ++b)
+        s.slices = std::max<int64_t>(s.slices, (s.first_slice(b + 1) - s.first_slice(b) + s.waves - 1) / s.waves);
+    s.cols = wide ? (s.slices == 1 ? 6 : 10) * 384 : 16 * 192;
+    s.width = wide ? 16 : 32;
+    if (s.slices > (wide ? 2 : 1))
+        s.G = 0;
+    return s;
+}
+
+static void plan_resident_rows(Plan &p, const int32_t *ptr, const int32_t *idx)
+{
+    if (!p.slices)
         return;
-    int64_t width = 0, slices = (p.vec_chunk + kBlock - 1) / kBlock; // slices per wavefront = vector rows per thread
+    const int64_t n = p.n, ns = (int64_t)p.sl_off.size() - 1;
+    const ResidentShape sh = resident_shape(p, ns, p.csr_blocks);
+    const int64_t G = sh.G, waves = sh.waves;
+    int64_t width = 0;
     for (int64_t s = 0; s < ns; ++s)
         width = std::max<int64_t>(width, (p.sl_off[s + 1] - p.sl_off[s]) / kSliceRows);
-    // first product workgroup and first slice of workgroup b
-    const auto first_wg = [&](int64_t b) { return b * nsig / G; };
-    const auto first_slice = [&](int64_t b) { return first_wg(b) * ns / nsig; };
-    for (int64_t b = 0; b < G; ++b)
-        slices = std::max<int64_t>(slices, (first_slice(b + 1) - first_slice(b) + waves - 1) / waves);
-    const int64_t cols = wide ? (slices == 1 ? 6 : 10) * 384 : 16 * 192;
-    if (slices > (wide ? 2 : 1) || width > (wide ? 16 : 32))
+    if (G == 0 || width > sh.width)
         return;
-    std::vector<int32_t> gptr(1, 0), gcol, place((size_t)n);
-    std::vector<uint16_t> mark((size_t)n, 0); // workgroup + 1 that touched the column last
-    std::vector<uint16_t> lcol((size_t)p.sl_off[ns], 0xffff), lown((size_t)n, 0);
-    int64_t most = 0;
-    for (int64_t b = 0; b < G; ++b) {
-        const int64_t r0 = first_slice(b) * kSliceRows, r1 = std::min(n, first_slice(b + 1) * kSliceRows);
-        const uint16_t id = (uint16_t)(b + 1);
-        int64_t lo = n, hi = -1;
-        for (int64_t r = r0; r < r1; ++r) {
-            mark[r] = id;
-            for (int64_t k = ptr[r]; k < ptr[r + 1]; ++k)
-                mark[idx[k]] = id;
-            const int64_t c0 = ptr[r] < ptr[r + 1] ? std::min<int64_t>(r, idx[ptr[r]]) : r; // columns ascend
-            const int64_t c1 = ptr[r] < ptr[r + 1] ? std::max<int64_t>(r, idx[ptr[r + 1] - 1]) : r;
-            lo = std::min(lo, c0);
-            hi = std::max(hi, c1);
-        }
-        const size_t first = gcol.size();
-        for (int64_t c = lo; c <= hi; ++c)
-            if (mark[c] == id) {
-                place[c] = (int32_t)(gcol.size() - first);
-                gcol.push_back((int32_t)c);
+    const auto first_slice = [&](int64_t b) { return sh.first_slice(b); };
+    // column lists and places, for runs of workgroups side by side
+    const size_t npos = (size_t)p.sl_off[ns], first_at = p.rs_first();
+    std::vector<int32_t> data(first_at, -1); // (two empty places each)
+    uint16_t *const entry = reinterpret_cast<uint16_t *>(data.data()), *const own = entry + npos;
+    std::atomic<bool> fits{true};
+    struct Lists {
+        std::vector<int32_t> col, len;
+    };
+    const auto lists_of = [&](int64_t b0, int64_t b1) {
+        Lists l;
+        std::vector<uint16_t> place; // of the columns from the first one that the workgroup touches
+        for (int64_t b = b0; b < b1 && fits; ++b) {
+            const int64_t r0 = first_slice(b) * kSliceRows, r1 = std::min(n, first_slice(b + 1) * kSliceRows);
+            int64_t lo = r0, hi = r1 - 1;
+            for (int64_t r = r0; r < r1; ++r)
+                if (ptr[r] < ptr[r + 1]) { // columns ascend
+                    lo = std::min<int64_t>(lo, idx[ptr[r]]);
+                    hi = std::max<int64_t>(hi, idx[ptr[r + 1] - 1]);
+                }
+            place.assign((size_t)(hi - lo + 1), 0);
+            uint16_t *const at = place.data();
+            std::fill(at + (r0 - lo), at + (r1 - lo), (uint16_t)1);
+            for (int64_t k = ptr[r0]; k < ptr[r1]; ++k)
+                at[idx[k] - lo] = 1;
+            const size_t first = l.col.size();
+            l.col.resize(first + (size_t)std::min<int64_t>(hi - lo + 1, sh.cols + 1));
+            int64_t len = 0;
+            for (int64_t c = lo; c <= hi && len <= sh.cols; ++c) {
+                l.col[first + (size_t)len] = (int32_t)c;
+                const int64_t touched = at[c - lo];
+                at[c - lo] = (uint16_t)len;
+                len += touched;
             }
-        const int64_t len = (int64_t)(gcol.size() - first);
-        if (len > cols)
-            return;
-        for (int64_t r = r0; r < r1; ++r) {
-            const int64_t s = r / kSliceRows;
-            lown[r] = (uint16_t)place[r];
-            for (int64_t k = ptr[r]; k < ptr[r + 1]; ++k)
-                lcol[p.sl_off[s] + (k - ptr[r]) * kSliceRows + r % kSliceRows] = (uint16_t)(8 * place[idx[k]]);
+            l.col.resize(first + (size_t)len);
+            if (len > sh.cols) {
+                fits = false;
+                break;
+            }
+            for (int64_t s = r0 / kSliceRows; s * kSliceRows < r1; ++s)
+                for (int64_t r = s * kSliceRows; r < std::min(r1, (s + 1) * kSliceRows); ++r) {
+                    own[r] = at[r - lo];
+                    uint16_t *e = entry + p.sl_off[s] + r % kSliceRows;
+                    for (int64_t k = ptr[r]; k < ptr[r + 1]; ++k, e += kSliceRows)
+                        *e = (uint16_t)(8 * at[idx[k] - lo]);
+                }
+            l.len.push_back((int32_t)len);
         }
-        most = std::max(most, len);
-        gptr.push_back((int32_t)gcol.size());
-    }
+        return l;
+    };
+    const int64_t parts = std::min(G, parts_for(ptr[n]));
+    std::vector<Lists> lists((size_t)parts + 1);
+    lists[0] = lists_of(0, 1); // (rows in no order: already too long)
+    if (fits)
+        side_by_side(parts, [&](int64_t t) {
+            lists[(size_t)t + 1] = lists_of(std::max<int64_t>(1, t * G / parts), (t + 1) * G / parts);
+        });
+    if (!fits)
+        return;
+    size_t columns = 0;
+    for (const Lists &l : lists)
+        columns += l.col.size();
+    data.reserve(first_at + (size_t)G + 1 + columns);
+    data.push_back(0);
+    int32_t most = 0;
+    for (const Lists &l : lists)
+        for (const int32_t len : l.len) {
+            most = std::max(most, len);
+            data.push_back(data.back() + len);
+        }
+    for (const Lists &l : lists)
+        data.insert(data.end(), l.col.begin(), l.col.end());
     p.rs_wgs = (int)G;
     p.rs_threads = (int)(waves * kSliceRows);
-    p.rs_slices = (int)slices;
+    p.rs_slices = (int)sh.slices;
     p.rs_width = (int)width;
     p.rs_cols = (int)most;
-    p.rs_gptr.swap(gptr);
-    p.rs_gcol.swap(gcol);
-    p.rs_lcol.swap(lcol);
-    p.rs_lown.swap(lown);
+    p.rs_data.swap(data);
 }
 
 bool choice_fails(const char *where)
@@ -1157,24 +1265,9 @@ static bool plan_sym_expanded(Plan &p, const int32_t *ptr, const int32_t *idx)
     return true;
 }
 
-bool takes_row_plan(const Plan &p)
-{
-    return p.panel || (p.sym_compact && p.n <= kRowsSolveMax);
-}
-
-bool row_plan_ahead(int fmt, int64_t n, int64_t nnz)
-{
-    return nnz > 65536 && (fmt == kCsc || (fmt == kSymCsr && n > 65536 && n <= kRowsSolveMax));
-}
-
-bool build_row_plan(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx, Plan &rows)
+static bool build_row_plan(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx, Plan &rows)
 {
     rows = Plan{};
-    if (n == 0 || slice_mode() < 0)
-        return false;
-    if (const char *e = std::getenv("CGMI_SYM_EXPAND"))
-        if (std::strcmp(e, "0") == 0)
-            return false;
     Rows f;
     if (fmt == kCsc)
         transpose(n, ptr, idx, f);
@@ -1193,6 +1286,100 @@ bool build_row_plan(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx, 
         plan_resident(rows, f.ptr.data(), f.idx.data());
     rows.cached = decide_cached(rows);
     return true;
+}
+
+// Whether the mean line and the column list of the first resident workgroup of
+// the matrix's full rows fit the kernels: long rows, and rows in no order, fail
+// here, before anything is laid out.
+static bool first_list_fits(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx)
+{
+    Plan v;
+    v.n = n;
+    plan_vectors(v);
+    const int64_t ns = (n + kSliceRows - 1) / kSliceRows, nsig = (ns + kWavesPerBlock - 1) / kWavesPerBlock;
+    const ResidentShape sh = resident_shape(v, ns, nsig);
+    if (sh.G == 0 || (fmt == kCsc ? (int64_t)ptr[n] : 2 * (int64_t)ptr[n] - n) > sh.width * n)
+        return false;
+    const int64_t rows = std::min(n, sh.first_slice(1) * kSliceRows);
+    int64_t len = rows;
+    if (fmt == kCsc) { // columns past the rows with an entry in one of them: entries ascend
+        for (int64_t j = rows; j < n && len <= sh.cols; ++j)
+            len += ptr[j] < ptr[j + 1] && idx[ptr[j]] < rows;
+        return len <= sh.cols;
+    }
+    std::vector<int32_t> past; // upper rows: entries to the left of the diagonal are in rows before
+    for (int64_t k = 0; k < ptr[rows]; ++k)
+        if (idx[k] >= rows)
+            past.push_back(idx[k]);
+    std::sort(past.begin(), past.end());
+    return len + (std::unique(past.begin(), past.end()) - past.begin()) <= sh.cols;
+}
+
+// What full rows are for, beside the storage format's own layout: nothing; or
+// lone products, and solves if they turn out resident; or everything, if they do.
+enum class RowsUse { kNone, kBeside, kAll };
+static RowsUse rows_use(int fmt, int64_t n, const int32_t *ptr, const int32_t *idx, int target_entries, bool mixed)
+{
+    if (n == 0 || fmt == kCsr || slice_mode() < 0)
+        return RowsUse::kNone;
+    if (const char *e = std::getenv("CGMI_SYM_EXPAND"))
+        if (std::strcmp(e, "0") == 0)
+            return RowsUse::kNone;
+    if (fmt == kSymCsr) {
+        // as build_plan: expanded up to 65 536 rows, compact blocks of short
+        // lines beyond, up to kRowsSolveMax with rows
+        Plan v;
+        v.n = n;
+        plan_vectors(v);
+        if (target_entries > 0 || !compact_allowed() || v.vec_blocks <= kBlock || n > kRowsSolveMax)
+            return RowsUse::kNone;
+        for (int64_t l = 0; l < n; ++l)
+            if (ptr[l + 1] - ptr[l] > kStreamPerThread)
+                return RowsUse::kNone;
+    }
+    const bool resident = n <= kRowsSolveMax && first_list_fits(fmt, n, ptr, idx);
+    return resident && !mixed ? RowsUse::kAll : RowsUse::kBeside;
+}
+
+int build_plans(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int target_entries, bool mixed,
+                Plan &plan, Plan &rows, std::string &err)
+{
+    const auto by_rows = [&] {
+        try {
+            if (choice_fails("host"))
+                throw std::bad_alloc();
+            return build_row_plan(fmt, n, ptr0, idx0, rows);
+        } catch (const std::bad_alloc &) {
+            rows = Plan{};
+            return false;
+        }
+    };
+    rows = Plan{};
+    RowsUse use = rows_use(fmt, n, ptr0, idx0, target_entries, mixed);
+    if (use == RowsUse::kAll && by_rows() && rows.rs_wgs > 0) {
+        plan = Plan{};
+        plan.format = fmt;
+        plan.n = n;
+        plan.nnz = ptr0[n];
+        plan.lanes = lanes_for_mean_length((double)plan.nnz / (double)n);
+        plan_vectors(plan);
+        return CG_OK;
+    }
+    std::future<bool> ahead; // (joined by its destructor where a step below throws)
+    if (use == RowsUse::kBeside && ptr0[n] > 65536) {
+        try {
+            ahead = std::async(std::launch::async, by_rows);
+        } catch (const std::system_error &) { // no thread: planned below
+        }
+    }
+    const int st = build_plan(fmt, n, ptr0, idx0, target_entries, plan, err);
+    if (ahead.valid())
+        ahead.get();
+    else if (st == CG_OK && use == RowsUse::kBeside)
+        by_rows();
+    if (st != CG_OK)
+        rows = Plan{};
+    return st;
 }
 
 int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int target_entries, Plan &p,

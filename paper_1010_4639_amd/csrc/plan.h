@@ -219,8 +219,13 @@ struct Plan {
     // (bytes of a double, 0xffff = padding; entry k of lane l of a slice at
     // off + 64 k + l), per row its own.
     int rs_wgs = 0, rs_threads = 0, rs_slices = 0, rs_width = 0, rs_cols = 0;
-    std::vector<int32_t> rs_gptr, rs_gcol;
-    std::vector<uint16_t> rs_lcol, rs_lown;
+    // One array: places (16 bits) of the entries' columns [positions] and of the
+    // rows [n, rounded up to even]; first column of each workgroup [rs_wgs + 1];
+    // the columns.
+    std::vector<int32_t> rs_data;
+    const uint16_t *rs_entry() const { return reinterpret_cast<const uint16_t *>(rs_data.data()); }
+    const uint16_t *rs_own() const { return rs_entry() + sl_src.size(); }
+    size_t rs_first() const { return (sl_src.size() + (size_t)n + 1) / 2; } // of the workgroups' first columns
 
     // bytes one sliced product reads from the matrix side (positions, slot
     // descriptors, contribution lists, parked sums); 0 if not sliced
@@ -246,25 +251,24 @@ int validate_and_normalise(int fmt, int64_t n, const int32_t *ptr, const int32_t
 int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int target_entries, Plan &plan,
                std::string &err);
 
-// Second layout of a planned matrix that is not stored by rows: its full rows,
-// sliced like CSR.  CSC: lone products run on it (one sum per row; on the
-// panels a row's sum is in two parts, one of them parked and added by a second
-// kernel: 565 k rows 26.6 -> 17.4 us, 160^3 174 -> 124), and so do solves up to
-// kRowsSolveMax rows, which then can be resident.  Symmetric compact blocks up
-// to that size: both (216 000 rows: product 19.5 -> 7.7 us, solve 4.85 -> 2.38
-// ms; the bytes that the triangle saves do not matter in the caches).  Larger
-// solves keep the panels and the compact blocks.  build_row_plan's false: no
-// such layout (rows too ragged for slices; experiments: CGMI_SYM_EXPAND=0,
-// CGMI_ROW_LAYOUT=rows).  Where the host or the device has no memory for it, or
-// for a resident solve, a handle does without (tests: CGMI_CHOICE_FAILS=host,
-// =device).  It needs the matrix only, so where the main plan is
-// likely to take it (row_plan_ahead) and holds enough entries to pay for a
-// thread, the two are planned side by side: create of a 100^3 CSC system
-// 197 -> 115 ms, of a 60^3 symmetric one 132 -> 118.
+// Plans of a handle, the storage format's and, for a matrix not stored by rows,
+// one of its full rows, sliced like CSR (rows.n = 0: none).  CSC: lone products
+// run on the rows (one sum per row; on panels a row's sum is in two parts, one of
+// them parked and added by a second kernel: 565 k rows 26.6 -> 17.4 us, 160^3
+// 174 -> 124), and so do solves of up to kRowsSolveMax rows that can
+// be resident.  Symmetric compact blocks up to that size: both (216 000 rows:
+// product 19.5 -> 7.7 us, solve 4.85 -> 2.38 ms; the bytes that the triangle
+// saves do not matter in the caches).  Larger solves keep the panels and the
+// compact blocks.  Where everything runs by rows (a resident solve is planned,
+// no mixed precision) `plan` is an outline without the format's layout, which
+// took most of the time (create of a 262 144-row symmetric system 70 -> 16 ms);
+// elsewhere the two are planned side by side.  No rows: too ragged for
+// slices; experiments: CGMI_SYM_EXPAND=0, CGMI_ROW_LAYOUT=rows.  Where the host
+// or the device has no memory for them, or for a resident solve, a handle does
+// without (tests: CGMI_CHOICE_FAILS=host, =device).
 constexpr int64_t kRowsSolveMax = 262144;
-bool takes_row_plan(const Plan &plan);
-bool row_plan_ahead(int fmt, int64_t n, int64_t nnz);
-bool build_row_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, Plan &rows);
+int build_plans(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int target_entries, bool mixed,
+                Plan &plan, Plan &rows, std::string &err);
 bool choice_fails(const char *where);
 
 int lanes_for_mean_length(double mean_len);
