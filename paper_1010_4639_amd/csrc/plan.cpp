@@ -1338,6 +1338,9 @@ static RowsUse rows_use(int fmt, int64_t n, const int32_t *ptr, const int32_t *i
                 return RowsUse::kNone;
     }
     const bool resident = n <= kRowsSolveMax && first_list_fits(fmt, n, ptr, idx);
+    int64_t bw;
+    if (fmt == kCsc && !resident && panel_width(n, ptr, idx, bw) == n)
+        return RowsUse::kNone; // one panel: its slots are whole rows
     return resident && !mixed ? RowsUse::kAll : RowsUse::kBeside;
 }
 
@@ -1377,7 +1380,7 @@ int build_plans(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, in
         ahead.get();
     else if (st == CG_OK && use == RowsUse::kBeside)
         by_rows();
-    if (st != CG_OK)
+    if (st != CG_OK || (plan.panel && plan.pn_npanels == 1 && rows.rs_wgs == 0))
         rows = Plan{};
     return st;
 }

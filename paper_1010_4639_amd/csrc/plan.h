@@ -253,9 +253,10 @@ int build_plan(int fmt, int64_t n, const int32_t *ptr0, const int32_t *idx0, int
 
 // Plans of a handle, the storage format's and, for a matrix not stored by rows,
 // one of its full rows, sliced like CSR (rows.n = 0: none).  CSC: lone products
-// run on the rows (one sum per row; on panels a row's sum is in two parts, one of
-// them parked and added by a second kernel: 565 k rows 26.6 -> 17.4 us, 160^3
-// 174 -> 124), and so do solves of up to kRowsSolveMax rows that can
+// run on the rows (one sum per row; on two or more panels a row's sum is in two
+// parts, one of them parked and added by a second kernel: 565 k rows 26.6 ->
+// 17.4 us, 160^3 174 -> 124; on one panel it is whole, and rows are of use in
+// resident solves only), and so do solves of up to kRowsSolveMax rows that can
 // be resident.  Symmetric compact blocks up to that size: both (216 000 rows:
 // product 19.5 -> 7.7 us, solve 4.85 -> 2.38 ms; the bytes that the triangle
 // saves do not matter in the caches).  Larger solves keep the panels and the

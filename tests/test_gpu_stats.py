@@ -2,6 +2,7 @@
 runs on where there are any, the storage format's blocks only while something
 runs on them, and bytes that the allocations account for.
 """
+import numpy as np
 import pytest
 
 from paper_1010_4639_amd import cgmi
@@ -36,3 +37,34 @@ def test_summary(fmt, grid, mixed, kind):
     for f in BLOCKS:
         assert st[f] == (0 if kind == "rows" else own[f]), f
     assert st["device_bytes"] >= st["plan_bytes"] + 4 * (s.n + 1) + 4 * len(arrs[1])
+
+
+@pytest.mark.parametrize("n,kind", [(300000, "blocks"), (200000, "blocks"), (300000, "beside"), (200000, "rows")])
+def test_rows_beside_one_panel(n, kind, monkeypatch):
+    """Columns in no order are one panel, whose slots are whole rows: no second
+    layout, unless solves can be resident (here: rows coupled to the next one and,
+    on one panel, the first to the last)."""
+    i = np.arange(n)
+    if kind == "blocks":
+        g = np.random.default_rng(7)
+        far = [g.permutation(n) for _ in range(4)]
+        pairs = [(f[:-1], f[1:]) for f in far]
+    else:
+        pairs = [(i[:-1], i[1:])] + ([(i[:1], i[-1:])] if kind == "rows" else [])
+    r = np.concatenate([i] + [p[0] for p in pairs] + [p[1] for p in pairs])
+    c = np.concatenate([i] + [p[1] for p in pairs] + [p[0] for p in pairs])
+    key = np.unique(r.astype(np.int64) * n + c)
+    ptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int32)
+    col = (key % n).astype(np.int32)
+    val = np.where(col == key // n, 9.0, -1.0)
+    own = cgmi.cg_analyze("csc", n, ptr, col)[1]
+    size = {}
+    for expand in ("0", None):
+        monkeypatch.setenv("CGMI_SYM_EXPAND", expand) if expand else monkeypatch.delenv("CGMI_SYM_EXPAND")
+        with cgmi.Solver("csc", ptr, col, val) as S:
+            st = S.stats()
+            size[expand] = st["device_bytes"]
+    say(f"{n} {kind}: {st}, {size}")
+    assert (own["colors"] == 2) == (kind == "beside")
+    assert st["slots"] == (0 if kind == "rows" else own["slots"])
+    assert (size[None] == size["0"]) == (kind == "blocks")
