@@ -256,6 +256,8 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
     m.vec_blocks = p.vec_blocks;
     m.vec_chunk = p.vec_chunk;
     m.matrix_cached = p.matrix_cached();
+    for (int64_t l = 0; l < n; ++l)
+        m.longest = std::max(m.longest, ptr0[l + 1] - ptr0[l]);
     int st;
     int32_t *dptr, *didx;
     double *dval;
@@ -1527,7 +1529,7 @@ int cg_pattern_grad(cg_handle *h, const double *lam, const double *x, double *gr
         h->err = "lam / x / grad NULL";
         return CG_ERR_ARG;
     }
-    launch_pattern_grad(h->dm, lam, x, h->perm, grad, h->stream);
+    launch_pattern_grad(h->dm, h->plan.nnz, lam, x, h->perm, grad, h->stream);
     HIP_TRY(h, hipGetLastError());
     return CG_OK;
 }

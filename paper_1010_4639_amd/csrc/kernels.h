@@ -62,6 +62,7 @@ struct DevMatrix {
     int format = 0;
     int n = 0;
     int lanes = 16;
+    int longest = 0;               // entries of the longest stored line
     const int32_t *ptr = nullptr;
     const int32_t *idx = nullptr;
     const double *val = nullptr;   // null where only the planned layout's copy is kept (keeps_val)
@@ -252,7 +253,7 @@ void launch_set_values(int64_t nnz, const double *src, const int32_t *perm, doub
 // m.val; *bad <- 1 on a bad diagonal
 void launch_mx_rescale(const DevMatrix &m, double *sc, float *v32, int32_t *bad, hipStream_t s);
 // out[perm ? perm[k] : k] = dL/d(stored value k) from the adjoint lam and the solution x
-void launch_pattern_grad(const DevMatrix &m, const double *lam, const double *x, const int32_t *perm, double *out,
-                         hipStream_t s);
+void launch_pattern_grad(const DevMatrix &m, int64_t nnz, const double *lam, const double *x, const int32_t *perm,
+                         double *out, hipStream_t s);
 
 } // namespace cgmi

@@ -1645,12 +1645,14 @@ __global__ __launch_bounds__(kBlock) void k_mx_scale(int n, const int32_t *__res
 // line's own lam / x come from that lane's register.  Bytes bound it: 12 per
 // entry (14.8 M entries: 45 us, 4.0 TB/s; one thread per line, writing 8 and
 // reading 4 bytes a cache line apart, took 280 us).  The loads of one pass are
-// in flight together, and a pass takes what 64 lines of a tetrahedral mesh
-// hold (15 entries a full line, 8 a triangle's): 45 us, where 4 a lane needed
-// four dependent passes and 54 us, 8 two and 48.5; a triangle, which gathers
-// twice, 33 us with 8 (35 with 4, 50 with 16: registers).
+// in flight together, kGradUnroll a lane: what 64 lines hold on average, so that
+// one pass does it and loads little beyond the run's end (launch_pattern_grad).
+// 15 entries a line: 45 us with 16, where 4 need four dependent passes and 54
+// us; 5 a line (1 M lines): 19.6 with 6, 29 with 16; 3: 12.2 with 3, 24 with 16.
+// A triangle, which gathers twice, takes 8 at most (registers): 8 a line 33 us
+// with 8, 50 with 16; 3 a line 16.4 with 3, 24 with 8.
 constexpr int kGradWindow = 1024; // entries mapped at a time
-template <int FMT>
+template <int FMT, int kGradUnroll>
 __global__ __launch_bounds__(kBlock) void k_pattern_grad(int n, const int32_t *__restrict__ ptr,
                                                          const int32_t *__restrict__ idx,
                                                          const double *__restrict__ lam,
@@ -1660,7 +1662,6 @@ __global__ __launch_bounds__(kBlock) void k_pattern_grad(int n, const int32_t *_
 #pragma clang fp contract(off)
     __shared__ uint8_t map[kWaves][kGradWindow];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    constexpr int kGradUnroll = FMT == kSymCsr ? 8 : 16;
     const int l0 = (blockIdx.x * kWaves + wv) * 64;
     const int l = min(l0 + lane, n - 1);
     const bool has = l0 + lane < n;
@@ -1713,6 +1714,29 @@ __global__ __launch_bounds__(kBlock) void k_pattern_grad(int n, const int32_t *_
             }
         }
         __syncthreads();
+    }
+}
+
+// One thread per line: lines of one or two entries, whose lanes read and write
+// whole cache lines anyway (1 M lines of a bidiagonal triangle 9.0 us, along
+// the run 10.7).
+__global__ __launch_bounds__(kBlock) void k_pattern_grad_lines(int fmt, int n, const int32_t *__restrict__ ptr,
+                                                               const int32_t *__restrict__ idx,
+                                                               const double *__restrict__ lam,
+                                                               const double *__restrict__ x,
+                                                               const int32_t *__restrict__ perm,
+                                                               double *__restrict__ out)
+{
+#pragma clang fp contract(off)
+    const int l = blockIdx.x * kBlock + threadIdx.x;
+    if (l >= n)
+        return;
+    const double ll = lam[l], xl = x[l];
+    for (int k = ptr[l]; k < ptr[l + 1]; ++k) {
+        const int j = idx[k];
+        const double t1 = ll * x[j], t2 = lam[j] * xl;
+        const double g = fmt == kCsr ? -t1 : fmt == kCsc ? -t2 : j == l ? -t1 : -(t1 + t2);
+        out[perm ? perm[k] : k] = g;
     }
 }
 
@@ -2212,18 +2236,43 @@ void launch_mx_rescale(const DevMatrix &m, double *sc, float *v32, int32_t *bad,
     hipLaunchKernelGGL(k_mx_scale, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, m.val, sc, v32);
 }
 
-void launch_pattern_grad(const DevMatrix &m, const double *lam, const double *x, const int32_t *perm, double *out,
-                         hipStream_t s)
+namespace {
+template <int U>
+void pattern_grad(const DevMatrix &m, const double *lam, const double *x, const int32_t *perm, double *out,
+                  hipStream_t s)
+{
+    const dim3 g((m.n + kBlock - 1) / kBlock), b(kBlock);
+    if (m.format == kCsr)
+        hipLaunchKernelGGL((k_pattern_grad<kCsr, U>), g, b, 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
+    else if (m.format == kCsc)
+        hipLaunchKernelGGL((k_pattern_grad<kCsc, U>), g, b, 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
+    else
+        hipLaunchKernelGGL((k_pattern_grad<kSymCsr, (U < 8 ? U : 8)>), g, b, 0, s, m.n, m.ptr, m.idx, lam, x, perm,
+                           out);
+}
+} // namespace
+
+void launch_pattern_grad(const DevMatrix &m, int64_t nnz, const double *lam, const double *x, const int32_t *perm,
+                         double *out, hipStream_t s)
 {
     if (m.n <= 0)
         return;
-    const dim3 g((m.n + kBlock - 1) / kBlock);
-    if (m.format == kCsr)
-        hipLaunchKernelGGL(k_pattern_grad<kCsr>, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
-    else if (m.format == kCsc)
-        hipLaunchKernelGGL(k_pattern_grad<kCsc>, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
+    // entries a line, rounded up; with long lines among them (runs of many
+    // passes, which one wavefront makes) as if all were
+    const int64_t mean = m.longest <= 64 ? (nnz + m.n - 1) / m.n : m.longest;
+    if (mean <= 2 && m.longest <= 8)
+        hipLaunchKernelGGL(k_pattern_grad_lines, dim3((m.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m.format, m.n,
+                           m.ptr, m.idx, lam, x, perm, out);
+    else if (mean <= 3)
+        pattern_grad<3>(m, lam, x, perm, out, s);
+    else if (mean <= 4)
+        pattern_grad<4>(m, lam, x, perm, out, s);
+    else if (mean <= 6)
+        pattern_grad<6>(m, lam, x, perm, out, s);
+    else if (mean <= 8)
+        pattern_grad<8>(m, lam, x, perm, out, s);
     else
-        hipLaunchKernelGGL(k_pattern_grad<kSymCsr>, g, dim3(kBlock), 0, s, m.n, m.ptr, m.idx, lam, x, perm, out);
+        pattern_grad<16>(m, lam, x, perm, out, s);
 }
 
 } // namespace cgmi
