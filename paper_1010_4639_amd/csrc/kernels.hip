@@ -627,6 +627,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_slices(int nl, int ns, const in
             w - 1 < len ? (staged ? stage[wv][a - base + w - 1] : src[a + w - 1]) : T(0);
 }
 
+constexpr int64_t kFillBlockLines = 256; // lines of a block on average from which k_fill_compact pays
 // Values of symmetric rows into their compact blocks, from the row pointers:
 // thread t of a block's workgroup reads its line's (at most 8) entries, which
 // are contiguous, and writes them at the block's positions.  8 bytes read and
@@ -2199,7 +2200,10 @@ void fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, const T 
     } else if (m.panel) {
         launch_permute(nnz, src, m.pn_src, pn, s, order);
     }
-    if (m.compact && order == nullptr) {
+    // a workgroup a block: where pockets of the graph make blocks of a few lines,
+    // the list as well (1 M lines in blocks of one 560 us, by the list 6.5; of 64
+    // 12.9 / 6.0, of 512 7.7 / 6.0, and beyond the caches the list's bytes cost more)
+    if (m.compact && order == nullptr && (int64_t)m.nblocks * kFillBlockLines <= m.n) {
         if (m.nblocks > 0)
             hipLaunchKernelGGL(k_fill_compact<T>, dim3(m.nblocks), dim3(kCompactThreads), 0, s, m.cblocks, m.vperm,
                                m.ptr, src, ss);
