@@ -46,6 +46,7 @@ struct cg_handle {
     DevMatrix rows;
     cg_plan_stats row_stats{};
     int64_t row_positions = 0;
+    bool rows_from_panels = false; // rows.sl_src: positions of the panels' slices, not entries
     bool rows_solve = false;
     // products and solves all run by rows: `plan` is an outline (plan.h)
     bool lean = false;
@@ -236,6 +237,10 @@ int upload_rows(cg_handle *h)
     fill_stats(p, &h->row_stats);
     return upload_slices(h, p, m, false);
 }
+
+// Bytes of a CSC panel's width of values beyond which the rows' are filled from
+// the panels' (refresh_values).
+constexpr int64_t kReachBytes = 3 << 20;
 
 int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector<int32_t> &idx0, const double *vals)
 {
@@ -549,6 +554,16 @@ int upload_all(cg_handle *h, const std::vector<int32_t> &ptr0, const std::vector
             return st;
         m.val32 = dv32;
         m.dscale = dsc;
+    }
+    // the rows' values from the panels' where a panel's do not stay in an L2 (refresh_values)
+    int64_t reach = n > 0 ? p.pn_width * p.nnz / n * (int64_t)sizeof(double) : 0;
+    if (const char *v = std::getenv("CGMI_ROWS_FROM_PANELS")) // (tests)
+        reach = std::strcmp(v, "0") != 0 ? INT64_MAX : 0;
+    if (h->rows.n > 0 && m.panel && m.slices && reach > kReachBytes) {
+        launch_chain_lists((int64_t)p.sl_src.size(), m.sl_src, h->row_positions, const_cast<int32_t *>(h->rows.sl_src),
+                           reinterpret_cast<int32_t *>(m.sl_val), nullptr);
+        HIP_TRY(h, hipGetLastError());
+        h->rows_from_panels = true;
     }
     hipError_t e = hipHostMalloc((void **)&h->host_st, 2 * sizeof(DevState) + sizeof(*h->word),
                                  hipHostMallocMapped | hipHostMallocCoherent);
@@ -869,7 +884,16 @@ int refresh_values(cg_handle *h, const double *src, const int32_t *order)
     DevMatrix &m = h->dm;
     const int64_t nnz = h->plan.nnz, np = (int64_t)h->plan.sl_src.size();
     launch_fill_layout(m, nnz, np, src, order, h->stream);
-    if (h->rows.n > 0)
+    // Columns into rows is a transposition: neighbouring rows take turns at the
+    // cache lines of a panel's width of columns.  Where those do not stay in an L2
+    // (4 MB, shared with what streams past), only the panels' slots are filled that
+    // way, and the rows from them: a row's values are runs of one or two slots, and
+    // neighbouring rows read along.  Both from `src` / rows from panels: 3.5 MB, 27
+    // entries a row, 208 / 194 us; 4.1 MB, 2.2 M rows of 15, 374 / 316; but 2.4 MB,
+    // 1 M rows of 15, 110 / 139, as the panels' values come back from memory.
+    if (h->rows_from_panels)
+        launch_fill_layout(h->rows, 0, h->row_positions, m.sl_val, nullptr, h->stream);
+    else if (h->rows.n > 0)
         launch_fill_layout(h->rows, 0, h->row_positions, src, order, h->stream);
     HIP_TRY(h, hipGetLastError());
     if (h->mixed && m.n > 0) {

@@ -247,6 +247,9 @@ void launch_permute(int64_t nnz, const float *src, const int32_t *perm, float *d
 void launch_fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, const double *src,
                         const int32_t *order, hipStream_t s);
 void launch_fill_layout32(const DevMatrix &m, int64_t nnz, int64_t sl_positions, hipStream_t s);
+// second[q] = position p of `first` with first[p] = second[q] (-1 stays): a list
+// of entries becomes one of positions of another layout.  tmp: an int32 per entry.
+void launch_chain_lists(int64_t m1, const int32_t *first, int64_t m2, int32_t *second, int32_t *tmp, hipStream_t s);
 // val[k] = src[perm ? perm[k] : k] for k < nnz
 void launch_set_values(int64_t nnz, const double *src, const int32_t *perm, double *val, hipStream_t s);
 // mixed precision: recompute D^-1/2 (into sc, the caller's row order) and the FP32 scaled values from

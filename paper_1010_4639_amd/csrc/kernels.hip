@@ -580,6 +580,23 @@ __global__ __launch_bounds__(kBlock) void k_permute(int64_t nnz, const T *__rest
     }
 }
 
+// inv[list[p]] = p; list[q] = inv[list[q]] (negative entries: padding)
+__global__ __launch_bounds__(kBlock) void k_list_inverse(int64_t m, const int32_t *__restrict__ list,
+                                                         int32_t *__restrict__ inv)
+{
+    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (p < m && list[p] >= 0)
+        inv[list[p]] = (int32_t)p;
+}
+
+__global__ __launch_bounds__(kBlock) void k_list_through(int64_t m, const int32_t *__restrict__ inv,
+                                                         int32_t *__restrict__ list)
+{
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (q < m && list[q] >= 0)
+        list[q] = inv[list[q]];
+}
+
 // Values of CSR rows into their slices, straight from the row pointers (the
 // entries of 64 consecutive rows are one contiguous run): a wavefront stages
 // the run in LDS with coalesced loads and writes the positions from there,
@@ -2222,6 +2239,16 @@ void launch_fill_layout(const DevMatrix &m, int64_t nnz, int64_t sl_positions, c
 void launch_fill_layout32(const DevMatrix &m, int64_t nnz, int64_t sl_positions, hipStream_t s)
 {
     fill_layout(m, nnz, sl_positions, m.val32, nullptr, m.sl_val32, m.ss_val32, m.pn_val32, s);
+}
+
+void launch_chain_lists(int64_t m1, const int32_t *first, int64_t m2, int32_t *second, int32_t *tmp, hipStream_t s)
+{
+    if (m1 > 0)
+        hipLaunchKernelGGL(k_list_inverse, dim3((unsigned)((m1 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, m1, first,
+                           tmp);
+    if (m2 > 0)
+        hipLaunchKernelGGL(k_list_through, dim3((unsigned)((m2 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, m2, tmp,
+                           second);
 }
 
 void launch_set_values(int64_t nnz, const double *src, const int32_t *perm, double *val, hipStream_t s)
