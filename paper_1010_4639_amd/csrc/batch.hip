@@ -876,6 +876,8 @@ struct cg_batch {
     int32_t *ptr = nullptr, *idx = nullptr, *rb_row = nullptr, *sys_wg0 = nullptr;
     double *val = nullptr;
     WgDesc *wgs = nullptr;
+    WgDesc *lone = nullptr; // the split of lone products, where it is another one
+    int G_lone = 0;
     int32_t *live = nullptr; // per workgroup: its system has instances that run
     Inst *inst = nullptr;
     double *P = nullptr, *Rv = nullptr, *Q = nullptr, *Xw = nullptr;
@@ -942,10 +944,73 @@ void drop_graph(cg_batch *h)
     h->graph_batch = 0;
 }
 
-// Row blocks (<= 256*ept entries, <= 256 rows, never across systems) and the
-// workgroup split: system s gets max(1, round(wg_target * nnz_s / nnz))
-// workgroups (at most one per row block), each a contiguous run of its row
-// blocks.  Returns the partial-array size needed (G * R).
+// The workgroup split: system s gets max(1, round(wg_target * nnz_s / nnz))
+// workgroups, at most `most` and one per part (row block or slice), each a
+// contiguous run of its parts.  part0: first part of each system (and the end),
+// row0: first row of each part; wg0: first workgroup of each system.
+std::vector<WgDesc> split(const cg_batch *h, int wg_target, int most, const std::vector<int32_t> &part0,
+                          const std::vector<int32_t> &row0, std::vector<int32_t> &wg0)
+{
+    const int32_t *ptr = h->hptr.data();
+    std::vector<WgDesc> w;
+    wg0.resize((size_t)h->nsys);
+    for (int s = 0; s < h->nsys; ++s) {
+        const int q0 = part0[s], nq = part0[s + 1] - q0;
+        const int64_t nnzs = (int64_t)ptr[h->sys_off[s + 1]] - ptr[h->sys_off[s]];
+        int g = (int)std::llround((double)wg_target * (double)nnzs / (double)std::max<int64_t>(h->nnz, 1));
+        g = std::max(1, std::min({g, nq, most}));
+        wg0[s] = (int32_t)w.size();
+        for (int k = 0; k < g; ++k) {
+            WgDesc d{};
+            d.sys = s;
+            d.lead = k == 0;
+            d.rb0 = q0 + (int)((int64_t)k * nq / g);
+            d.rb1 = q0 + (int)((int64_t)(k + 1) * nq / g);
+            d.i0 = row0[d.rb0];
+            d.i1 = d.rb1 < q0 + nq ? row0[d.rb1] : (int32_t)h->sys_off[s + 1];
+            w.push_back(d);
+        }
+    }
+    for (auto &d : w) {
+        d.wg0 = wg0[d.sys];
+        d.wg1 = d.sys + 1 < h->nsys ? wg0[d.sys + 1] : (int32_t)w.size();
+    }
+    return w;
+}
+
+// A plan's splits on the device: of the solves, and of lone products where more
+// workgroups pay there, which have no partials to sum (lone_target in all, `lone`
+// times kMaxSysWgs a system; lone = 1: none).
+int upload_split(cg_batch *h, int wg_target, int lone_target, int lone, const std::vector<int32_t> &part0,
+                 const std::vector<int32_t> &row0)
+{
+    std::vector<int32_t> wg0, wg0_lone;
+    const std::vector<WgDesc> w = split(h, wg_target, kMaxSysWgs, part0, row0, wg0);
+    std::vector<WgDesc> l;
+    if (lone > 1)
+        l = split(h, lone_target, lone * kMaxSysWgs, part0, row0, wg0_lone);
+    if (l.size() <= w.size())
+        l.clear();
+    int st;
+    const size_t np = w.size() * (size_t)h->R, nl = std::max(w.size(), l.size()) * (size_t)h->R;
+    if ((st = bupload(h, h->plan_allocs, &h->wgs, w.data(), w.size())) != CG_OK ||
+        (st = bupload(h, h->plan_allocs, &h->sys_wg0, wg0.data(), wg0.size())) != CG_OK ||
+        (st = balloc(h, h->plan_allocs, &h->sig, nl)) != CG_OK ||
+        (st = balloc(h, h->plan_allocs, &h->rho, np)) != CG_OK ||
+        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK ||
+        (st = balloc(h, h->plan_allocs, &h->live, w.size())) != CG_OK)
+        return st;
+    h->lone = nullptr;
+    if (!l.empty() && (st = bupload(h, h->plan_allocs, &h->lone, l.data(), l.size())) != CG_OK)
+        return st;
+    h->G = (int)w.size();
+    h->G_lone = (int)l.size();
+    return CG_OK;
+}
+
+// Row blocks (<= 256*ept entries, <= 256 rows, never across systems), split over
+// workgroups.  Lone products take up to 2048 a system with one or two right-hand
+// sides: 100^3 63.3 -> 50.9 us with one, 75.8 -> 61.3 with two (four: 105 -> 109).
 int build_plan(cg_batch *h, int ept, int wg_target)
 {
     const int E = kBlock * ept;
@@ -973,42 +1038,12 @@ int build_plan(cg_batch *h, int ept, int wg_target)
     }
     sys_rb0[h->nsys] = (int32_t)rb.size();
     rb.push_back((int32_t)h->N);
-    std::vector<WgDesc> w;
-    std::vector<int32_t> wg0(h->nsys);
-    for (int s = 0; s < h->nsys; ++s) {
-        const int nrbs = sys_rb0[s + 1] - sys_rb0[s];
-        const int64_t nnzs = (int64_t)ptr[h->sys_off[s + 1]] - ptr[h->sys_off[s]];
-        int g = (int)std::llround((double)wg_target * (double)nnzs / (double)std::max<int64_t>(h->nnz, 1));
-        g = std::max(1, std::min({g, nrbs, kMaxSysWgs}));
-        wg0[s] = (int32_t)w.size();
-        for (int k = 0; k < g; ++k) {
-            WgDesc d{};
-            d.sys = s;
-            d.lead = k == 0;
-            d.rb0 = sys_rb0[s] + (int)((int64_t)k * nrbs / g);
-            d.rb1 = sys_rb0[s] + (int)((int64_t)(k + 1) * nrbs / g);
-            d.i0 = rb[d.rb0];
-            d.i1 = rb[d.rb1];
-            w.push_back(d);
-        }
-    }
-    for (auto &d : w) {
-        d.wg0 = wg0[d.sys];
-        d.wg1 = d.sys + 1 < h->nsys ? wg0[d.sys + 1] : (int32_t)w.size();
-    }
     drop_graph(h);
     free_list(h->plan_allocs);
     int st;
-    const size_t np = w.size() * (size_t)h->R;
     if ((st = bupload(h, h->plan_allocs, &h->rb_row, rb.data(), rb.size())) != CG_OK ||
-        (st = bupload(h, h->plan_allocs, &h->wgs, w.data(), w.size())) != CG_OK ||
-        (st = bupload(h, h->plan_allocs, &h->sys_wg0, wg0.data(), wg0.size())) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->sig, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->rho, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->live, w.size())) != CG_OK)
+        (st = upload_split(h, wg_target, wg_target, h->R <= 2 ? 2 : 1, sys_rb0, rb)) != CG_OK)
         return st;
-    h->G = (int)w.size();
     h->nrb = (int)rb.size() - 1;
     h->ept = ept;
     h->wg_target = wg_target;
@@ -1092,84 +1127,60 @@ int ensure_slices(cg_batch *h)
     return CG_OK;
 }
 
-// Workgroup split over the slices: system s gets max(1, round(wg_target *
-// nnz_s / nnz)) workgroups (at most one per slice), each a contiguous run of
-// its slices.
+// The slices split over workgroups.  Lone products of a matrix that comes from
+// memory take up to 8192, 4096 a system: 100^3 and two of them, two right-hand sides,
+// 44.6 -> 37.6 us and 77.0 -> 68.8 (with 8 positions in flight, spmm_slices);
+// four 55.3 -> 50.6 and 103 -> 94; from the cache 60^3 10.7 -> 14.0.
 int build_plan_slices(cg_batch *h, int wg_target)
 {
     int st = ensure_slices(h);
     if (st != CG_OK)
         return st;
-    const int32_t *ptr = h->hptr.data();
-    std::vector<WgDesc> w;
-    std::vector<int32_t> wg0(h->nsys);
-    for (int s = 0; s < h->nsys; ++s) {
-        const int q0 = h->hsl_sys0[s], nq = h->hsl_sys0[s + 1] - q0;
-        const int64_t nnzs = (int64_t)ptr[h->sys_off[s + 1]] - ptr[h->sys_off[s]];
-        int g = (int)std::llround((double)wg_target * (double)nnzs / (double)std::max<int64_t>(h->nnz, 1));
-        g = std::max(1, std::min({g, nq, kMaxSysWgs}));
-        wg0[s] = (int32_t)w.size();
-        for (int k = 0; k < g; ++k) {
-            WgDesc d{};
-            d.sys = s;
-            d.lead = k == 0;
-            d.rb0 = q0 + (int)((int64_t)k * nq / g);
-            d.rb1 = q0 + (int)((int64_t)(k + 1) * nq / g);
-            d.i0 = h->hsl_row[d.rb0];
-            d.i1 = d.rb1 < q0 + nq ? h->hsl_row[d.rb1] : (int32_t)h->sys_off[s + 1];
-            w.push_back(d);
-        }
-    }
-    for (auto &d : w) {
-        d.wg0 = wg0[d.sys];
-        d.wg1 = d.sys + 1 < h->nsys ? wg0[d.sys + 1] : (int32_t)w.size();
-    }
     drop_graph(h);
     free_list(h->plan_allocs);
-    const size_t np = w.size() * (size_t)h->R;
-    if ((st = bupload(h, h->plan_allocs, &h->wgs, w.data(), w.size())) != CG_OK ||
-        (st = bupload(h, h->plan_allocs, &h->sys_wg0, wg0.data(), wg0.size())) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->sig, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->rho, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->bb, np)) != CG_OK ||
-        (st = balloc(h, h->plan_allocs, &h->live, w.size())) != CG_OK)
+    if ((st = upload_split(h, wg_target, 8192, h->deep ? 4 : 1, h->hsl_sys0, h->hsl_row)) != CG_OK)
         return st;
     h->rb_row = nullptr;
-    h->G = (int)w.size();
     h->nrb = 0;
     h->wg_target = wg_target;
     h->lanes = 1;
     return CG_OK;
 }
 
+// Workgroups of a product
+struct Split {
+    const WgDesc *wgs;
+    int n;
+};
+
 template <int R, int EPT>
-void spmm_r(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+void spmm_r(cg_batch *h, const double *P, double *Q, Inst *inst, const Split &g, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_bspmm<R, EPT>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->rb_row, h->ptr, h->idx, h->val,
+    hipLaunchKernelGGL((k_bspmm<R, EPT>), dim3(g.n), dim3(kBlock), 0, s, g.wgs, h->rb_row, h->ptr, h->idx, h->val,
                        P, Q, h->sig, inst, h->live);
 }
 
 template <int R>
-void spmm_e(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+void spmm_e(cg_batch *h, const double *P, double *Q, Inst *inst, const Split &g, hipStream_t s)
 {
     // LDS holds 256 * EPT * R products (<= 32 KB)
     if (h->ept == 1)
-        spmm_r<R, 1>(h, P, Q, inst, s);
+        spmm_r<R, 1>(h, P, Q, inst, g, s);
     else if (h->ept == 2)
-        spmm_r<R, 2>(h, P, Q, inst, s);
+        spmm_r<R, 2>(h, P, Q, inst, g, s);
     else
-        spmm_r<R, 4>(h, P, Q, inst, s);
+        spmm_r<R, 4>(h, P, Q, inst, g, s);
 }
 
 template <int R>
-void spmm_lanes(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+void spmm_lanes(cg_batch *h, const double *P, double *Q, Inst *inst, const Split &g, hipStream_t s)
 {
     constexpr int U = R == 4 ? 1 : 2; // rows in flight per lane group (registers: 8 waves per SIMD)
     if (h->lanes == 8)
-        hipLaunchKernelGGL((k_bspmm_lanes<R, 8, U>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->ptr, h->idx, h->val,
+        hipLaunchKernelGGL((k_bspmm_lanes<R, 8, U>), dim3(g.n), dim3(kBlock), 0, s, g.wgs, h->ptr, h->idx, h->val,
                            P, Q, h->sig, inst, h->live);
     else
-        hipLaunchKernelGGL((k_bspmm_lanes<R, 16, U>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->ptr, h->idx,
+        hipLaunchKernelGGL((k_bspmm_lanes<R, 16, U>), dim3(g.n), dim3(kBlock), 0, s, g.wgs, h->ptr, h->idx,
                            h->val, P, Q, h->sig, inst, h->live);
 }
 
@@ -1180,72 +1191,57 @@ void spmm_lanes(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t
 // always.  Solves, 8 / 16: matrix of 74 MB (17 systems of 25^3..35^3, two
 // right-hand sides) 5.63 / 5.91 ms, 120 MB (17 of 29^3..44^3) 10.3 / 10.2, 170
 // MB (24 of those) 16.0 / 14.7, 213 MB (24 of 30^3..48^3, one) 17.9 / 16.0; 260
-// MB with four 34.8 / 35.7.
+// MB with four 34.8 / 35.7.  Lone products on a split of their own, which have
+// the workgroups: 8.
 template <int R, int U>
-void spmm_slices_u(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+void spmm_slices_u(cg_batch *h, const double *P, double *Q, Inst *inst, const Split &g, hipStream_t s)
 {
     if (h->sl_d16)
-        hipLaunchKernelGGL((k_bspmm_slices<R, U, int16_t>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sl_row,
+        hipLaunchKernelGGL((k_bspmm_slices<R, U, int16_t>), dim3(g.n), dim3(kBlock), 0, s, g.wgs, h->sl_row,
                            h->sl_off, h->sl_d16, h->sl_val, P, Q, h->sig, inst, h->live);
     else
-        hipLaunchKernelGGL((k_bspmm_slices<R, U, int32_t>), dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->sl_row,
+        hipLaunchKernelGGL((k_bspmm_slices<R, U, int32_t>), dim3(g.n), dim3(kBlock), 0, s, g.wgs, h->sl_row,
                            h->sl_off, h->sl_col, h->sl_val, P, Q, h->sig, inst, h->live);
 }
 
 template <int R>
-void spmm_slices(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+void spmm_slices(cg_batch *h, const double *P, double *Q, Inst *inst, const Split &g, hipStream_t s)
 {
     if constexpr (R <= 2) {
-        if (h->deep)
-            return spmm_slices_u<R, 16>(h, P, Q, inst, s);
+        if (h->deep && g.wgs != h->lone)
+            return spmm_slices_u<R, 16>(h, P, Q, inst, g, s);
     }
-    spmm_slices_u<R, 8>(h, P, Q, inst, s);
+    spmm_slices_u<R, 8>(h, P, Q, inst, g, s);
 }
 
 // the product of the current plan and schedule
 template <int R>
-void spmm_any(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+void spmm_any(cg_batch *h, const double *P, double *Q, Inst *inst, const Split &g, hipStream_t s)
 {
     if (h->lanes == 1)
-        spmm_slices<R>(h, P, Q, inst, s);
+        spmm_slices<R>(h, P, Q, inst, g, s);
     else if (h->lanes)
-        spmm_lanes<R>(h, P, Q, inst, s);
+        spmm_lanes<R>(h, P, Q, inst, g, s);
     else
-        spmm_e<R>(h, P, Q, inst, s);
+        spmm_e<R>(h, P, Q, inst, g, s);
 }
 
-void spmm(cg_batch *h, const double *P, double *Q, Inst *inst, hipStream_t s)
+// The product outside the iteration: for the caller (lone), for a schedule's time
+void spmm(cg_batch *h, const double *P, double *Q, bool lone, hipStream_t s)
 {
-    if (h->lanes == 1) {
-        if (h->R == 1)
-            spmm_slices<1>(h, P, Q, inst, s);
-        else if (h->R == 2)
-            spmm_slices<2>(h, P, Q, inst, s);
-        else
-            spmm_slices<4>(h, P, Q, inst, s);
-        return;
-    }
-    if (h->lanes) {
-        if (h->R == 1)
-            spmm_lanes<1>(h, P, Q, inst, s);
-        else if (h->R == 2)
-            spmm_lanes<2>(h, P, Q, inst, s);
-        else
-            spmm_lanes<4>(h, P, Q, inst, s);
-        return;
-    }
+    const Split g = lone && h->lone ? Split{h->lone, h->G_lone} : Split{h->wgs, h->G};
     if (h->R == 1)
-        spmm_e<1>(h, P, Q, inst, s);
+        spmm_any<1>(h, P, Q, nullptr, g, s);
     else if (h->R == 2)
-        spmm_e<2>(h, P, Q, inst, s);
+        spmm_any<2>(h, P, Q, nullptr, g, s);
     else
-        spmm_e<4>(h, P, Q, inst, s);
+        spmm_any<4>(h, P, Q, nullptr, g, s);
 }
 
 template <int R>
 void iteration_r(cg_batch *h, bool report, hipStream_t s)
 {
-    spmm_any<R>(h, h->P, h->Q, h->inst, s);
+    spmm_any<R>(h, h->P, h->Q, h->inst, {h->wgs, h->G}, s);
     hipLaunchKernelGGL(k_bupdate_r<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->Rv, h->Q, h->inst, h->sig, h->rho,
                        h->live);
     hipLaunchKernelGGL(k_bupdate_xp<R>, dim3(h->G + (report ? 1 : 0)), dim3(kBlock), 0, s, h->wgs, h->Xw, h->P, h->Rv, h->inst, h->rho,
@@ -1265,7 +1261,7 @@ void iteration(cg_batch *h, bool report, hipStream_t s)
 template <int R>
 void init_r(cg_batch *h, const double *B, const double *X0, double tol, int maxit, hipStream_t s)
 {
-    spmm_any<R>(h, X0, h->Q, nullptr, s);
+    spmm_any<R>(h, X0, h->Q, nullptr, {h->wgs, h->G}, s);
     hipLaunchKernelGGL(k_binit_vec<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, B, X0, h->Q, h->Rv, h->P, h->Xw,
                        h->rho, h->bb, h->live);
     hipLaunchKernelGGL(k_binit_state<R>, dim3(h->nsys), dim3(kBlock), 0, s, h->wgs, h->sys_wg0, h->inst, h->rho,
@@ -1275,7 +1271,7 @@ void init_r(cg_batch *h, const double *B, const double *X0, double tol, int maxi
 template <int R>
 void finish_r(cg_batch *h, const double *B, double *X, hipStream_t s)
 {
-    spmm_any<R>(h, h->Xw, h->Q, nullptr, s);
+    spmm_any<R>(h, h->Xw, h->Q, nullptr, {h->wgs, h->G}, s);
     hipLaunchKernelGGL(k_bresid<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, B, h->Q, h->bb);
     hipLaunchKernelGGL(k_bfinish<R>, dim3(h->G), dim3(kBlock), 0, s, h->wgs, h->inst, h->bb, h->Xw, X);
 }
@@ -1438,7 +1434,7 @@ int cg_batch_spmm(cg_batch *h, const double *X, double *Y)
 {
     if (!h || !X || !Y || X == Y)
         return CG_ERR_ARG;
-    spmm(h, X, Y, nullptr, h->stream);
+    spmm(h, X, Y, true, h->stream);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? CG_OK : bfail(h, e, "launch");
 }
@@ -1477,10 +1473,10 @@ int cg_batch_autotune(cg_batch *h, int32_t *entries_per_block, int32_t *lanes_pe
             if ((st = cd.lanes == 1 ? build_plan_slices(h, 2 * wgt) : build_plan(h, cd.ept, wgt)) != CG_OK)
                 break;
             h->lanes = cd.lanes;
-            spmm(h, X, Y, nullptr, h->stream);
+            spmm(h, X, Y, false, h->stream);
             (void)hipEventRecord(a, h->stream);
             for (int i = 0; i < 10; ++i)
-                spmm(h, X, Y, nullptr, h->stream);
+                spmm(h, X, Y, false, h->stream);
             (void)hipEventRecord(b, h->stream);
             (void)hipEventSynchronize(b);
             float ms = 0.f;
