@@ -168,11 +168,15 @@ def _host_f64(a):
 def _current_stream():
     """The caller's current torch stream (on the current device) as an address.
     The raw lookup takes 0.1 us; torch.cuda.current_stream() makes a stream
-    object for 2.5 us, a quarter of a small product's call."""
+    object for 2.5 us, a quarter of a small product's call.  Its two names are
+    not public: where a version of torch lacks one, the object."""
     import torch
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if torch.cuda.is_initialized():
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, n, name):
