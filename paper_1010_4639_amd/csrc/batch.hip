@@ -483,11 +483,13 @@ __device__ __forceinline__ void sys_sums(double s, double (&red)[kWaves][R], dou
 // starts at a multiple of R elements), the first kBPre loads of a thread
 // before the system's partials are summed.  A thread keeps its right-hand
 // sides, because the stride kBlock * V is a multiple of R.  One load ahead is
-// enough: the plans give a workgroup one or two elements a thread, a deeper
-// prefetch mostly loads its last element again and holds registers that
-// further workgroups need (kBPre 1 / 2 / 4: 24 systems of 20^3..60^3 with four
-// right-hand sides 34.7 / 34.7 / 35.9 ms, 17 of 25^3..35^3 4.65 / 4.75 / 5.02,
-// one of 40^3 2.90 / 2.97 / 3.17).
+// enough: a workgroup of systems up to 60^3 has one or two vectors a thread, and a
+// deeper prefetch mostly loads its last one again and holds registers that further
+// workgroups need (kBPre 1 / 2 / 4: 24 systems of 20^3..60^3 with four right-hand
+// sides 34.7 / 34.7 / 35.9 ms, 17 of 25^3..35^3 4.65 / 4.75 / 5.02, one of 40^3
+// 2.90 / 2.97 / 3.17).  A larger system has more (100^3 with four: seven or eight)
+// and gains 2 % at most by four: iteration 105.7 / 105.6 / 103.6 us with four,
+// 54.2 / 54.1 / 53.8 with one.
 constexpr int kBPre = 1;
 template <int R>
 struct BVec {

@@ -92,3 +92,23 @@ def test_mixed_with_rows(fmt, way):
         assert S.report()["path"] == cgmi.CG_PATH_LAUNCHES and info["status"] == cgmi.CG_OK
         assert np.array_equal(m.cpu().numpy(), F.solve_mixed(b, tol=1e-11)[0].cpu().numpy())
         assert np.linalg.norm(m.cpu().numpy() - x) <= 1e-6 * np.linalg.norm(x)
+
+
+@pytest.mark.parametrize("fmt", ["csc", "symcsr"])
+def test_values_that_mixed_precision_refuses(fmt, way):
+    """A diagonal entry that is not positive: the call says so, and the FP64
+    matrix has its new values in every layout all the same."""
+    s = W.fem_p1_system(43, 42, 40, nu_iron=0.5, seed=5)
+    full = (s.rowptr, s.col, s.val)
+    ptr, col, val = W.upper_triangle(*full) if fmt == "symcsr" else full
+    new = val * 1.5
+    line = np.repeat(np.arange(s.n), np.diff(ptr))
+    new[np.nonzero((line == col) & (line == s.n // 2))[0][0]] = -1.0
+    x = to_dev(W.uniform_vector(s.n, seed=6))
+    with cgmi.Solver(fmt, ptr, col, val, mixed=True) as S, cgmi.Solver(fmt, ptr, col, new) as F:
+        with pytest.raises(cgmi.CgError) as e:
+            S.set_values(to_dev(new))
+        assert e.value.status == cgmi.CG_ERR_ARG
+        assert np.array_equal(S.spmv(x).cpu().numpy(), F.spmv(x).cpu().numpy())
+        S.set_values(to_dev(val))
+        assert S.solve_mixed(to_dev(s.b), tol=1e-10)[1]["status"] == cgmi.CG_OK
