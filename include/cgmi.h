@@ -167,8 +167,11 @@ int cg_set_batch(cg_handle *h, int32_t iters_per_launch);
  * device -- the paper moves only the scalars between host and GPU; here the
  * host follows them in a word of pinned memory, written each iteration.  Systems of
  * at most 262 144 rows whose rows are sliced run the whole iteration in one
- * kernel where a workgroup per compute unit has a place on the device (same
- * bits as the launches it takes otherwise).
+ * kernel (same bits as the launches otherwise) where lines hold at most 32
+ * entries (16 beyond 65 536 rows), the rows of each workgroup touch at most 3072
+ * columns (2304 beyond 65 536 rows, 3840 beyond 131 072; cg_analyze_resident)
+ * and a workgroup per compute unit has a place on the device;
+ * cg_get_solve_report tells.
  *   b     device, n float64 (read only)
  *   x     device, n float64: in x0, out the solution / last iterate; a
  *         buffer distinct from b (CG_ERR_ARG otherwise).
@@ -255,9 +258,9 @@ const char *cg_batch_last_error(const cg_batch *h);
 /* y = A x (device pointers, n float64 each, x and y must not overlap):
  * the sparse matrix-vector product of section III in the handle's storage
  * (CSR: one sum per row; symmetric: the stored triangle by rows plus its
- * mirror by columns; CSC, and symmetric systems of at most 262 144 rows: one
- * sum per row of the full rows that the handle lays out beside the format's
- * own plan).  Asynchronous on the handle's stream. */
+ * mirror by columns; CSC on more than one panel, and symmetric systems of at
+ * most 262 144 rows: one sum per row of the full rows that the handle lays out
+ * beside the format's own plan or instead of it).  Asynchronous on the handle's stream. */
 int cg_spmv(cg_handle *h, const double *x, double *y);
 
 /*

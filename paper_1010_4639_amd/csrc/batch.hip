@@ -17,7 +17,7 @@
 // p = r + beta p; the system's lead workgroup publishes r'r and the stop
 // decision), as in the single-system solver.  Instances that stopped are
 // skipped; a system whose instances have all stopped costs only early
-// returns.  Every iteration is reported to the host with the decision
+// returns.  Every fourth iteration is reported to the host with the decision
 // whether any instance still runs (kernels.h, Report).
 #include <hip/hip_runtime.h>
 
