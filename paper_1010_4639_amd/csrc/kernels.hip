@@ -311,8 +311,16 @@ __global__ __launch_bounds__(kBlock) void k_spmv_csr_rows(int nrb, const int2 *_
         __syncthreads();
         if (t < nr) {
             double a = 0.0;
+            int k = lptr[t];
             const int k1 = lptr[t + 1];
-            for (int k = lptr[t]; k < k1; ++k)
+            for (; k + 3 < k1; k += 4) { // four reads of LDS in flight, added in order
+                const double p0 = prod[k], p1 = prod[k + 1], p2 = prod[k + 2], p3 = prod[k + 3];
+                a += p0;
+                a += p1;
+                a += p2;
+                a += p3;
+            }
+            for (; k < k1; ++k)
                 a += prod[k];
             y[r0 + t] = a;
             sig = fma((double)x[r0 + t], a, sig);
