@@ -293,7 +293,16 @@ __global__ __launch_bounds__(kBlock) void k_bspmm(const WgDesc *__restrict__ wgs
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 double a = 0.0;
-                for (int k = k0; k < k1; ++k)
+                int k = k0;
+                for (; k + 3 < k1; k += 4) { // four reads of LDS in flight, added in order
+                    const double *p = prod + r * E + k;
+                    const double p0 = p[0], p1 = p[1], p2 = p[2], p3 = p[3];
+                    a += p0;
+                    a += p1;
+                    a += p2;
+                    a += p3;
+                }
+                for (; k < k1; ++k)
                     a += prod[r * E + k];
                 Q[(size_t)(r0 + t) * R + r] = a;
                 sig[r] = fma(P[(size_t)(r0 + t) * R + r], a, sig[r]);
